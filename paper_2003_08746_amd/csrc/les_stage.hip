@@ -61,10 +61,9 @@
 // Work per thread is independent of the floating-point type T (double for
 // the FP64 path, float for the mixed path); metrics, Q^(0), the stage
 // update, J and all reductions stay in FP64.  The FP32 path has registers
-// and LDS to spare, and spends them on latency: it loads the helper ring one
-// plane ahead and its own column two planes ahead (in phase E, consumed in C
-// of the next plane), and it keeps two LDS Q planes, written at B of
-// alternate planes.  Phase E reads no other LDS array of the current plane
+// and LDS to spare, and spends them on latency: it loads its own column two
+// planes ahead (in phase E, consumed in C of the next plane), and it keeps
+// two LDS Q planes, written at B of alternate planes.  Phase E reads no other LDS array of the current plane
 // at other threads' nodes (p, u, v, w, T are read at neighbours only in C;
 // the node fluxes, radii and sensors are next written in C, after the next
 // plane's first barrier), so the barrier at the end of a plane is not needed
@@ -223,14 +222,21 @@ __device__ __forceinline__ void lds_barrier() {
 // Optional paths of the stage kernel (template bit mask EXT)
 constexpr int kExtSgs = 1;   // dynamic closure coefficients, isotropic SGS stress
 constexpr int kExtAxis = 2;  // the O-grid's polar axis at j = 0
+// an anisotropy exponent other than 1/2: the six inlined pow calls, kept out
+// of the other instantiations, cost them 1,000 static FP64 instructions and
+// 84 spilled scalar registers per plane (345 -> 334 us per FP64 stage at 256 x
+// 128 x 128 without them)
+constexpr int kExtPow = 4;
 
 template <class T, class QI, bool NORM, bool CFL, int EXT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) k_stage(KArgs a, const QI* __restrict__ Qin, const double* Q0, double* Qout,
                                               float* Qsh, const double* __restrict__ dtp, double dt_host,
                                               double alpha, double* __restrict__ part, double* __restrict__ cpart) {
-  // the FP32 path has the registers to prefetch the helper ring one plane
-  // ahead; the FP64 path loads it at phase B (holding it would spill)
-  constexpr bool kPrefetchRing = sizeof(T) == 4;
+  // the helper ring is loaded one plane ahead (in C, consumed in B of the
+  // next plane): 334 -> 316 us per FP64 stage at 256 x 128 x 128, output
+  // bitwise equal.  The FP64 stage with the norms loads it at phase B: there
+  // the five values spill (12 registers)
+  constexpr bool kPrefetchRing = sizeof(T) == 4 || !NORM;
   // the FP32 path also loads the own column two planes ahead (in E)
   constexpr bool kPrefetchQ = sizeof(T) == 4;
   constexpr bool kQ2 = kQBuf<T> == 2;
@@ -508,7 +514,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
         // anisotropic scaling Lam_d = lam_d [1 + sum_e (lam_e / lam_d)^alpha]
         auto aniso_n = [&](int d, int e, int f) -> T {
-          if (P.alpha_half) return lam[d] + sl[d] * (sl[e] + sl[f]);
+          if (!(EXT & kExtPow) || P.alpha_half) return lam[d] + sl[d] * (sl[e] + sl[f]);
           return aniso(lam[d], lam[e], lam[f], P);
         };
         auto node_flux = [&](int e, T H[5]) {
@@ -628,8 +634,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
               if (on_axis) R = 0.0;
               const double qn = q0v[c] - adt * R;
               qnv[c] = qn;
-              if (Qout) sto(Qout + sb + c * fe, n, qn);
-              if (Qsh) sto(Qsh + sb + c * fe, n, (float)qn);
+              if (sizeof(T) == 8 || Qout) sto(Qout + sb + c * fe, n, qn);
+              if (sizeof(T) == 4 && Qsh) sto(Qsh + sb + c * fe, n, (float)qn);
               if (NORM) {
                 n2[c] += R * R;
                 const double a = fabs(R);
@@ -788,14 +794,17 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
   // the optional SGS models (dynamic closure, isotropic SGS stress) and the
   // polar axis run in instantiations of their own, so that each path keeps
   // only the registers it needs
-  const int x = ((sa.P.sgs == 2 || sa.P.CI43 != 0.0) ? kExtSgs : 0) | (sa.axis ? kExtAxis : 0);
+  const int x = !sa.P.alpha_half ? kExtPow | kExtSgs | kExtAxis
+                                 : ((sa.P.sgs == 2 || sa.P.CI43 != 0.0) ? kExtSgs : 0) | (sa.axis ? kExtAxis : 0);
   if ((x & kExtSgs) && sa.P.sgs == 2 && !sa.dyn) return hipErrorInvalidValue;
   switch (x) {
     case 0: return launch_x<T, QI, 0>(st, c, a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
     case kExtSgs: return launch_x<T, QI, kExtSgs>(st, c, a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
     case kExtAxis: return launch_x<T, QI, kExtAxis>(st, c, a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
-    default:
+    case kExtSgs | kExtAxis:
       return launch_x<T, QI, kExtSgs | kExtAxis>(st, c, a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
+    default:
+      return launch_x<T, QI, kExtPow | kExtSgs | kExtAxis>(st, c, a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
   }
 }
 
