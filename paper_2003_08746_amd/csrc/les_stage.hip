@@ -19,55 +19,61 @@
 // block.  Each thread keeps the k-direction stencil of its own column in
 // registers (conserved variables at t-2 .. t+1, primitives at t-1 and t+1,
 // the zeta node flux and the partial residual of the plane below), so the
-// zeta direction needs no LDS.  The in-plane (xi, eta) stencil goes
-// through LDS in three phases per plane, separated by barriers (a third
-// barrier closes the plane in the FP64 path; the FP32 path double-buffers
-// the LDS Q plane instead, see below):
+// zeta direction needs no LDS.  The in-plane (xi, eta) stencil works in three
+// phases per plane with two barriers:
 //   B  fill:  every node of the patch (and a second halo ring along the
-//             axes, written by helper threads) stores Q, p, u, v, w, T;
-//   C  node:  every non-corner node of the patch computes its velocity and
-//             temperature gradient (chain rule through its metrics), the
-//             viscous stress with Sutherland and Smagorinsky viscosity, the
-//             node fluxes it is responsible for, the Turkel-Vatsa
-//             anisotropic spectral radii and the pressure sensors;
-//   E  face:  tile nodes difference the node fluxes, build the four in-plane
-//             dissipation faces from LDS and the zeta face from registers,
-//             and finish the residual and stage update of the plane below
-//             (stage 1 also accumulates R^2 and max |R| per thread; the
-//             block reduces them once, after its last plane).
+//             axes, written by helper threads) stores Q, p, u, v, w, T to LDS;
+//   C  node:  every node of the patch computes its velocity and temperature
+//             gradient (chain rule through its metrics), the viscous stress
+//             with Sutherland and Smagorinsky viscosity, the node fluxes, the
+//             Turkel-Vatsa anisotropic spectral radii and the pressure
+//             sensors; then the xi part of the residual, whose neighbours are
+//             adjacent lanes of the same wave (a tile row is 32 lanes): node
+//             fluxes, radii, sensors and the lower face by lane shifts;
+//   E  face:  the eta part through LDS, the zeta face from registers, and the
+//             residual and stage update of the plane below (stage 1 also
+//             accumulates R^2 and max |R| per thread; the block reduces them
+//             once, after its last plane).  FP64 evaluates each eta face once:
+//             the row below it leaves it in LDS, and the row above adds it in
+//             phase C of the next plane, before its residual is finished.
+// The LDS Q plane is double-buffered, so E of one plane and B of the next
+// need no barrier between them.  (Before: xi through LDS too, one Q plane and
+// a third barrier; the 25 KB of the xi arrays hold the second plane now.)
 // Memory.  Wave w owns patch rows 2w and 2w+1 (rows 4w .. 4w+3 with the
-// 16-wide patch the shape constants also allow).  The ten metric fields and
-// Q^(0) of those rows are wave-private, so they travel as asynchronous
-// global->LDS copies (16 bytes per lane) into per-wave LDS blocks with no
-// barrier: Q^(0) of the plane being finished is issued at the start of C
-// and read at the start of E; the next plane's metrics are issued right
-// after that read and land during E (E stores nothing to LDS, so no LDS
-// store has to wait for them).  The block barriers order LDS data only:
-// a full __syncthreads would also drain every outstanding global load,
-// store and copy of the wave, so each barrier would wait out the latency of
-// what was just issued.  Reads of copied blocks are preceded by counted
-// vmcnt waits instead.  The own-column loads are branch-free (threads past
-// the padded box load a clamped node), which lets the compiler see that
-// they have completed and keeps it from adding full vmcnt waits of its own.
+// 16-wide patch the shape constants also allow).  The ten metric fields of
+// those rows are wave-private, so they travel as asynchronous global->LDS
+// copies (16 bytes per lane) into per-wave LDS blocks with no barrier.  The
+// copies of the next plane's metrics and the loads of the own column two
+// planes ahead are issued one at a time between the sub-steps of C, the
+// helper ring of the next plane at its start, Q^(0) of the plane being
+// finished at its end.  The block barriers order LDS data only: a full
+// __syncthreads would also drain every outstanding global load, store and
+// copy of the wave.  All loads of a plane are waited for once, before the
+// stage update's stores and on every path, so that no later use of a loaded
+// value has to wait for those stores (the counter of outstanding operations
+// is in order).  The own-column loads are branch-free (threads past the
+// padded box load a clamped node).
 // The flow constants are read from the kernel-argument segment where they
 // are used, instead of occupying scalar registers across the loop.  Divisions and square roots
 // use short Newton-refined sequences (valid for the positive, normal
 // arguments met here).  Scheduling fences split phases C and E into short
-// regions (gradient / stress / spectral radii / each node flux; each
-// dissipation direction / zeta face / residual): without them the scheduler
-// hoists LDS reads of later regions over the FP64 work of earlier ones and
-// the live ranges exceed the 256 registers of a two-wave-per-SIMD launch.
+// regions: without them the scheduler hoists LDS reads of later regions over
+// the FP64 work of earlier ones and the live ranges exceed the 256 registers
+// of a two-wave-per-SIMD launch.
+//
+// What bounds it, 256 x 128 x 128 FP64 (268 us a stage, 346 before): two waves
+// per SIMD (LDS and registers allow no more) spend 6,500 cycles of a plane's
+// 10,800 issuing vector instructions, most of the rest at the two barriers,
+// where the older wave of each SIMD waits for the younger; the core runs at
+// 2.0 GHz under this load (2.36 GHz on a block of 32^3).  At 800 x 500 x 500 the
+// traffic between L2 and memory is as near.
 //
 // Work per thread is independent of the floating-point type T (double for
 // the FP64 path, float for the mixed path); metrics, Q^(0), the stage
-// update, J and all reductions stay in FP64.  The FP32 path has registers
-// and LDS to spare, and spends them on latency: it loads its own column two
-// planes ahead (in phase E, consumed in C of the next plane), and it keeps
-// two LDS Q planes, written at B of alternate planes.  Phase E reads no other LDS array of the current plane
-// at other threads' nodes (p, u, v, w, T are read at neighbours only in C;
-// the node fluxes, radii and sensors are next written in C, after the next
-// plane's first barrier), so the barrier at the end of a plane is not needed
-// there.  The FP64 path has neither the registers nor the 24 KB of LDS.
+// update, J and all reductions stay in FP64.  The FP32 path keeps the order of
+// operations that its results were first defined by (its rounding is visible
+// at 1e-8), the FP64 path works with twice the residual and joins the
+// pressure to the normal stresses.
 #include <stdlib.h>
 
 #include "les_stage.hpp"
@@ -113,20 +119,16 @@ struct KArgs {
   int nxcd;             // XCDs of the device
 };
 
-// The FP32 path has the LDS for two Q planes (written at B of alternate
-// planes), which removes the barrier at the end of a plane: the only LDS
-// values that E reads at other threads' nodes are Q.
-template <class T>
-constexpr int kQBuf = sizeof(T) == 4 ? 2 : 1;
+// Two Q planes, written at B of alternate planes: the only LDS values that E
+// reads at other threads' nodes and B of the next plane would overwrite.
 template <class T>
 struct Smem {
-  T q[kQBuf<T>][5][EY][EX];
+  T q[2][5][EY][EX];
   T p[EY][EX];
   T u[EY][EX], v[EY][EX], w[EY][EX], tem[EY][EX];
-  T hx[5][TY][BX];  // xi node flux, patch rows 1..TY
   T hy[5][BY][TX];  // eta node flux, patch columns 1..TX
-  T lx[TY][BX], nx[TY][BX];
   T ly[BY][TX], ny[BY][TX];
+  T dy[sizeof(T) == 8 ? 5 : 0][BY - 1][TX];  // FP64: dissipation of the eta face above patch rows 0..BY-2
 };
 
 // Global accesses use a uniform (scalar) base per field plus a 32-bit
@@ -146,20 +148,29 @@ __device__ __forceinline__ void load_q(const QI* __restrict__ Q, long long fe, u
   for (int c = 0; c < 5; ++c) q[c] = (T)ldo(Q + c * fe, off);
 }
 
-// Dissipation flux of the face between nodes a and b = a + 1 along a line
-// (am = a - 1, bp = b + 1), given the node spectral radii and sensors.
+// Dissipation of the face between nodes a and b = a + 1 along a line
+// (am = a - 1, bp = b + 1), given the node spectral radii and sensors: the
+// bracket X = eps2 dQ - eps4 d3Q; returns the radius factor, so that the flux
+// (FP64: twice the flux, see kTwice) is the factor times X.
 template <class T>
-__device__ __forceinline__ void face_diss(const Phys& P, T La, T Lb, T na, T nb, const T qam[5], const T qa[5],
-                                          const T qb[5], const T qbp[5], T D[5]) {
+__device__ __forceinline__ T face_bracket(const Phys& P, T La, T Lb, T na, T nb, const T qam[5], const T qa[5],
+                                          const T qb[5], const T qbp[5], T X[5]) {
   const T e2 = T(P.k2) * tmax(na, nb);
   const T e4 = tmax(T(0), T(P.k4) - e2);
-  const T Lf = T(0.5) * (La + Lb);
 #pragma unroll
   for (int c = 0; c < 5; ++c) {
     const T d1 = qb[c] - qa[c];
     const T d3 = qbp[c] - T(3) * qb[c] + T(3) * qa[c] - qam[c];
-    D[c] = Lf * (e2 * d1 - e4 * d3);
+    X[c] = e2 * d1 - e4 * d3;
   }
+  return sizeof(T) == 8 ? La + Lb : T(0.5) * (La + Lb);
+}
+template <class T>
+__device__ __forceinline__ void face_diss(const Phys& P, T La, T Lb, T na, T nb, const T qam[5], const T qa[5],
+                                          const T qb[5], const T qbp[5], T D[5]) {
+  const T Lf = face_bracket(P, La, Lb, na, nb, qam, qa, qb, qbp, D);
+#pragma unroll
+  for (int c = 0; c < 5; ++c) D[c] *= Lf;
 }
 
 // Per-wave reduction of the threads' R^2 sums and |R| maxima into the ten
@@ -219,6 +230,25 @@ __device__ __forceinline__ void lds_barrier() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// The value of the lane before / after this one (DPP wave shifts by one lane;
+// the end lanes read 0).
+__device__ __forceinline__ float lane_prev(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_next(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_prev(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_next(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
 // Optional paths of the stage kernel (template bit mask EXT)
 constexpr int kExtSgs = 1;   // dynamic closure coefficients, isotropic SGS stress
 constexpr int kExtAxis = 2;  // the O-grid's polar axis at j = 0
@@ -232,18 +262,14 @@ template <class T, class QI, bool NORM, bool CFL, int EXT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) k_stage(KArgs a, const QI* __restrict__ Qin, const double* Q0, double* Qout,
                                               float* Qsh, const double* __restrict__ dtp, double dt_host,
                                               double alpha, double* __restrict__ part, double* __restrict__ cpart) {
-  // the helper ring is loaded one plane ahead (in C, consumed in B of the
-  // next plane): 334 -> 316 us per FP64 stage at 256 x 128 x 128, output
-  // bitwise equal.  The FP64 stage with the norms loads it at phase B: there
-  // the five values spill (12 registers)
-  constexpr bool kPrefetchRing = sizeof(T) == 4 || !NORM;
-  // the FP32 path also loads the own column two planes ahead (in E)
-  constexpr bool kPrefetchQ = sizeof(T) == 4;
-  constexpr bool kQ2 = kQBuf<T> == 2;
+  // FP64: phases C and E work with twice the residual, so that the halves of
+  // the central differences and face means are applied once, through J / 2
+  constexpr bool kTwice = sizeof(T) == 8;
+  constexpr T kHalf = kTwice ? T(1) : T(0.5);
   __shared__ Smem<T> s;
   __shared__ double mbw[NW][10][RPW][BX];  // per-wave metrics rows of the current plane
-  __shared__ double q0w[NW][5][RPW][BX];   // per-wave Q^(0) rows of the plane being finished
-  static_assert(sizeof(Smem<T>) + sizeof(mbw) + sizeof(q0w) <= 163840 / BPC, "LDS of BPC blocks per CU");
+  __shared__ double red_s[NW][10];         // block reductions
+  static_assert(sizeof(Smem<T>) + sizeof(mbw) + sizeof(red_s) <= 163840 / BPC, "LDS of BPC blocks per CU");
   const Layout& L = a.L;
   // a (the first kernel argument) sits at the start of the kernel-argument
   // segment; the loop re-reads the flow constants through this pointer
@@ -337,9 +363,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int i = i0 - 1 + tx, j = j0 - 1 + ty;
     const bool load_ok = i <= L.ni + 1 && j <= L.nj + 1;
     const bool node_ok = load_ok && i <= L.ni && j <= L.nj && !(xh && yh);
-    const bool need_x = node_ok && !yh;  // xi node flux / sensor needed here
     const bool need_y = node_ok && !xh;  // eta node flux / sensor needed here
     const bool out_ok = !xh && !yh && i < L.ni && j < L.nj;
+    const bool wave_in = __builtin_amdgcn_ballot_w64(load_ok) != 0;  // some row of the wave is in the padded box
+    const bool fy_ok = !xh && ty < BY - 1 && i < L.ni && j < L.nj;  // eta face (j, j + 1) of a tile column
+    const bool fx_ok = !yh && tx < BX - 1 && i < L.ni && j < L.nj;  // xi face (i, i + 1) of a tile row
     const int hi = i0 - 2 + hx2, hj = j0 - 2 + hy2;
     const bool h_ok = tid < NH2 && hi <= L.ni + 1 && hj <= L.nj + 1;
     // element offsets of nodes (i, j, kr) and (hi, hj, kr) from the segment
@@ -385,10 +413,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     dma_rows<10>((const char*)(kp->M + lane_el + (long long)(kb - 1) * L.sk), fstep2, &mbw[wave][0][0][0], lane);
     load_q<T>(Qs, fe, qcol, qm1);
     load_q<T>(Qs, fe, qcol + sk, qw);
-    if (kPrefetchQ) load_q<T>(Qs, fe, qcol + 2 * sk, qa);
+    load_q<T>(Qs, fe, qcol + 2 * sk, qa);
     prims(kp->P, qm1, um1, pm1);
     prims(kp->P, qw, up1, pp1);  // plane kb-1, written at the first B
-    if (kPrefetchRing && h_ok) load_q<T>(Qs, fe, hcol + sk, hq);
+    if (h_ok) load_q<T>(Qs, fe, hcol + sk, hq);
+    wait_vm<0>();  // the first metric rows (later ones are waited for before each stage update)
 
     for (int t = kb - 1; t <= ke; ++t) {
       const unsigned nt = col + (unsigned)(t - kr) * sk;
@@ -399,10 +428,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // the first and last plane of a segment only provide zeta quantities
       // of the tile columns; their in-plane fluxes and residual are not needed
       const bool inner = t >= kb && t < ke;
-      const bool nx_t = need_x && inner, ny_t = need_y && inner;
-      const bool node_t = inner ? node_ok : out_ok;
-      T(*const sq)[EY][EX] = s.q[kQ2 ? qbuf : 0];
-      if (kQ2) qbuf ^= 1;
+      T(*const sq)[EY][EX] = s.q[qbuf];
+      qbuf ^= 1;
 
       // ---- B: fill LDS plane t ----
       if (load_ok) {
@@ -411,17 +438,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         s.p[ey][ex] = pp1;
         s.u[ey][ex] = up1[0]; s.v[ey][ex] = up1[1]; s.w[ey][ex] = up1[2]; s.tem[ey][ex] = up1[3];
       }
-      if (!kPrefetchQ) load_q<T>(Qs, fe, qcol + (unsigned)(t + 1 - kr) * sk, qa);  // plane t+1 of the own column
       if (h_ok) {
         T hu[4], hp;
-        if (!kPrefetchRing) load_q<T>(Qs, fe, hcol + (unsigned)(t - kr) * sk, hq);
         prims(P, hq, hu, hp);
 #pragma unroll
         for (int c = 0; c < 5; ++c) sq[c][hy2][hx2] = hq[c];
         s.p[hy2][hx2] = hp;
         s.u[hy2][hx2] = hu[0]; s.v[hy2][hx2] = hu[1]; s.w[hy2][hx2] = hu[2]; s.tem[hy2][hx2] = hu[3];
       }
-      wait_vm<0>();  // metrics of plane t, helper ring, plane t+1 of the own column
       lds_barrier();
 
       // ---- C: node work at plane t ----
@@ -436,40 +460,83 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int c = 0; c < 5; ++c) sq[c][ey][ex] = T(2) * sq[c][ey + 1][ex] - sq[c][ey + 2][ex];
       }
       prims(P, qa, up1, pp1);  // plane t+1 of the own column
-      // Q^(0) rows of the plane finished in this iteration (t-1), needed in E
-      if (t > kb)
-        dma_rows<5>((const char*)(Q0 + lane_el + (long long)(t - 1) * L.sk), fstep2, &q0w[wave][0][0][0], lane);
       T hz[5] = {0, 0, 0, 0, 0};
       T lz = 0, nz = 0;
       double Jn = 0.0;
       T mt[9];
-      Jn = mbw[wave][9][ty1][tx];
-#pragma unroll
-      for (int c = 0; c < 9; ++c) mt[c] = (T)mbw[wave][c][ty1][tx];
-      wait_lgkm_all();  // the wave's metric reads are done before its copies overwrite them
-      // issue the next plane's loads now so that they land during C and E:
-      // helper ring (FP32 path), then the wave's metric rows (five copies)
-      if (kPrefetchRing && h_ok && t < ke) load_q<T>(Qs, fe, hcol + (unsigned)(t + 1 - kr) * sk, hq);
-      if (node_t) {
-        const T Jt = (T)Jn;
+      {
+        // (read by hand, with the wait for the reads in the same block: the
+        // compiler would wait for every outstanding copy, load and store of
+        // the wave before an LDS read of a block that copies write; the
+        // copies of this plane were waited for above.  The reads are done
+        // before the next plane's copies overwrite the block.)
+        typedef double d2 __attribute__((ext_vector_type(2)));
+        d2 m0, m1, m2, m3, m4;
+        const unsigned la =
+            (unsigned)(uintptr_t)(__attribute__((address_space(3))) const double*)&mbw[wave][0][ty1][tx];
+        asm volatile(
+            "ds_read2st64_b64 %0, %5 offset0:0 offset1:1\n"
+            "ds_read2st64_b64 %1, %5 offset0:2 offset1:3\n"
+            "ds_read2st64_b64 %2, %5 offset0:4 offset1:5\n"
+            "ds_read2st64_b64 %3, %5 offset0:6 offset1:7\n"
+            "ds_read2st64_b64 %4, %5 offset0:8 offset1:9\n"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(m0), "=&v"(m1), "=&v"(m2), "=&v"(m3), "=&v"(m4)
+            : "v"(la)
+            : "memory");
+        mt[0] = (T)m0.x; mt[1] = (T)m0.y; mt[2] = (T)m1.x; mt[3] = (T)m1.y; mt[4] = (T)m2.x;
+        mt[5] = (T)m2.y; mt[6] = (T)m3.x; mt[7] = (T)m3.y; mt[8] = (T)m4.x;
+        Jn = m4.y;
+      }
+      const char* const msrc = (const char*)(kq->M + lane_el + (long long)(t + 1) * L.sk);
+      double* const mdst = &mbw[wave][0][0][0];
+      // Loads for the following planes: the helper ring of t+1, then, after each
+      // sub-step q = 1..5, one copy of the wave's metric rows of t+1 and one
+      // value of the own column at t+2.  Issued together they fill the memory
+      // pipeline's queue and both waves of a SIMD wait to issue; spread over
+      // the node work that wait is hidden (256 x 128 x 128: 303 -> 270 us per
+      // FP64 stage, 253 -> 239 us mixed).  At t = ke nothing more is needed:
+      // FP64 skips the loads; FP32 issues them all the same (planes ke + 1 at
+      // most, inside the padded box), because the branches between its
+      // sub-steps cost more (247 against 239 us) than the loads.
+      const unsigned qoff2 = qcol + (unsigned)(min(t + 2, ke + 1) - kr) * sk;
+      auto load_ahead = [&](int q) {
+        if (sizeof(T) == 4 || t < ke) {
+          if (q == 0) {
+            if (h_ok) load_q<T>(Qs, fe, hcol + (unsigned)(t + 1 - kr) * sk, hq);
+          } else {
+            __builtin_amdgcn_global_load_lds((const void*)(msrc + (q - 1) * fstep2),
+                                             (__attribute__((address_space(3))) void*)(mdst + (q - 1) * 128), 16, 0, 0);
+            qn[q - 1] = (T)ldo(Qs + (q - 1) * fe, qoff2);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      load_ahead(0);
+      T hxf[5] = {0, 0, 0, 0, 0}, lx = 0, nx = 0;  // xi node flux, radius and sensor
+      // (every lane of such a wave does the node work: the values of lanes that
+      // are no node are never published, and the loads between the sub-steps
+      // need the whole wave)
+      if (wave_in) {
+        const T Jh = T(0.5) * (T)Jn;
         T g[4][3];
         {
           // derivatives along xi, eta (LDS) and zeta (registers), chain rule
           const T(*F[4])[EX] = {s.u, s.v, s.w, s.tem};
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const T dx = T(0.5) * (F[q][ey][ex + 1] - F[q][ey][ex - 1]);
-            const T dy = T(0.5) * (F[q][ey + 1][ex] - F[q][ey - 1][ex]);
-            const T dz = T(0.5) * (up1[q] - um1[q]);
+            // (the halves of the central differences are in Jh)
+            const T dx = F[q][ey][ex + 1] - F[q][ey][ex - 1];
+            const T dy = F[q][ey + 1][ex] - F[q][ey - 1][ex];
+            const T dz = up1[q] - um1[q];
 #pragma unroll
-            for (int x = 0; x < 3; ++x) g[q][x] = Jt * (mt[x] * dx + mt[3 + x] * dy + mt[6 + x] * dz);
+            for (int x = 0; x < 3; ++x) g[q][x] = Jh * (mt[x] * dx + mt[3 + x] * dy + mt[6 + x] * dz);
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
+        load_ahead(1);
         const T s11 = g[0][0], s22 = g[1][1], s33 = g[2][2];
-        const T s12 = T(0.5) * (g[0][1] + g[1][0]);
-        const T s13 = T(0.5) * (g[0][2] + g[2][0]);
-        const T s23 = T(0.5) * (g[1][2] + g[2][1]);
+        // off-diagonal strains (FP64: twice)
+        const T w12 = kHalf * (g[0][1] + g[1][0]), w13 = kHalf * (g[0][2] + g[2][0]), w23 = kHalf * (g[1][2] + g[2][1]);
         const T skk3 = (s11 + s22 + s33) * T(1.0 / 3.0);
         const T rho = sq[0][ey][ex];
         const T u = s.u[ey][ex], vv = s.v[ey][ex], w = s.w[ey][ex];
@@ -477,7 +544,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const T mu = sutherland_fast(tn, P);
         T mus = T(0), kaps = T(0), pis = T(0);
         if (P.sgs) {
-          const T ss = s11 * s11 + s22 * s22 + s33 * s33 + T(2) * (s12 * s12 + s13 * s13 + s23 * s23);
+          const T ss = s11 * s11 + s22 * s22 + s33 * s33 + T(kTwice ? 0.5 : 2.0) * (w12 * w12 + w13 * w13 + w23 * w23);
           T d2 = (T)icbrt(Jn);  // (1/J)^(1/3)
           d2 *= d2;
           const T rd = rho * d2 * sqrt_nn(T(2) * ss);
@@ -485,21 +552,22 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             mus = T(P.Cs2) * rd;
             kaps = mus * T(P.Cp_over_Prsgs);
           } else {  // dynamic coefficients of this column
-            const long long cc = dyn_col(kq->L, i, j);
+            const long long cc = dyn_col(kq->L, min(i, L.ni + 1), min(j, L.nj + 1));
             mus = T(kq->dyn[cc]) * rd;
             kaps = T(P.Cp) * T(kq->dyn[dyn_ncol(kq->L) + cc]) * rd;
           }
           // isotropic SGS stress: sigma_kk / 3, added to the pressure of the fluxes
           if ((EXT & kExtSgs) && P.CI43 != 0.0) pis = T(P.CI43) * rho * d2 * ss;
         }
-        const T mt2 = T(2) * (mu + mus);
+        const T mt1 = mu + mus, mt2 = T(2) * mt1;
         const T t11 = mt2 * (s11 - skk3), t22 = mt2 * (s22 - skk3), t33 = mt2 * (s33 - skk3);
-        const T t12 = mt2 * s12, t13 = mt2 * s13, t23 = mt2 * s23;
+        const T mtw = kTwice ? mt1 : mt2;
+        const T t12 = mtw * w12, t13 = mtw * w13, t23 = mtw * w23;
         const T kap = mu * T(P.Cp_over_Pr) + kaps;
         const T th0 = u * t11 + vv * t12 + w * t13 + kap * g[3][0];
         const T th1 = u * t12 + vv * t22 + w * t23 + kap * g[3][1];
         const T th2 = u * t13 + vv * t23 + w * t33 + kap * g[3][2];
-        __builtin_amdgcn_sched_barrier(0);
+        load_ahead(2);
         const T p = s.p[ey][ex];
         const T pe = (EXT & kExtSgs) ? p + pis : p;  // pressure of the fluxes
         const T c2 = T(P.gamma_R) * tn;  // c^2 = gamma p / rho = gamma R T
@@ -517,27 +585,31 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
           if (!(EXT & kExtPow) || P.alpha_half) return lam[d] + sl[d] * (sl[e] + sl[f]);
           return aniso(lam[d], lam[e], lam[f], P);
         };
+        const T e11 = pe - t11, e22 = pe - t22, e33 = pe - t33;
         auto node_flux = [&](int e, T H[5]) {
           const T mx = mt[3 * e], my = mt[3 * e + 1], mz = mt[3 * e + 2];
           const T Ue = U[e];
           H[0] = rho * Ue;
-          H[1] = sq[1][ey][ex] * Ue + mx * pe - (mx * t11 + my * t12 + mz * t13);
-          H[2] = sq[2][ey][ex] * Ue + my * pe - (mx * t12 + my * t22 + mz * t23);
-          H[3] = sq[3][ey][ex] * Ue + mz * pe - (mx * t13 + my * t23 + mz * t33);
+          if (kTwice) {  // pressure joined to the normal stresses: six operations fewer per direction
+            H[1] = sq[1][ey][ex] * Ue + mx * e11 - my * t12 - mz * t13;
+            H[2] = sq[2][ey][ex] * Ue + my * e22 - mx * t12 - mz * t23;
+            H[3] = sq[3][ey][ex] * Ue + mz * e33 - mx * t13 - my * t23;
+          } else {
+            H[1] = sq[1][ey][ex] * Ue + mx * pe - (mx * t11 + my * t12 + mz * t13);
+            H[2] = sq[2][ey][ex] * Ue + my * pe - (mx * t12 + my * t22 + mz * t23);
+            H[3] = sq[3][ey][ex] * Ue + mz * pe - (mx * t13 + my * t23 + mz * t33);
+          }
           H[4] = (sq[4][ey][ex] + pe) * Ue - (mx * th0 + my * th1 + mz * th2);
         };
-        __builtin_amdgcn_sched_barrier(0);
-        if (nx_t) {
-          T H[5];
-          node_flux(0, H);
-#pragma unroll
-          for (int q = 0; q < 5; ++q) s.hx[q][ty - 1][tx] = H[q];
-          s.lx[ty - 1][tx] = aniso_n(0, 1, 2);
+        load_ahead(3);
+        if (inner) {
+          node_flux(0, hxf);
+          lx = aniso_n(0, 1, 2);
           const T pa = s.p[ey][ex + 1], pb = s.p[ey][ex - 1];
-          s.nx[ty - 1][tx] = fabs(pa - T(2) * p + pb) * rcp_nr(pa + T(2) * p + pb);
+          nx = fabs(pa - T(2) * p + pb) * rcp_nr(pa + T(2) * p + pb);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (ny_t) {
+        load_ahead(4);
+        if (need_y && inner) {
           T H[5];
           node_flux(1, H);
           // on the polar axis eta/J = 0: the eta node flux and radius take
@@ -549,138 +621,185 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
           const T pa = s.p[ey + 1][ex], pb = s.p[ey - 1][ex];
           s.ny[ty][tx - 1] = fabs(pa - T(2) * p + pb) * rcp_nr(pa + T(2) * p + pb);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (out_ok) {
+        load_ahead(5);
+        {
           node_flux(2, hz);
           lz = aniso_n(2, 0, 1);
           nz = fabs(pp1 - T(2) * p + pm1) * rcp_nr(pp1 + T(2) * p + pm1);
         }
       }
-      lds_barrier();
-
-      double q0v[5] = {0, 0, 0, 0, 0};
-      if (t > kb) {
-        wait_vm<0>();  // the Q^(0) copies (issued in C)
+      if (kTwice && t > kb && out_ok) {  // plane t-1's eta face below this row
 #pragma unroll
-        for (int c = 0; c < 5; ++c) q0v[c] = q0w[wave][c][ty1][tx];
+        for (int c = 0; c < 5; ++c) racc[c] += s.dy[c][ty - 1][tx - 1];
       }
-      // the wave's metric rows of the next plane, landing during E (which
-      // stores nothing to LDS); read at C of the next plane
-      if (t < ke)
-        dma_rows<10>((const char*)(kq->M + lane_el + (long long)(t + 1) * L.sk), fstep2, &mbw[wave][0][0][0], lane);
-      if (kPrefetchQ && t < ke) load_q<T>(Qs, fe, qcol + (unsigned)(t + 2 - kr) * sk, qn);  // consumed at C of t+1
-
-      // ---- E: residual (tile nodes) ----
-      if (out_ok) {
-        const int cx = tx - 1, cy = ty - 1;  // tile-local column / row
-        T r[5] = {0, 0, 0, 0, 0};
-        if (inner) {
-          // central differences of the in-plane node fluxes
+      // xi direction of the residual: a tile row is 32 consecutive lanes of one
+      // wave, so the neighbours' node fluxes, radii and sensors and the face
+      // on the lower side come from the adjacent lanes
+      T r[5] = {0, 0, 0, 0, 0}, rd[5] = {0, 0, 0, 0, 0};  // FP64: r; FP32: flux difference r, dissipation rd
+      if (inner) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int q = 0; q < 5; ++q)
-            r[q] = T(0.5) * (s.hx[q][cy][tx + 1] - s.hx[q][cy][tx - 1]) +
-                   T(0.5) * (s.hy[q][ty + 1][cx] - s.hy[q][ty - 1][cx]);
-          // in-plane dissipation faces
-          T q_a[5], q_b[5], q_c[5], q_d[5], q_e[5], D1[5], D0[5];
+        for (int q = 0; q < 5; ++q) r[q] = kHalf * (lane_next(hxf[q]) - lane_prev(hxf[q]));
+        const T lxn = lane_next(lx), nxn = lane_next(nx);
+        T X[5] = {0, 0, 0, 0, 0}, Lf = 0;
+        if (fx_ok) {
+          T q_b[5], q_c[5], q_d[5], q_e[5];
 #pragma unroll
           for (int c = 0; c < 5; ++c) {
-            q_a[c] = sq[c][ey][ex - 2]; q_b[c] = sq[c][ey][ex - 1]; q_c[c] = sq[c][ey][ex];
+            q_b[c] = sq[c][ey][ex - 1]; q_c[c] = sq[c][ey][ex];
             q_d[c] = sq[c][ey][ex + 1]; q_e[c] = sq[c][ey][ex + 2];
           }
-          face_diss(P, s.lx[cy][tx], s.lx[cy][tx + 1], s.nx[cy][tx], s.nx[cy][tx + 1], q_b, q_c, q_d, q_e, D1);
-          face_diss(P, s.lx[cy][tx - 1], s.lx[cy][tx], s.nx[cy][tx - 1], s.nx[cy][tx], q_a, q_b, q_c, q_d, D0);
+          Lf = face_bracket(P, lx, lxn, nx, nxn, q_b, q_c, q_d, q_e, X);
+        }
 #pragma unroll
-          for (int c = 0; c < 5; ++c) r[c] -= D1[c] - D0[c];
-          __builtin_amdgcn_sched_barrier(0);
+        for (int c = 0; c < 5; ++c) {
+          const T D = Lf * X[c], Dm = lane_prev(D);
+          if (kTwice)
+            r[c] -= D - Dm;
+          else
+            rd[c] = fma(Lf, X[c], -Dm);
+        }
+      }
+      double q0v[5] = {0, 0, 0, 0, 0};
+      if (t > kb && out_ok) {
 #pragma unroll
-          for (int c = 0; c < 5; ++c) {
-            q_a[c] = sq[c][ey - 2][ex]; q_b[c] = sq[c][ey - 1][ex];
-            q_d[c] = sq[c][ey + 1][ex]; q_e[c] = sq[c][ey + 2][ex];
+        for (int c = 0; c < 5; ++c) q0v[c] = ldo(Q0 + sb + c * fe, nt - sk);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      lds_barrier();
+
+      // ---- E: residual (tile nodes) ----
+      if (kTwice && inner && fy_ok) {
+        // FP64: the eta face above this row, subtracted from this row's
+        // residual and left in LDS for the row above, which adds it in phase C
+        // of the next plane
+        const int cx = tx - 1;
+        T q_b[5], q_c[5], q_d[5], q_e[5], D1[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          q_b[c] = sq[c][ey - 1][ex]; q_c[c] = sq[c][ey][ex];
+          q_d[c] = sq[c][ey + 1][ex]; q_e[c] = sq[c][ey + 2][ex];
+        }
+        face_diss(P, s.ly[ty][cx], s.ly[ty + 1][cx], s.ny[ty][cx], s.ny[ty + 1][cx], q_b, q_c, q_d, q_e, D1);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          s.dy[c][ty][cx] = D1[c];
+          r[c] -= D1[c];
+        }
+      }
+      if (out_ok) {
+        const int cx = tx - 1;  // tile-local column
+        if (inner) {
+          // eta direction: central difference of the node fluxes (FP32: and
+          // both dissipation faces, in the order of operations that the
+          // mixed path's results are defined by)
+#pragma unroll
+          for (int q = 0; q < 5; ++q) {
+            r[q] += kHalf * (s.hy[q][ty + 1][cx] - s.hy[q][ty - 1][cx]);
+            if (!kTwice) r[q] -= rd[q];
           }
-          face_diss(P, s.ly[ty][cx], s.ly[ty + 1][cx], s.ny[ty][cx], s.ny[ty + 1][cx], q_b, q_c, q_d, q_e, D1);
-          face_diss(P, s.ly[ty - 1][cx], s.ly[ty][cx], s.ny[ty - 1][cx], s.ny[ty][cx], q_a, q_b, q_c, q_d, D0);
-#pragma unroll
-          for (int c = 0; c < 5; ++c) r[c] -= D1[c] - D0[c];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // CFL only: the nine metric terms of the node finished in this
-        // iteration (plane t-1), read back through the caches (they were
-        // copied to LDS two planes ago); consumed after the update
-        double cm[9];
-        if (CFL) {
-          const unsigned n = (out_ok && t > kb) ? nt - sk : qcol;
-#pragma unroll
-          for (int c = 0; c < 9; ++c) cm[c] = ldo(kq->M + sb + c * fe, n);
-        }
-        if (t >= kb) {
-          // zeta face t - 1/2 between plane t-1 and plane t
-          T qc[5], D[5], fz[5];
-#pragma unroll
-          for (int c = 0; c < 5; ++c) qc[c] = sq[c][ey][ex];
-          face_diss(P, lz_prev, lz, nz_prev, nz, qm2, qm1, qc, qa, D);
-#pragma unroll
-          for (int c = 0; c < 5; ++c) fz[c] = T(0.5) * (hz_prev[c] + hz[c]) - D[c];
-          __builtin_amdgcn_sched_barrier(0);
-          if (t > kb) {
-            // residual of plane t-1 and its stage update
-            const int k = t - 1;
-            const unsigned n = nt - sk;
-            double qnv[5];
-            const bool on_axis = (EXT & kExtAxis) && kq->axis && j == 0;  // advanced by the centerline condition
+          if (!kTwice) {
+            T q_a[5], q_b[5], q_c[5], q_d[5], q_e[5], D1[5], D0[5];
 #pragma unroll
             for (int c = 0; c < 5; ++c) {
-              double R = J_prev * (double)(racc[c] + fz[c]);
-              if (kq->f && i == kq->i_f) R -= kq->f[((long long)c * kq->L.nk + k) * kq->L.nj + j];
-              if (on_axis) R = 0.0;
-              const double qn = q0v[c] - adt * R;
-              qnv[c] = qn;
-              if (sizeof(T) == 8 || Qout) sto(Qout + sb + c * fe, n, qn);
-              if (sizeof(T) == 4 && Qsh) sto(Qsh + sb + c * fe, n, (float)qn);
-              if (NORM) {
-                n2[c] += R * R;
-                const double a = fabs(R);
-                nm[c] = (a > nm[c] || a != a) ? a : nm[c];  // NaN wins so that it is reported
-              }
+              q_a[c] = sq[c][ey - 2][ex]; q_b[c] = sq[c][ey - 1][ex]; q_c[c] = sq[c][ey][ex];
+              q_d[c] = sq[c][ey + 1][ex]; q_e[c] = sq[c][ey + 2][ex];
             }
-            if (CFL && !on_axis) cmin = min_nan(cmin, cfl_local(qnv[0], qnv[1], qnv[2], qnv[3], qnv[4], J_prev, cm, kq->P));
+            face_diss(P, s.ly[ty][cx], s.ly[ty + 1][cx], s.ny[ty][cx], s.ny[ty + 1][cx], q_b, q_c, q_d, q_e, D1);
+            face_diss(P, s.ly[ty - 1][cx], s.ly[ty][cx], s.ny[ty - 1][cx], s.ny[ty][cx], q_a, q_b, q_c, q_d, D0);
+#pragma unroll
+            for (int c = 0; c < 5; ++c) r[c] -= D1[c] - D0[c];
           }
-#pragma unroll
-          for (int c = 0; c < 5; ++c) racc[c] = r[c] - fz[c];
-        } else {
-#pragma unroll
-          for (int c = 0; c < 5; ++c) racc[c] = r[c];
         }
-#pragma unroll
-        for (int c = 0; c < 5; ++c) hz_prev[c] = hz[c];
-        lz_prev = lz;
-        nz_prev = nz;
-        J_prev = Jn;
       }
-      // ---- shift the column queues (plane t values from LDS) ----
+      __builtin_amdgcn_sched_barrier(0);
+      // CFL only: the nine metric terms of the node finished in this
+      // iteration (plane t-1), read back through the caches (they were
+      // copied to LDS two planes ago); consumed after the update
+      double cm[9];
+      if (CFL) {
+        const unsigned n = (out_ok && t > kb) ? nt - sk : qcol;
+#pragma unroll
+        for (int c = 0; c < 9; ++c) cm[c] = ldo(kq->M + sb + c * fe, n);
+      }
+      // zeta face t - 1/2 between plane t-1 and plane t; it completes the
+      // residual of plane t-1 (rs) and opens that of plane t (racc)
+      T rs[5] = {0, 0, 0, 0, 0};
+      if (t >= kb) {
+        T qc[5], D[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) qc[c] = sq[c][ey][ex];
+        face_diss(P, lz_prev, lz, nz_prev, nz, qm2, qm1, qc, qa, D);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          const T fz = kHalf * (hz_prev[c] + hz[c]) - D[c];
+          rs[c] = racc[c] + fz;
+          racc[c] = r[c] - fz;
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) racc[c] = r[c];
+      }
+      const double J_fin = J_prev;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) hz_prev[c] = hz[c];
+      lz_prev = lz;
+      nz_prev = nz;
+      J_prev = Jn;
+      // ---- shift the column queues (plane t values from LDS), before the
+      // stores: the shift takes the column loads of this plane, and a wait
+      // for them after the stores would wait for the stores too ----
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         qm2[c] = qm1[c];
         qm1[c] = sq[c][ey][ex];
         qw[c] = qa[c];
-        if (kPrefetchQ) qa[c] = qn[c];
+        qa[c] = qn[c];
       }
       um1[0] = s.u[ey][ex]; um1[1] = s.v[ey][ex]; um1[2] = s.w[ey][ex]; um1[3] = s.tem[ey][ex];
       pm1 = s.p[ey][ex];
-      if (!kQ2) lds_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm<0>();  // Q^(0); on every path, so that nothing issued before the stores is waited for after them
+      if (t > kb && out_ok) {
+        // stage update of plane t-1
+        const int k = t - 1;
+        const unsigned n = nt - sk;
+        double qnv[5], Rv[5];
+        const double Jr = kTwice ? 0.5 * J_fin : J_fin;
+        const bool on_axis = (EXT & kExtAxis) && kq->axis && j == 0;  // advanced by the centerline condition
+#pragma unroll
+        for (int c = 0; c < 5; ++c) Rv[c] = Jr * (double)rs[c];
+        if (kq->f && i == kq->i_f) {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) Rv[c] -= kq->f[((long long)c * kq->L.nk + k) * kq->L.nj + j];
+        }
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          const double R = on_axis ? 0.0 : Rv[c];
+          const double qu = q0v[c] - adt * R;
+          qnv[c] = qu;
+          if (sizeof(T) == 8 || Qout) sto(Qout + sb + c * fe, n, qu);
+          if (sizeof(T) == 4 && Qsh) sto(Qsh + sb + c * fe, n, (float)qu);
+          if (NORM) {
+            n2[c] += R * R;
+            const double a = fabs(R);
+            nm[c] = (a > nm[c] || a != a) ? a : nm[c];  // NaN wins so that it is reported
+          }
+        }
+        if (CFL && !on_axis) cmin = min_nan(cmin, cfl_local(qnv[0], qnv[1], qnv[2], qnv[3], qnv[4], J_fin, cm, kq->P));
+      }
     }
   }
 
   // ---- block partial norms ----
-  // (the wave's Q^(0) block is free: its last copy was waited for and read)
   if (NORM) {
-    constexpr int QW = 5 * RPW * BX;  // doubles per wave in q0w
-    norm_wave(n2, nm, &q0w[wave][0][0][0], lane);
+    norm_wave(n2, nm, red_s[wave], lane);
     __syncthreads();
     if (tid < 10) {
-      const double* red = &q0w[0][0][0][0];
+      const double* red = &red_s[0][0];
       double r = red[tid];
       for (int w = 1; w < NW; ++w) {
-        const double o = red[w * QW + tid];
+        const double o = red[w * 10 + tid];
         r = tid < 5 ? r + o : ((o > r || o != o) ? o : r);
       }
       part[(long long)v * 10 + tid] = r;
@@ -689,8 +808,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- block partial of the CFL bound (CFL only) ----
   if (CFL) {
     const double m = wave_min(cmin);
-    double* red = &q0w[0][0][0][0];
-    __syncthreads();  // every wave is past its last read of q0w
+    double* red = &red_s[0][0];
     if (lane == 0) red[wave] = m;
     __syncthreads();
     if (tid == 0) {
