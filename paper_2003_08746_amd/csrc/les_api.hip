@@ -59,7 +59,7 @@ struct les_ctx {
   int i_f = -1;
   double* part = nullptr;            // per-block reduction partials
   long long part_n = 0;              // capacity in blocks (10 doubles each)
-  double* cpart = nullptr;           // per-block CFL bounds from the last stage (stage_blocks doubles)
+  double* cpart = nullptr;           // per-block CFL bounds from the last stage (sch.nblocks doubles)
   double* dthist = nullptr;          // time steps of one les_advance call (LES_ADVANCE_DT_MAX doubles)
   double* scal = nullptr;            // [0] dt, [1..10] norms, [12] dt of the next step (les_advance)
   int* flag = nullptr;               // bit 0: bad dt, bit 1: non-finite norm
@@ -72,7 +72,7 @@ struct les_ctx {
   double* outside = nullptr;         // [5][fe] outside state of characteristic faces
   int axis = 0;                      // j = 0 is the polar axis of an O-grid (bc[1] == LES_BC_AXIS)
   int use_ref = 0;                   // 1: stage through the reference kernel
-  int kchunk = 0;                    // k planes per block of the fused kernel
+  les::Schedule sch;                 // segments of the fused kernel
   les::Machine mach;                 // CU and XCD counts of the device
   double* scratch = nullptr;         // this device's les_residual_noalloc scratch
   // optional HIP-event timing of every stage-kernel launch
@@ -328,10 +328,10 @@ int les_create(les_ctx** out, const les_grid* grid, const les_metrics* metrics, 
     else
       c->mach.xcds = 1;
   }
-  c->kchunk = les::stage_kchunk(c->L, c->mach);
+  c->sch = les::stage_schedule(c->L, c->mach);
   // partials of the reference kernel, the fused kernel and the CFL kernel
   c->part_n = les::ref_blocks(c->L);
-  const long long sb = les::stage_blocks(c->L, c->kchunk, c->mach), cb = les::cfl_blocks(c->L);
+  const long long sb = c->sch.nblocks, cb = les::cfl_blocks(c->L);
   if (sb > c->part_n) c->part_n = sb;
   if (cb > c->part_n) c->part_n = cb;
   bool ok = hipMalloc(&c->M, 10 * fe * sizeof(double)) == hipSuccess &&
@@ -437,9 +437,9 @@ int les_residual(les_ctx* ctx, double* Q, double* R, double* norms) {
     const les::Layout& L = ctx->L;
     HIPCHK(ctx, les::launch_zero(ctx->s, R, 5 * L.fe));
     HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
-    const les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->kchunk, ctx->dyn, ctx->axis, ctx->mach};
+    const les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
     HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, Q, R, R, nullptr, 1.0, -1.0, part, nullptr));
-    nb = les::stage_blocks(L, ctx->kchunk, ctx->mach);
+    nb = ctx->sch.nblocks;
   } else {
     HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
     HIPCHK(ctx, les::launch_residual_ref(ctx->s, ctx->L, ctx->P, ctx->M, Q, ctx->f, ctx->i_f, R, part, ctx->dyn,
@@ -459,7 +459,7 @@ int les_residual_noalloc(les_ctx* ctx, double* Q, double* R, double* norms_dev) 
   if (((uintptr_t)R) & 15) return fail(ctx, LES_ERR_ARG, "les_residual_noalloc: R must be 16-byte aligned");
   if (!ctx->scratch) return fail(ctx, LES_ERR_STATE, "les_residual_noalloc: no scratch on this device");
   const les::Layout& L = ctx->L;
-  const long long nb = les::stage_blocks(L, ctx->kchunk, ctx->mach);
+  const long long nb = ctx->sch.nblocks;
   if (nb > LES_NOALLOC_BLOCKS)
     return fail(ctx, LES_ERR_ARG, "les_residual_noalloc: %lld kernel blocks exceed the scratch's %d", nb,
                 LES_NOALLOC_BLOCKS);
@@ -467,7 +467,7 @@ int les_residual_noalloc(les_ctx* ctx, double* Q, double* R, double* norms_dev) 
   HIPCHK(ctx, les::launch_zero(ctx->s, R, 5 * L.fe));
   const double* f = ctx->i_f >= 0 ? ctx->f : nullptr;
   HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
-  const les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->kchunk, ctx->dyn, ctx->axis, ctx->mach};
+  const les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
   double* part = norms_dev ? ctx->scratch : nullptr;
   HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, Q, R, R, nullptr, 1.0, -1.0, part, nullptr));
   if (norms_dev) {
@@ -523,7 +523,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
   const double* f = ctx->i_f >= 0 ? ctx->f : nullptr;
   const double cnt = (double)L.ni * L.nj * L.nk;
   if (ctx->prec == LES_MIXED) {
-    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->kchunk, ctx->dyn, ctx->axis, ctx->mach};
+    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
     for (int l = 0; l < 5; ++l) {
       const float* in32 = (l == 0 && !shadow_in) ? nullptr : ctx->Sf[(l + 1 + par) & 1];
       float* out32 = (l < 4 || shadow_out) ? ctx->Sf[(l + par) & 1] : nullptr;
@@ -540,7 +540,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
     }
     if (ctx->axis) HIPCHK(ctx, les::launch_axis_avg(ctx->s, L, Q));
     if (with_norms)
-      HIPCHK(ctx, les::launch_norm_final(ctx->s, ctx->part, les::stage_blocks(L, ctx->kchunk, ctx->mach), cnt,
+      HIPCHK(ctx, les::launch_norm_final(ctx->s, ctx->part, ctx->sch.nblocks, cnt,
                                          ctx->scal + 1, ctx->flag));
   } else {
     if (stage_ckpt) HIPCHK(ctx, hipMemcpyAsync(stage_ckpt, Q, 5 * fe * sizeof(double), hipMemcpyDeviceToDevice, ctx->s));
@@ -559,7 +559,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
         HIPCHK(ctx, les::launch_stage_ref(ctx->s, L, ctx->P, ctx->M, in, Q, out, dtp, dt, les::rk_alpha(l), f,
                                           ctx->i_f, part, ctx->dyn, ctx->axis));
       } else {
-        les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->kchunk, ctx->dyn, ctx->axis, ctx->mach};
+        les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
         HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, in, Q, out, dtp, dt, les::rk_alpha(l), part,
                                            l == 4 ? cpart : nullptr));
       }
@@ -568,7 +568,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
       in = out;
     }
     if (ctx->axis) HIPCHK(ctx, les::launch_axis_avg(ctx->s, L, Q));
-    long long nb = ctx->use_ref ? les::ref_blocks(L) : les::stage_blocks(L, ctx->kchunk, ctx->mach);
+    const long long nb = ctx->use_ref ? les::ref_blocks(L) : (long long)ctx->sch.nblocks;
     if (with_norms) HIPCHK(ctx, les::launch_norm_final(ctx->s, ctx->part, nb, cnt, ctx->scal + 1, ctx->flag));
   }
   return LES_OK;
@@ -604,7 +604,7 @@ int les_advance(les_ctx* ctx, double* Q, int nsteps, double* dt_out, double* nor
   if (dt_out && nsteps > LES_ADVANCE_DT_MAX)
     return fail(ctx, LES_ERR_ARG, "les_advance: dt_out holds at most %d steps (got %d)", LES_ADVANCE_DT_MAX, nsteps);
   les::Layout& L = ctx->L;
-  const long long nb = les::stage_blocks(L, ctx->kchunk, ctx->mach);
+  const long long nb = ctx->sch.nblocks;
   // the first step's dt by a pass of its own; each later one was reduced by
   // the last stage of the step before (the state it reads is that stage's
   // output, untouched since)

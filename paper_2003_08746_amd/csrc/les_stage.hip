@@ -10,13 +10,11 @@
 //
 // Decomposition.  A block of 32 x 16 threads owns the nodes of a 32 x 16
 // patch of one k-plane: the 30 x 14 output tile and a one-node halo ring.
-// Blocks are persistent (one per CU of the device): block v marches a contiguous range of
-// (tile, k) planes in chunk-major order (k chunks as long as one block's
-// range, tiles within a chunk, planes within a tile), so the blocks that
-// run together on one XCD start on neighbouring tiles at the same plane and
-// read the halo lines they share while those are still in the XCD's L2, and
-// the per-tile start-up cost (two extra planes) is paid about once per
-// block.  Each thread keeps the k-direction stencil of its own column in
+// Blocks are persistent (one per CU of the device) and take (k chunk, tile)
+// segments round robin in chunk-major order, so the blocks that run together
+// on one XCD work on neighbouring tiles at the same planes and read the halo
+// lines they share while those are still in the XCD's L2.
+// Each thread keeps the k-direction stencil of its own column in
 // registers (conserved variables at t-2 .. t+1, primitives at t-1 and t+1,
 // the zeta node flux and the partial residual of the plane below), so the
 // zeta direction needs no LDS.  The in-plane (xi, eta) stencil works in three
@@ -109,11 +107,8 @@ struct KArgs {
   int axis;             // j = 0 is the polar axis
   int i_f;
   int ntx, nty;         // tiles in i, j
-  long long total;      // tile-planes = ntx * nty * nk
-  long long per_block;  // tile-planes per block (contiguous range)
-  int kc;               // planes per k chunk of the chunk-major order
-  int rr;               // 1: blocks take (chunk, tile) segments round robin
-  long long nseg;       // segments in round-robin mode
+  int kc;               // planes per k chunk
+  int nseg;             // (chunk, tile) segments
   int nblocks;          // blocks with work
   int per_xcd;          // blocks per XCD in the remapped order
   int nxcd;             // XCDs of the device
@@ -283,11 +278,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int hb = blockIdx.x;
   const int v = (hb % a.nxcd) * a.per_xcd + hb / a.nxcd;
   if (v >= a.nblocks) return;
-  // contiguous mode: tile-planes [w_begin, w_end) of the chunk-major order;
-  // round-robin mode: segments v, v + nblocks, v + 2 nblocks, ...
-  const long long w_begin = a.rr ? (long long)v : (long long)v * a.per_block;
-  const long long w_end = a.rr ? a.nseg : min(a.total, w_begin + a.per_block);
-
   const int tid = threadIdx.x;
   const int tx = tid % BX, ty = tid / BX;
   const int ex = tx + 1, ey = ty + 1;
@@ -322,35 +312,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // updated state Q^(l) = Q^{n+1} over the block's nodes
   double cmin = INFINITY;
   int qbuf = 0;  // LDS Q plane written at the next B (alternates every plane)
-  for (long long wq = w_begin; wq < w_end;) {
+  for (int wq = v; wq < a.nseg; wq += a.nblocks) {
     // ---- one segment: planes [kb, ke) of one tile ----
-    // tile-planes are ordered k chunk by k chunk (kc planes; the last chunk
-    // may be shorter), tile by tile within a chunk, plane by plane within a
-    // tile: the blocks that run at the same time on one XCD start on
-    // neighbouring tiles at the same plane, so the halo lines they share
-    // are read while they are still in that XCD's L2.  A block takes a
-    // contiguous range of that order when its share is at most one chunk;
-    // with larger shares it takes whole (chunk, tile) segments round robin,
-    // which keeps the blocks of an XCD on neighbouring tiles throughout.
-    int tile, kb, ke;
-    if (a.rr) {
-      const long long ntiles = (long long)a.ntx * a.nty;
-      const int ch = (int)(wq / ntiles);
-      tile = (int)(wq % ntiles);
-      kb = ch * a.kc;
-      ke = min(L.nk, kb + a.kc);
-      wq += a.nblocks;
-    } else {
-      const long long cfull = (long long)a.ntx * a.nty * a.kc;
-      const int ch = (int)(wq / cfull);
-      const int k0 = ch * a.kc;
-      const int kcc = min(a.kc, L.nk - k0);
-      const long long rr = wq - (long long)ch * cfull;
-      tile = (int)(rr / kcc);
-      kb = k0 + (int)(rr % kcc);
-      ke = (int)min((long long)(k0 + kcc), (long long)kb + (w_end - wq));
-      wq += ke - kb;
-    }
+    // segments are ordered k chunk by k chunk (kc planes; the last chunk may
+    // be shorter) and tile by tile within a chunk, and the blocks take them
+    // round robin: the blocks that run at the same time on one XCD work on
+    // neighbouring tiles at the same planes, so the halo lines they share are
+    // read while they are still in that XCD's L2
+    const int ntiles = a.ntx * a.nty;
+    const int ch = wq / ntiles, tile = wq % ntiles;
+    const int kb = ch * a.kc, ke = min(L.nk, kb + a.kc);
     // segment base: plane kb - 2, the first the segment reads.  Per-thread
     // element offsets are taken from there, so they stay below 2^29 for any
     // block whose planes are small enough that kc + 6 of them are (the
@@ -831,62 +802,20 @@ int stage_kmax(const Layout& L) {
 
 namespace {
 
-// Stage kernel configuration for a layout.
+// Stage kernel configuration for a layout and a schedule.
 struct Config {
-  int ntx, nty, nblocks, grid, per_xcd, kc, rr, nxcd;
-  long long total, per_block, nseg;
+  int ntx, nty, nseg, grid, per_xcd;
 };
 
-long long auto_per_block(const Layout& L, const Machine& m) {
-  const long long tiles = (long long)((L.ni + TX - 1) / TX) * ((L.nj + TY - 1) / TY);
-  const long long total = tiles * L.nk;
-  // one persistent block per resident slot (BPC per CU), at least 8 planes each
-  const long long slots = (long long)m.cus * BPC;
-  long long pb = (total + slots - 1) / slots;
-  return pb < 8 ? 8 : pb;
-}
-
-Config config(const Layout& L, long long per_block, const Machine& m) {
+Config config(const Layout& L, const Schedule& sch, int nxcd) {
   Config c;
   c.ntx = (L.ni + TX - 1) / TX;
   c.nty = (L.nj + TY - 1) / TY;
-  c.total = (long long)c.ntx * c.nty * L.nk;
-  c.per_block = per_block < 1 ? 1 : per_block;
-  c.rr = c.per_block > L.nk;
-  c.nseg = 0;
-  const int kmax = stage_kmax(L);
-  if (!c.rr) {
-    c.kc = (int)(c.per_block < kmax ? c.per_block : kmax);
-    c.nblocks = (int)((c.total + c.per_block - 1) / c.per_block);
-  } else {
-    // the number of k chunks (from the fewest whose chunks fit the 32-bit
-    // offsets, at most 16 more, chunks of at least 32 planes when nk allows)
-    // that best fills whole rounds of the blocks there are slots for; fewer
-    // chunks on ties (fewer segment start-ups)
-    const long long ntiles = (long long)c.ntx * c.nty;
-    const long long slots = (c.total + c.per_block - 1) / c.per_block;
-    const int n0 = (L.nk + kmax - 1) / kmax;
-    double best = -1.0;
-    for (int n = n0; n <= n0 + 15; ++n) {
-      const int kc = (L.nk + n - 1) / n;
-      if (n > n0 && kc < 32) break;
-      const long long nseg = ntiles * ((L.nk + kc - 1) / kc);
-      const long long nb = nseg < slots ? nseg : slots;
-      const long long rounds = (nseg + nb - 1) / nb;
-      const double eff = (double)nseg / (double)(rounds * nb);
-      if (eff > best + 1e-9) {
-        best = eff;
-        c.kc = kc;
-        c.nseg = nseg;
-        c.nblocks = (int)nb;
-      }
-    }
-  }
-  // hardware block b runs on XCD b mod xcds: virtual block (b mod xcds)
-  // per_xcd + b / xcds, so consecutive virtual blocks share an XCD
-  c.nxcd = m.xcds;
-  c.per_xcd = (c.nblocks + c.nxcd - 1) / c.nxcd;
-  c.grid = c.per_xcd * c.nxcd;
+  c.nseg = c.ntx * c.nty * ((L.nk + sch.kc - 1) / sch.kc);
+  // hardware block b runs on XCD b mod nxcd: virtual block (b mod nxcd)
+  // per_xcd + b / nxcd, so consecutive virtual blocks share an XCD
+  c.per_xcd = (sch.nblocks + nxcd - 1) / nxcd;
+  c.grid = c.per_xcd * nxcd;
   return c;
 }
 
@@ -906,9 +835,9 @@ template <class T, class QI>
 hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const double* Q0, double* Qout, float* Qsh,
                   const double* dtp, double dt, double alpha, double* part, double* cpart) {
   if (part && cpart) return hipErrorInvalidValue;  // norms belong to stage 1, the CFL bound to stage 5
-  Config c = config(sa.L, sa.kchunk, sa.mach);
-  KArgs a{sa.L,        sa.P,   sa.M,   sa.f,   sa.dyn,  sa.axis,  sa.i_f,    c.ntx,    c.nty,
-          c.total,     c.per_block, c.kc, c.rr, c.nseg, c.nblocks, c.per_xcd, c.nxcd};
+  const Config c = config(sa.L, sa.sch, sa.mach.xcds);
+  KArgs a{sa.L,  sa.P,  sa.M,      sa.f,   sa.dyn,         sa.axis,   sa.i_f,
+          c.ntx, c.nty, sa.sch.kc, c.nseg, sa.sch.nblocks, c.per_xcd, sa.mach.xcds};
   // the optional SGS models (dynamic closure, isotropic SGS stress) and the
   // polar axis run in instantiations of their own, so that each path keeps
   // only the registers it needs
@@ -928,13 +857,47 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
 
 }  // namespace
 
-int stage_kchunk(const Layout& L, const Machine& m) {
-  const char* env = getenv("LES_SEG");
-  if (env && atoi(env) > 0) return atoi(env);
-  return (int)auto_per_block(L, m);
+// The schedule of a layout: (k chunk, tile) segments round robin over one
+// persistent block per CU.  A segment of n planes runs n + 2 iterations (the
+// planes below and above it) and about one more for its start, so the time of
+// a launch is that of its slowest block, block 0: the sum of n + 3 over its
+// segments.  The number of chunks with the smallest sum is taken, the fewest
+// on ties.  (Against contiguous ranges of at least 8 tile-planes per block,
+// which could straddle two tiles, as used before; FP64 stage: 32^3 52 -> 18 us,
+// 64^3 49 -> 32, 128 x 64 x 64 49 -> 45, 256 x 128 x 128 267 -> 262,
+// 400 x 250 x 250 1992 -> 1313, O-grid 256 x 128 x 361 784 -> 700,
+// 800 x 500 x 500 10.95 -> 10.55 ms; mixed 75 x 61 x 47 45 -> 23 us.)
+Schedule stage_schedule(const Layout& L, const Machine& m) {
+  const long long ntiles = (long long)((L.ni + TX - 1) / TX) * ((L.nj + TY - 1) / TY);
+  const int slots = m.cus * BPC, kmax = stage_kmax(L);
+  Schedule best;
+  if (const char* env = getenv("LES_SEG")) {
+    const int seg = atoi(env);
+    if (seg > 0) {  // chunks of seg planes, one block per seg tile-planes
+      best.kc = seg < L.nk ? seg : L.nk;
+      if (best.kc > kmax) best.kc = kmax;
+      const long long nseg = ntiles * ((L.nk + best.kc - 1) / best.kc), nb = (ntiles * L.nk + seg - 1) / seg;
+      best.nblocks = (int)(nseg < nb ? nseg : nb);
+      return best;
+    }
+  }
+  long long cost = -1;
+  for (int n = (L.nk + kmax - 1) / kmax; n <= L.nk; ++n) {
+    const int kc = (L.nk + n - 1) / n;
+    if ((L.nk + kc - 1) / kc != n) continue;  // the same chunks as fewer of them
+    const int last = L.nk - (n - 1) * kc;
+    const long long nseg = ntiles * n, nb = nseg < slots ? nseg : slots;
+    const long long rounds = (nseg + nb - 1) / nb, full = (ntiles * (n - 1) + nb - 1) / nb;
+    const long long c = full * kc + (rounds - full) * last + rounds * 3;
+    if (cost < 0 || c < cost) {
+      cost = c;
+      best.kc = kc;
+      best.nblocks = (int)nb;
+    }
+    if (rounds * 3 > cost) break;  // more chunks only add starts
+  }
+  return best;
 }
-
-long long stage_blocks(const Layout& L, int kchunk, const Machine& m) { return config(L, kchunk, m).nblocks; }
 
 hipError_t launch_stage_fp64(hipStream_t s, const StageArgs& a, const double* Qin, const double* Q0, double* Qout,
                              const double* dtp, double dt, double alpha, double* part, double* cpart) {

@@ -12,34 +12,38 @@ struct Machine {
   int xcds = 8;
 };
 
+// Work of the persistent blocks: (k chunk, tile) segments of kc planes, taken
+// round robin by nblocks blocks (fixed per context).
+struct Schedule {
+  int kc = 0;
+  int nblocks = 0;
+};
+
 struct StageArgs {
   Layout L;
   Phys P;
   const double* M;  // metrics [10][fe]
   const double* f;  // source [5][nk][nj] or null
   int i_f;
-  int kchunk;       // k planes per block (from stage_kchunk, fixed per context)
+  Schedule sch;     // from stage_schedule
   const double* dyn = nullptr;  // dynamic SGS coefficients per column (P.sgs == 2)
   int axis = 0;                 // j = 0 is the polar axis of an O-grid
   Machine mach;
 };
 
-// k planes per block of the fused kernel for this layout (LES_SEG in
-// the environment overrides the automatic choice; read once per context).
-int stage_kchunk(const Layout& L, const Machine& m);
+// The schedule of the fused kernel for this layout (LES_SEG in the environment
+// overrides the automatic choice of planes per segment; read once per context).
+Schedule stage_schedule(const Layout& L, const Machine& m);
 
 // Largest number of k planes per segment of the stage kernel's schedule for
 // this layout (0: a single k plane is too large for the kernel's 32-bit
 // per-thread offsets, which les_create refuses).
 int stage_kmax(const Layout& L);
 
-// Number of per-block norm partials written by one fused stage launch.
-long long stage_blocks(const Layout& L, int kchunk, const Machine& m);
-
 // One FP64 stage: Qout = Q0 - alpha dt R(Qin) on the interior (Qin's ghosts
 // already filled).  dtp (device) overrides dt when non-null.  part: norm
 // partials (or null).  cpart (or null): per-block minima of the local CFL
-// bound of the updated state (stage_blocks doubles; not together with part).
+// bound of the updated state (one double per block; not together with part, ten).
 // Q0 and Qout may alias.
 hipError_t launch_stage_fp64(hipStream_t s, const StageArgs& a, const double* Qin, const double* Q0, double* Qout,
                              const double* dtp, double dt, double alpha, double* part, double* cpart);

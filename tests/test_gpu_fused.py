@@ -28,6 +28,29 @@ def _rel(a, b):
     return np.abs(ai - bi).reshape(ai.shape[0], -1).max(1) / den
 
 
+@pytest.mark.parametrize("shape,prec", [((5, 5, 5), 0), ((30, 14, 8), 0), ((31, 15, 33), 0), ((60, 28, 300), 0),
+                                        ((200, 100, 21), 0), ((31, 15, 33), 1)])
+def test_automatic_schedule_bitwise(lesmi, shape, prec, monkeypatch):
+    """The automatic number of k chunks over its range: one plane per segment,
+    one tile, a second tile of one row and column, many chunks of one tile,
+    several rounds of blocks.  The arithmetic of a point does not depend on
+    the schedule, so the result equals that of chunks of 7 planes bit for
+    bit."""
+    ni, nj, nk = shape
+    case = I.jet_case(ni, nj, nk, seed=3)
+    print(f"[gpu] automatic schedule {shape} prec={prec}", flush=True)
+    monkeypatch.delenv("LES_SEG", raising=False)
+    a = lesmi.Solver(case, prec=prec)
+    monkeypatch.setenv("LES_SEG", "7")
+    b = lesmi.Solver(case, prec=prec)
+    Qa, Qb = a.upload(case["Q"]), b.upload(case["Q"])
+    a.rk_step(Qa, 1e-3)
+    b.rk_step(Qb, 1e-3)
+    assert np.array_equal(a.download(Qa), b.download(Qb))
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("shape,seg", [((61, 29, 23), "5"), ((31, 15, 9), "4"), ((93, 43, 17), ""),
                                        ((40, 20, 12), "7"), ((61, 29, 23), "40"), ((93, 43, 37), "200")])
 def test_fused_matches_reference_kernel(lesmi, shape, seg, monkeypatch):
