@@ -286,7 +286,7 @@ int les_advance(les_ctx *ctx, double *Q, int nsteps, double *dt_out, double *nor
  * Qbar: device, library layout, FP64, in: dJ/dQ^{n+1} (interior), out: dJ/dQ^n
  *    (interior; ghost layers are used as scratch).
  * fbar: device, dense [5][nk][nj], accumulated, or NULL.
- * The first adjoint call allocates the work arrays (84 fields of field_elems
+ * The first adjoint call allocates the work arrays (35 fields of field_elems
  * doubles; LES_ERR_NOMEM if they do not fit).  LES_ERR_STATE for the
  * dynamic closure, and for a block of 2^30 padded nodes or more.  With
  * LES_BC_AXIS the centerline condition on every stage input and on the
@@ -304,7 +304,7 @@ int les_adjoint_step(les_ctx *ctx, const double *stage_ckpt, double dt, double *
  * Q: device, library layout, FP64; its ghost layers are filled in place.
  * Rbar: device, library layout; only interior values are read.
  * Qbar: device, library layout; interior written (must not alias Q or Rbar).
- * Allocates the adjoint work arrays on first use (84 fields of field_elems
+ * Allocates the adjoint work arrays on first use (35 fields of field_elems
  * doubles, kept by the context). */
 int les_residual_adjoint(les_ctx *ctx, double *Q, const double *Rbar, double *Qbar);
 

@@ -6,35 +6,31 @@
 // dissipation): node primitives -> node gradients -> stress / heat flux /
 // eddy viscosity -> node fluxes and spectral radii / sensors -> face fluxes
 // -> residual.  Every backward step that would scatter is written as a
-// gather over stored per-node weights, so no atomics are needed:
-//   pass 1 (node, nodes with indices in [-1, n]): with W = J Rbar (zero off
-//      the interior) the node flux adjoint is Hbar_d(n) = (W(n-e_d) -
-//      W(n+e_d))/2; the thread reverses its node flux, viscous stress, heat
-//      flux, Smagorinsky and Sutherland viscosity and its share of the two
-//      dissipation faces on each side, and stores: the adjoint in primitive
-//      variables (rho, u, v, w, p, T), the direct Q adjoint of the fluxes,
-//      the gradient-stencil weights a_{q,d} = J m_d . gbar_q, the sensor
-//      weights for p at n +- e_d, and the face coefficients
-//      Lambda eps2, Lambda eps4 of the face (n, n + e_d);
-//   pass 2 (gather, interior nodes and their periodic ghost images):
-//      collects the gradient and sensor weights of its neighbours and the
-//      dissipation faces whose five-point stencil contains it, and maps the
-//      primitive adjoint back to conserved variables;
-//   pass 3 (fold, interior nodes with ghost images): adds the adjoint of
-//      every periodic ghost image to its interior node and pulls the
-//      adjoint of a boundary face's ghosts back to the face's boundary node
-//      through the face rule's Jacobian (frozen Dirichlet ghosts carry no
-//      dependence).
+// gather, so no atomics are needed, and every gather stays on the chip: two
+// tiled passes march in k as the stage kernel does (les_stage.hip), with
+// W = J Rbar (zero off the interior):
+//   flux pass (k_adj_flux): the node flux adjoint is Hbar_d(n) = (W(n-e_d) -
+//      W(n+e_d))/2; reverses node flux, viscous stress, heat flux,
+//      Smagorinsky and Sutherland viscosity and the node gradients, and maps
+//      the primitive adjoint to conserved variables;
+//   dissipation pass (k_adj_diss): reverses the faces, radii and sensors and
+//      adds the flux pass's part.  Output nodes are the interior nodes and
+//      the ghost nodes that are images of interior nodes;
+//   fold (interior nodes with ghost images): adds the adjoint of every
+//      periodic ghost image to its interior node and pulls the adjoint of a
+//      boundary face's ghosts back to the face's boundary node through the
+//      face rule's Jacobian (frozen Dirichlet ghosts carry no dependence).
 // Non-smooth points take the derivative of the active branch: d|x|/dx =
 // sign(x) with 0 at 0, max(a, b) follows a when a >= b, and the eddy
 // viscosity's |S| has derivative 0 at |S| = 0.
 //
 // les_adjoint_step applies it stage by stage in reverse from the stage
-// inputs saved by les_rk_step: for l = 5..1, acc += qbar, fbar += alpha_l dt
-// qbar on the source plane, qbar = (dR/dQ|Q^(l-1))^T (-alpha_l dt qbar);
-// finally Qbar = acc + qbar.  The accumulation, the fbar update and the
-// final sum run inside passes 2 and 3 of the next (or last) stage.
+// inputs saved by les_rk_step: for l = 5..1, fbar += alpha_l dt qbar on the
+// source plane and qbar' = (dR/dQ|Q^(l-1))^T (-alpha_l dt qbar); finally Qbar
+// is the sum of all qbar.  The fbar update and the final sum run inside the
+// dissipation pass and the fold of the next (or last) stage.
 #include "les_adjoint.hpp"
+#include "les_tile.hpp"
 
 namespace les {
 
@@ -42,86 +38,11 @@ namespace {
 
 // Work-array field indices (library layout, one field each).
 enum {
-  W_PRHO = 0, W_PU, W_PV, W_PW, W_PP, W_PT,  // primitive-variable adjoint (local part)
-  W_QD1, W_QD2, W_QD3, W_QD4,                 // direct Q adjoint of the node fluxes
-  W_A = 10,                                   // a_{q,d}: 12 fields, index W_A + 3 q + d
-  W_CP = 22,                                  // sensor weights for p(n +- e_d): 3 fields
-  W_A2 = 25,                                  // Lambda eps2 of face (n, n+e_d): 3 fields
-  W_A4 = 28,                                  // Lambda eps4 of face (n, n+e_d): 3 fields
-  W_LAM = 31,                                 // Lambda_d at the node: 3 fields
-  W_NU = 34,                                  // signed sensor (p+ - 2p + p-) / Sigma: 3 fields
-  W_LH = 37,                                  // half the face-mean adjoint of face (n, n+e_d): 3
-  W_NUA = 40,                                 // sensor adjoint of face (n, n+e_d) for node n: 3
-  W_NUB = 43,                                 // ... for node n + e_d: 3
-  W_Q1 = 46,                                  // stage adjoint ping-pong: 5 + 5 fields
-  W_ACC = 56,                                 // accumulated adjoint of Q^(0): 5 fields
-  W_DB = 61,                                  // Dbar = W(n+e_d) - W(n) of face (n, n+e_d): 15
-  W_IS = 76,                                  // 1 / Sigma of the sensor, Sigma = p+ + 2p + p-: 3
-  W_GG = 79,                                  // gather result at periodic ghost images: 5
-  W_NF = 84
+  W_FL = 0,   // flux part at the output nodes: 5 fields
+  W_GG = 5,   // adjoint at the ghost images of interior nodes: 5
+  W_Z = 10,   // Runge-Kutta reverse: the stages' results, 5 x 5 fields
+  W_NF = 35
 };
-
-struct Prim {
-  double rho, u, v, w, p, T;
-};
-
-__device__ __forceinline__ Prim prim_at(const double* __restrict__ Q, long long fe, long long n, const Phys& P) {
-  Prim r;
-  r.rho = Q[n];
-  prim_from_q_fast(r.rho, Q[fe + n], Q[2 * fe + n], Q[3 * fe + n], Q[4 * fe + n], P, r.u, r.v, r.w, r.p, r.T);
-  return r;
-}
-
-__device__ __forceinline__ long long dstr(const Layout& L, int d) { return d == 0 ? 1LL : (d == 1 ? L.sj : L.sk); }
-
-__device__ __forceinline__ bool interior(const Layout& L, int i, int j, int k) {
-  return i >= 0 && i < L.ni && j >= 0 && j < L.nj && k >= 0 && k < L.nk;
-}
-
-// Does the face (a, a + e_d) exist, i.e. is it used by an interior residual?
-__device__ __forceinline__ bool face_ok(const Layout& L, int d, int i, int j, int k) {
-  const int id[3] = {i, j, k};
-  const int nn[3] = {L.ni, L.nj, L.nk};
-  for (int e = 0; e < 3; ++e) {
-    if (e == d) {
-      if (id[e] < -1 || id[e] > nn[e] - 1) return false;
-    } else if (id[e] < 0 || id[e] >= nn[e]) {
-      return false;
-    }
-  }
-  return true;
-}
-
-// W = coef * J * qbar on the interior, zero elsewhere and on the polar axis
-// (whose nodes the residual does not advance; J is infinite there).
-__device__ __forceinline__ void Wat(const Layout& L, const double* __restrict__ M, const double* __restrict__ qb,
-                                    double coef, int i, int j, int k, double W[5], bool axis) {
-  if (!interior(L, i, j, k) || (axis && j == 0)) {
-    for (int c = 0; c < 5; ++c) W[c] = 0.0;
-    return;
-  }
-  const long long n = L.at(i, j, k);
-  const double s = coef * M[9 * L.fe + n];
-  for (int c = 0; c < 5; ++c) W[c] = s * qb[c * L.fe + n];
-}
-
-// Spectral radii and their ingredients at node n.
-struct Radii {
-  double lam[3], U[3], nrm[3], c;
-};
-
-__device__ __forceinline__ Radii radii_at(const double* __restrict__ M, long long fe, long long n, const Prim& q,
-                                          const Phys& P) {
-  Radii r;
-  r.c = sqrt_pos(P.gamma_R * q.T);  // c^2 = gamma p / rho = gamma R T
-  for (int e = 0; e < 3; ++e) {
-    const double mx = M[(3 * e) * fe + n], my = M[(3 * e + 1) * fe + n], mz = M[(3 * e + 2) * fe + n];
-    r.U[e] = mx * q.u + my * q.v + mz * q.w;
-    r.nrm[e] = sqrt_pos(mx * mx + my * my + mz * mz);
-    r.lam[e] = fabs(r.U[e]) + r.c * r.nrm[e];
-  }
-  return r;
-}
 
 // Anisotropic scaling Lam_d and its partial derivatives w.r.t. (lam_d, lam_e, lam_f).
 __device__ __forceinline__ double aniso_d(double ld, double le, double lf, const Phys& P, double& dd, double& de,
@@ -150,10 +71,11 @@ struct AdjK {
   const double* M;
   int bc0, bc1, bc2;
   int per[3];          // period of each axis: n (periodic), n - 1 (superposed), 0 (Dirichlet)
-  int lo[3], hi[3];    // pass-2 box: ghost layers of periodic axes and of active faces included
+  int lo[3], hi[3];    // output box: ghost layers of periodic axes and of active faces included
   Faces F;             // boundary faces
-  int general;         // a superposed axis, the polar axis or an active face: pass 3 visits every interior node
+  int general;         // a superposed axis, the polar axis or an active face: the fold visits every interior node
   int axis;            // j = 0 is the polar axis (bc1 == 3)
+  Machine mach;
 };
 
 AdjK make_adjk(const AdjArgs& a) {
@@ -167,6 +89,7 @@ AdjK make_adjk(const AdjArgs& a) {
   A.F = a.F;
   A.general = 0;
   A.axis = a.axis;
+  A.mach = a.mach;
   const int bc[3] = {a.bc0, a.bc1, a.bc2}, nn[3] = {a.L.ni, a.L.nj, a.L.nk};
   for (int d = 0; d < 3; ++d) {
     // bc 3 (polar axis, j only): its lo side is the axis, whose cross-axis
@@ -184,369 +107,393 @@ AdjK make_adjk(const AdjArgs& a) {
 }
 
 // ---------------------------------------------------------------------------
-// Pass 1
+// Flux pass: the adjoint of the node fluxes (inviscid, viscous, SGS), complete
+// at every output node.
+//
+// Blocks of 32 x 16 threads march a 30 x 14 tile of output nodes in k as the
+// stage kernel does (les_stage.hip): the patch is the tile and a one-node
+// ring, whose gradient weights the tile's outer nodes collect.  Per plane
+//   B  stores u, v, w, T and W = coef J Rbar of the patch (and of the second
+//      ring along the axes) to LDS;
+//   C  recomputes the node's gradients, stress and viscosities, reverses its
+//      node flux, stress, heat flux and viscosities with the node flux
+//      adjoints Hbar_d = (W(n-e_d) - W(n+e_d))/2, and forms the
+//      gradient-stencil weights a_{q,d} = J m_d . gbar_q; the xi differences
+//      of the weights come from the adjacent lanes, the zeta differences from
+//      the planes t -+ 1 through registers;
+//   E  takes the eta differences through LDS, finishes plane t-1 (its upper
+//      zeta neighbour is known now), maps it to conserved variables and
+//      stores it (W_FL: interior nodes, and the ghost nodes that are images
+//      of interior nodes).
+// One read of Q, the metrics and Rbar and one write of five fields: the
+// weights, the primitive adjoint and the direct terms (22 fields of the
+// one-thread-per-node pass this replaces, written, and read by the gather at
+// the neighbours) stay on the chip.  Bound by the FP64
+// issue rate at two waves a SIMD (255 registers); 49 us on the 128 x 64 x 64
+// jet, the node pass without the gather took 70.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_adj_flux(AdjK A, const double* __restrict__ Q, const double* __restrict__ qb,
-                                                  double coef, double* __restrict__ Wk) {
-  const Layout& L = A.L;
-  const Phys& P = A.P;
+constexpr int BX = 32, BY = 16, NT = BX * BY;  // patch (threads)
+constexpr int TX = BX - 2, TY = BY - 2;        // output tile of the flux pass
+constexpr int EX = BX + 2, EY = BY + 2;        // patch and second ring (LDS planes)
+constexpr int NH2 = 2 * TY + 2 * TX;           // second-ring nodes
+constexpr int NW = NT / 64;
+
+struct TileArgs {
+  AdjK A;
+  const double* Q;
+  const double* qb;
+  double coef;
+  double Rg, inv_gm1;  // gas constant, 1 / (gamma - 1)
+  double* Wk;
+  int ntx, nty, kc, nseg, nblocks, per_xcd, nxcd;
+};
+
+__device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
+
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) k_adj_flux(TileArgs a) {
+  __shared__ double su[EY][EX], sv[EY][EX], sw[EY][EX], st[EY][EX];
+  __shared__ double sW[5][EY][EX];
+  __shared__ double sa[4][BY][TX];  // eta weights, patch columns 1..TX
+  __shared__ double mbw[NW][10][2][BX];
+  const Layout& L = a.A.L;
+  typedef __attribute__((address_space(4))) const TileArgs CArgs;
+  CArgs* const ka = (CArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   const long long fe = L.fe;
-  const double* __restrict__ M = A.M;
-  // (the adjoint entry points refuse blocks of 2^30 padded nodes or more: 32-bit index math)
-  const unsigned ext_i = L.ni + 2, ext_j = L.nj + 2;
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ext_i * ext_j * (unsigned)(L.nk + 2)) return;
-  const int i = (int)(t % ext_i) - 1;
-  const int j = (int)((t / ext_i) % ext_j) - 1;
-  const int k = (int)(t / (ext_i * ext_j)) - 1;
-  const long long n = L.at(i, j, k);
+  const int hb = blockIdx.x;
+  const int v = (hb % a.nxcd) * a.per_xcd + hb / a.nxcd;
+  if (v >= a.nblocks) return;
+  const int tid = threadIdx.x;
+  const int tx = tid % BX, ty = tid / BX, ex = tx + 1, ey = ty + 1;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const bool xh = (tx == 0 || tx == BX - 1), yh = (ty == 0 || ty == BY - 1);
+  const unsigned sk = (unsigned)L.sk;
+  const double coef = a.coef;
+  int hx2 = 0, hy2 = 0;  // second-ring slot of helper thread tid < NH2
+  if (tid < NH2) {
+    const int h = tid;
+    if (h < TY) { hx2 = 0; hy2 = 2 + h; }
+    else if (h < 2 * TY) { hx2 = EX - 1; hy2 = 2 + h - TY; }
+    else if (h < 2 * TY + TX) { hy2 = 0; hx2 = 2 + h - 2 * TY; }
+    else { hy2 = EY - 1; hx2 = 2 + h - 2 * TY - TX; }
+  }
+  for (int wq = v; wq < a.nseg; wq += a.nblocks) {
+    const int ntiles = a.ntx * a.nty;
+    const int ch = wq / ntiles, tile = wq % ntiles;
+    const int kb = a.A.lo[2] + ch * a.kc, ke = min(a.A.hi[2] + 1, kb + a.kc);  // output planes
+    const int i = a.A.lo[0] - 1 + (tile % a.ntx) * TX + tx, j = a.A.lo[1] - 1 + (tile / a.ntx) * TY + ty;
+    const bool in_ij = i >= 0 && i < L.ni && j >= (a.A.axis ? 1 : 0) && j < L.nj;  // W may be nonzero
+    // nodes with weights: [-1, n]^3 (not on or below the polar axis, where
+    // the node flux is constant or serves only the axis)
+    const bool b1_ij = i >= -1 && i <= L.ni && j >= (a.A.axis ? 1 : -1) && j <= L.nj;
+    const bool out_ok = !xh && !yh && i <= a.A.hi[0] && j <= a.A.hi[1];
+    const int hi = i - tx + hx2 - 1, hj = j - ty + hy2 - 1;
+    const bool h_use = tid < NH2;
+    const bool h_in = hi >= 0 && hi < L.ni && hj >= (a.A.axis ? 1 : 0) && hj < L.nj;
+    // per-thread offsets from plane kb - 2 (nodes clamped into the padded box)
+    const int kr = kb - 2;
+    const long long sb = (long long)kr * L.sk;
+    const unsigned col = (unsigned)((long long)clampi(i, -2, L.ni + 1) + (long long)clampi(j, -2, L.nj + 1) * L.sj + L.o);
+    const unsigned hcol =
+        (unsigned)((long long)clampi(hi, -2, L.ni + 1) + (long long)clampi(hj, -2, L.nj + 1) * L.sj + L.o);
+    auto off = [&](unsigned c, int k) { return c + (unsigned)(clampi(k, -2, L.nk + 1) - kr) * sk; };
+    // row copies of the metrics (rows 2 wave, 2 wave + 1; see les_stage.hip)
+    const int fsel = lane >> 5, rsel = (lane / 16) % 2, pr = lane % 16;
+    int icp = i - tx + 2 * pr;
+    if (icp > L.ni) icp = L.ni - ((LEAD + L.ni) & 1);
+    const int jcp = clampi(j - ty + 2 * wave + rsel, -2, L.nj + 1);
+    const long long lane_el = (long long)fsel * fe + L.o + icp + (long long)jcp * L.sj;
+    const long long fstep2 = 2 * fe * (long long)sizeof(double);
+    double* const mdst = &mbw[wave][0][0][0];
 
-  const Prim q = prim_at(Q, fe, n, P);
-  double m[9];
-  for (int c = 0; c < 9; ++c) m[c] = M[c * fe + n];
-  const double J = M[9 * fe + n];
-
-  // ---- forward recomputation at the node ----
-  double g[4][3];
-  {
-    double dd[3][4];
-    for (int d = 0; d < 3; ++d) {
-      const long long s = dstr(L, d);
-      const Prim a = prim_at(Q, fe, n + s, P), b = prim_at(Q, fe, n - s, P);
-      dd[d][0] = 0.5 * (a.u - b.u);
-      dd[d][1] = 0.5 * (a.v - b.v);
-      dd[d][2] = 0.5 * (a.w - b.w);
-      dd[d][3] = 0.5 * (a.T - b.T);
-      // for the dissipation adjoint: signed sensor (p+ - 2p + p-) / Sigma and 1 / Sigma
-      const double iS = rcp_nr(a.p + 2.0 * q.p + b.p);
-      Wk[(W_NU + d) * fe + n] = (a.p - 2.0 * q.p + b.p) * iS;
-      Wk[(W_IS + d) * fe + n] = iS;
+    double up1[4], rp1 = 0, um1[4], rc = 0, rm1 = 0;  // u, v, w, T and rho at t+1 (at B: t), t-1; rho at t, t-1
+    double Wm[5], Wc[5];                              // W at t-1; at t (at B)
+    double qn[5], bn[5], Jn;                          // Q, Rbar and J of plane t+1 (loaded one plane ahead)
+    double a2[4] = {0, 0, 0, 0};                      // zeta weights of plane t-1
+    double pf[10];                                    // plane t-1: rho, u, v, w, p, T adjoint, direct Q1..Q4
+    auto prims = [&](const Phys& P, const double q[5], double uu[4], double& rr) {
+      double p;
+      rr = q[0];
+      prim_from_q_fast(q[0], q[1], q[2], q[3], q[4], P, uu[0], uu[1], uu[2], p, uu[3]);
+    };
+    auto load5 = [&](const double* f, unsigned o, double x[5]) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) x[c] = ldo(f + sb + c * fe, o);
+    };
+    auto Wset = [&](bool in, int k, const double b[5], double J, double W[5]) {
+      const bool ok = in && k >= 0 && k < L.nk;
+      const double s = coef * J;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) W[c] = ok ? s * b[c] : 0.0;
+    };
+    {
+      CArgs* kp4 = ka;
+      asm volatile("" : "+s"(kp4));
+      const TileArgs* kp = (const TileArgs*)kp4;
+      const char* msrc = (const char*)(kp->A.M + lane_el + (long long)clampi(kb - 1, -2, L.nk + 1) * L.sk);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) copy_to_lds(msrc + q * fstep2, mdst + q * 128);
+      const unsigned o0 = off(col, kb - 2), o1 = off(col, kb - 1), o2 = off(col, kb);
+      double q0[5], b0[5], q1[5], b1[5];
+      load5(kp->Q, o0, q0);
+      load5(kp->qb, o0, b0);
+      load5(kp->Q, o1, q1);
+      load5(kp->qb, o1, b1);
+      const double J0 = ldo(kp->A.M + sb + 9 * fe, o0), J1 = ldo(kp->A.M + sb + 9 * fe, o1);
+      load5(kp->Q, o2, qn);
+      load5(kp->qb, o2, bn);
+      Jn = ldo(kp->A.M + sb + 9 * fe, o2);
+      prims(kp->A.P, q0, um1, rm1);
+      prims(kp->A.P, q1, up1, rp1);
+      Wset(in_ij, kb - 2, b0, J0, Wm);
+      Wset(in_ij, kb - 1, b1, J1, Wc);
+      wait_vm<0>();
     }
-    for (int qq = 0; qq < 4; ++qq)
-      for (int x = 0; x < 3; ++x) g[qq][x] = J * (m[x] * dd[0][qq] + m[3 + x] * dd[1][qq] + m[6 + x] * dd[2][qq]);
-  }
-  if (A.axis && j <= 0) {
-    // polar axis: its residual is not formed (W = 0 around it along xi and
-    // zeta) and its eta node flux and spectral radius are the constant 0;
-    // the row below it (a ghost across the axis, where J < 0) serves only
-    // the axis residual.  Nothing but the pressure sensors (kept above)
-    // depends on them here
-    for (int d = 0; d < 3; ++d) Wk[(W_LAM + d) * fe + n] = 0.0;
-    for (int c = 0; c < 12; ++c) Wk[(W_A + c) * fe + n] = 0.0;
-    for (int c = W_PRHO; c <= W_PT; ++c) Wk[c * fe + n] = 0.0;
-    for (int a = 0; a < 4; ++a) Wk[(W_QD1 + a) * fe + n] = 0.0;
-    return;
-  }
-  {
-    // for the dissipation adjoint: Lambda_d at the node
-    const Radii r = radii_at(M, fe, n, q, P);
-    for (int d = 0; d < 3; ++d) {
-      double dd0, de0, df0;
-      Wk[(W_LAM + d) * fe + n] = aniso_d(r.lam[d], r.lam[(d + 1) % 3], r.lam[(d + 2) % 3], P, dd0, de0, df0);
-    }
-  }
-  const double S11 = g[0][0], S22 = g[1][1], S33 = g[2][2];
-  const double S12 = 0.5 * (g[0][1] + g[1][0]), S13 = 0.5 * (g[0][2] + g[2][0]), S23 = 0.5 * (g[1][2] + g[2][1]);
-  const double skk3 = (S11 + S22 + S33) * (1.0 / 3.0);
-  const double th = q.T * P.inv_Tref;
-  const double ithS = rcp_nr(th + P.S);
-  const double mu = P.mu_ref * P.one_plus_S * th * sqrt_pos(th) * ithS;
-  double mus = 0.0, Smag = 0.0, cd2 = 0.0, ss = 0.0, cid2 = 0.0, pis = 0.0;
-  if (P.sgs) {
-    ss = S11 * S11 + S22 * S22 + S33 * S33 + 2.0 * (S12 * S12 + S13 * S13 + S23 * S23);
-    Smag = sqrt_nn(2.0 * ss);
-    double d2 = icbrt(J);  // (1/J)^(1/3)
-    cd2 = P.Cs2 * d2 * d2;
-    mus = q.rho * cd2 * Smag;
-    // isotropic SGS stress: sigma_kk / 3 = CI43 rho D^2 S:S, added to the
-    // pressure of the momentum and energy fluxes (not to the sensor or the
-    // spectral radii)
-    cid2 = P.CI43 * d2 * d2;
-    pis = q.rho * cid2 * ss;
-  }
-  const double pe = q.p + pis;
-  const double mt = mu + mus;
-  const double mt2 = 2.0 * mt;
-  const double tau[3][3] = {{mt2 * (S11 - skk3), mt2 * S12, mt2 * S13},
-                            {mt2 * S12, mt2 * (S22 - skk3), mt2 * S23},
-                            {mt2 * S13, mt2 * S23, mt2 * (S33 - skk3)}};
-  const double kap = mu * P.Cp_over_Pr + mus * P.Cp_over_Prsgs;
-  const double uu[3] = {q.u, q.v, q.w};
+#pragma unroll
+    for (int c = 0; c < 10; ++c) pf[c] = 0.0;
 
-  // ---- adjoint accumulators ----
-  double rb = 0, ub[3] = {0, 0, 0}, pb = 0, Tb = 0;  // primitive adjoint
-  double qd[4] = {0, 0, 0, 0};                        // direct Q1..Q4 adjoint
-  double tb[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};  // tau adjoint (full, symmetrised below)
-  double thb[3] = {0, 0, 0};                          // Theta adjoint
-  const double Qv[5] = {q.rho, Q[fe + n], Q[2 * fe + n], Q[3 * fe + n], Q[4 * fe + n]};
-
-  // ---- node flux adjoints Hbar_d = (W(n-e) - W(n+e)) / 2 ----
-  for (int d = 0; d < 3; ++d) {
-    const int di = d == 0, dj = d == 1, dk = d == 2;
-    double Wm[5], Wp[5];
-    Wat(L, M, qb, coef, i - di, j - dj, k - dk, Wm, A.axis);
-    Wat(L, M, qb, coef, i + di, j + dj, k + dk, Wp, A.axis);
-    double Hb[5];
-    bool any = false;
-    for (int c = 0; c < 5; ++c) {
-      Hb[c] = 0.5 * (Wm[c] - Wp[c]);
-      any = any || Hb[c] != 0.0;
-    }
-    if (!any) continue;
-    const double mx = m[3 * d], my = m[3 * d + 1], mz = m[3 * d + 2];
-    const double mm[3] = {mx, my, mz};
-    const double U = mx * q.u + my * q.v + mz * q.w;
-    double Ub = 0.0;
-    // H0 = rho U
-    rb += Hb[0] * U;
-    Ub += Hb[0] * q.rho;
-    // H_{1+a} = Q_{1+a} U + m_a p - m . tau_a
-    for (int a = 0; a < 3; ++a) {
-      qd[a] += Hb[1 + a] * U;
-      Ub += Hb[1 + a] * Qv[1 + a];
-      pb += Hb[1 + a] * mm[a];
-      for (int x = 0; x < 3; ++x) tb[a][x] -= Hb[1 + a] * mm[x];
-    }
-    // H4 = (e + p) U - m . Theta
-    qd[3] += Hb[4] * U;
-    pb += Hb[4] * U;
-    Ub += Hb[4] * (Qv[4] + pe);
-    for (int x = 0; x < 3; ++x) thb[x] -= Hb[4] * mm[x];
-    ub[0] += Ub * mx;
-    ub[1] += Ub * my;
-    ub[2] += Ub * mz;
-  }
-  // so far pb is the adjoint of the flux pressure p + sigma_kk / 3
-  const double peb = pb;
-  // ---- Theta_x = u_a tau_ax + kappa dT/dx ----
-  double kapb = 0.0;
-  double gb[4][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  for (int x = 0; x < 3; ++x) {
-    for (int a = 0; a < 3; ++a) {
-      ub[a] += thb[x] * tau[a][x];
-      tb[a][x] += uu[a] * thb[x];
-    }
-    kapb += thb[x] * g[3][x];
-    gb[3][x] += kap * thb[x];
-  }
-  // ---- tau = 2 mt (S - delta skk/3), symmetric ----
-  const double t11 = tb[0][0], t22 = tb[1][1], t33 = tb[2][2];
-  const double t12 = tb[0][1] + tb[1][0], t13 = tb[0][2] + tb[2][0], t23 = tb[1][2] + tb[2][1];
-  const double mtb = 2.0 * ((S11 - skk3) * t11 + (S22 - skk3) * t22 + (S33 - skk3) * t33 + S12 * t12 + S13 * t13 +
-                            S23 * t23);
-  const double tr = (t11 + t22 + t33) * (1.0 / 3.0);
-  double Sb11 = mt2 * (t11 - tr), Sb22 = mt2 * (t22 - tr), Sb33 = mt2 * (t33 - tr);
-  double Sb12 = mt2 * t12, Sb13 = mt2 * t13, Sb23 = mt2 * t23;
-  // ---- viscosities ----
-  const double mub = mtb + kapb * P.Cp_over_Pr;
-  if (P.sgs) {
-    const double musb = mtb + kapb * P.Cp_over_Prsgs;
-    rb += musb * cd2 * Smag;
-    if (Smag > 0.0) {
-      const double sb = musb * q.rho * cd2 * rcp_nr(Smag);
-      Sb11 += 2.0 * S11 * sb;
-      Sb22 += 2.0 * S22 * sb;
-      Sb33 += 2.0 * S33 * sb;
-      Sb12 += 4.0 * S12 * sb;
-      Sb13 += 4.0 * S13 * sb;
-      Sb23 += 4.0 * S23 * sb;
-    }
-  }
-  if (cid2 != 0.0) {
-    // sigma_kk / 3 = CI43 rho D^2 S:S -> rho and S
-    rb += peb * cid2 * ss;
-    const double ssb = peb * q.rho * cid2;
-    Sb11 += 2.0 * S11 * ssb;
-    Sb22 += 2.0 * S22 * ssb;
-    Sb33 += 2.0 * S33 * ssb;
-    Sb12 += 4.0 * S12 * ssb;
-    Sb13 += 4.0 * S13 * ssb;
-    Sb23 += 4.0 * S23 * ssb;
-  }
-  // Sutherland: dmu/dT = mu (3/(2 th) - 1/(th + S)) / T_ref
-  Tb += mub * mu * (1.5 * rcp_nr(th) - ithS) * P.inv_Tref;
-  // ---- S from the velocity gradient ----
-  gb[0][0] += Sb11;
-  gb[1][1] += Sb22;
-  gb[2][2] += Sb33;
-  gb[0][1] += 0.5 * Sb12;
-  gb[1][0] += 0.5 * Sb12;
-  gb[0][2] += 0.5 * Sb13;
-  gb[2][0] += 0.5 * Sb13;
-  gb[1][2] += 0.5 * Sb23;
-  gb[2][1] += 0.5 * Sb23;
-  // gradient-stencil weights a_{q,d} = J m_d . gbar_q
-  for (int qq = 0; qq < 4; ++qq)
-    for (int d = 0; d < 3; ++d)
-      Wk[(W_A + 3 * qq + d) * fe + n] = J * (m[3 * d] * gb[qq][0] + m[3 * d + 1] * gb[qq][1] + m[3 * d + 2] * gb[qq][2]);
-
-  Wk[W_PRHO * fe + n] = rb;
-  Wk[W_PU * fe + n] = ub[0];
-  Wk[W_PV * fe + n] = ub[1];
-  Wk[W_PW * fe + n] = ub[2];
-  Wk[W_PP * fe + n] = pb;
-  Wk[W_PT * fe + n] = Tb;
-  for (int a = 0; a < 4; ++a) Wk[(W_QD1 + a) * fe + n] = qd[a];
-}
-
-// ---- dissipation adjoint, face by face (pass 1a also stores, per node and
-// direction, Lambda_d, the signed pressure sensor (p+ - 2p + p-) / Sigma and
-// 1 / Sigma) ----
-// Pass 1c (one thread per face (a, b = a + e_d) used by an interior
-// residual): the face's dissipation D = Lf (eps2 dQ - eps4 d3Q) reversed
-// with Dbar = W(b) - W(a).  Stores the face coefficients Lambda eps2,
-// Lambda eps4 (for the gather), half the adjoint of the face mean Lf (one
-// share per end node) and the sensor adjoint k2 eps2bar, given to the end
-// node whose sensor wins max(nu_a, nu_b) (a on ties).
-__global__ void __launch_bounds__(256) k_adj_face(AdjK A, const double* __restrict__ Q, const double* __restrict__ qb,
-                                                  double coef, double* __restrict__ Wk) {
-  const Layout& L = A.L;
-  const Phys& P = A.P;
-  const long long fe = L.fe;
-  const unsigned ni = L.ni, nj = L.nj, nk = L.nk;
-  const unsigned F0 = (ni + 1) * nj * nk, F1 = ni * (nj + 1) * nk, F2 = ni * nj * (nk + 1);
-  unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= F0 + F1 + F2) return;
-  int d, ai, aj, ak;
-  if (t < F0) {
-    d = 0;
-    ai = (int)(t % (ni + 1)) - 1; aj = (int)((t / (ni + 1)) % nj); ak = (int)(t / ((ni + 1) * nj));
-  } else if (t < F0 + F1) {
-    t -= F0;
-    d = 1;
-    ai = (int)(t % ni); aj = (int)((t / ni) % (nj + 1)) - 1; ak = (int)(t / (ni * (nj + 1)));
-  } else {
-    t -= F0 + F1;
-    d = 2;
-    ai = (int)(t % ni); aj = (int)((t / ni) % nj); ak = (int)(t / (ni * nj)) - 1;
-  }
-  const int di = d == 0, dj = d == 1, dk = d == 2;
-  const long long s = dstr(L, d);
-  const long long an = L.at(ai, aj, ak), bn = an + s;
-  const bool axis_face = A.axis && d == 1 && aj == 0;
-  const double La = Wk[(W_LAM + d) * fe + an], Lb = Wk[(W_LAM + d) * fe + bn];
-  const double na = fabs(Wk[(W_NU + d) * fe + an]), nb = fabs(Wk[(W_NU + d) * fe + bn]);
-  const double e2 = P.k2 * (na >= nb ? na : nb);
-  const double e4raw = P.k4 - e2;
-  const bool e4_active = !(0.0 >= e4raw);  // max(0, x) follows 0 on ties
-  const double e4 = e4_active ? e4raw : 0.0;
-  const double Lf = 0.5 * (La + Lb);
-  double Wa[5], Wb[5];
-  Wat(L, A.M, qb, coef, ai, aj, ak, Wa, A.axis);
-  Wat(L, A.M, qb, coef, ai + di, aj + dj, ak + dk, Wb, A.axis);
-  double Lfb = 0.0, e2b = 0.0, e4b = 0.0;
-  for (int c = 0; c < 5; ++c) {
-    const double Db = Wb[c] - Wa[c];
-    Wk[(W_DB + 5 * d + c) * fe + an] = Db;
-    const double* Qc = Q + c * fe;
-    const double d1 = Qc[bn] - Qc[an];
-    // the face between the axis and j = 1 takes the cross-axis value by
-    // linear extrapolation, Q(-1) = 2 Q(0) - Q(1): d3 = Q(2) - 2 Q(1) + Q(0)
-    const double qam = axis_face ? 2.0 * Qc[an] - Qc[bn] : Qc[an - s];
-    const double d3 = Qc[bn + s] - 3.0 * Qc[bn] + 3.0 * Qc[an] - qam;
-    Lfb += Db * (e2 * d1 - e4 * d3);
-    e2b += Db * Lf * d1;
-    e4b -= Db * Lf * d3;
-  }
-  if (e4_active) e2b -= e4b;
-  const bool a_wins = na >= nb;
-  Wk[(W_A2 + d) * fe + an] = Lf * e2;
-  Wk[(W_A4 + d) * fe + an] = Lf * e4;
-  Wk[(W_LH + d) * fe + an] = 0.5 * Lfb;
-  Wk[(W_NUA + d) * fe + an] = a_wins ? P.k2 * e2b : 0.0;
-  Wk[(W_NUB + d) * fe + an] = a_wins ? 0.0 : P.k2 * e2b;
-}
-
-// Pass 1d (nodes in [-1, n]^3): the node's shares of its two faces per
-// direction, back through Lambda_d(lam_d, lam_e, lam_f), lam = |U| + c|m|
-// and nu_d(p(n-e), p, p(n+e)) to the primitive variables (added to pass 1a's
-// part); stores the sensor weight of p(n +- e) for the gather.
-__global__ void __launch_bounds__(256) k_adj_dnode(AdjK A, const double* __restrict__ Q, double* __restrict__ Wk) {
-  const Layout& L = A.L;
-  const Phys& P = A.P;
-  const long long fe = L.fe;
-  const double* __restrict__ M = A.M;
-  const unsigned ext_i = L.ni + 2, ext_j = L.nj + 2;
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ext_i * ext_j * (unsigned)(L.nk + 2)) return;
-  const int i = (int)(t % ext_i) - 1;
-  const int j = (int)((t / ext_i) % ext_j) - 1;
-  const int k = (int)(t / (ext_i * ext_j)) - 1;
-  const long long n = L.at(i, j, k);
-
-  double rb = 0, ub[3] = {0, 0, 0}, pb = 0;
-  double lamb[3] = {0, 0, 0};
-  bool any = false;
-  // on the polar axis the spectral radii are constants (0 along eta; the
-  // others serve only faces between axis nodes, whose adjoint is 0): only
-  // the pressure sensors depend on the state there
-  const bool on_axis = A.axis && j == 0;
-  Prim q;
-  Radii r0;
-  for (int d = 0; d < 3; ++d) {
-    const long long s = dstr(L, d);
-    const int di = d == 0, dj = d == 1, dk = d == 2;
-    const bool f_lo = face_ok(L, d, i - di, j - dj, k - dk);  // face (n-e, n): node is b
-    const bool f_hi = face_ok(L, d, i, j, k);                 // face (n, n+e): node is a
-    double cpw = 0.0;
-    if (f_lo || f_hi) {
-      if (!any && !on_axis) {
-        q = prim_at(Q, fe, n, P);
-        r0 = radii_at(M, fe, n, q, P);
-        any = true;
+    for (int t = kb - 1; t <= ke; ++t) {
+      CArgs* kq4 = ka;
+      asm volatile("" : "+s"(kq4));
+      const TileArgs* kq = (const TileArgs*)kq4;
+      const Phys& P = kq->A.P;
+      // ---- B ----
+      su[ey][ex] = up1[0]; sv[ey][ex] = up1[1]; sw[ey][ex] = up1[2]; st[ey][ex] = up1[3];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sW[c][ey][ex] = Wc[c];
+      rc = rp1;
+      if (h_use) {
+        double hq[5], hv[5], hu[4], hr, hW[5];
+        const unsigned ho = off(hcol, t);
+        load5(kq->Q, ho, hq);
+        load5(kq->qb, ho, hv);
+        const double hJ = ldo(kq->A.M + sb + 9 * fe, ho);
+        prims(P, hq, hu, hr);
+        Wset(h_in, t, hv, hJ, hW);
+        su[hy2][hx2] = hu[0]; sv[hy2][hx2] = hu[1]; sw[hy2][hx2] = hu[2]; st[hy2][hx2] = hu[3];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) sW[c][hy2][hx2] = hW[c];
       }
-      const double nub = (f_lo ? Wk[(W_NUB + d) * fe + n - s] : 0.0) + (f_hi ? Wk[(W_NUA + d) * fe + n] : 0.0);
-      if (!on_axis) {
-        const double Lamb = (f_lo ? Wk[(W_LH + d) * fe + n - s] : 0.0) + (f_hi ? Wk[(W_LH + d) * fe + n] : 0.0);
-        // Lambda_d(n) -> lam_d, lam_e, lam_f
-        double dd0, de0, df0;
-        aniso_d(r0.lam[d], r0.lam[(d + 1) % 3], r0.lam[(d + 2) % 3], P, dd0, de0, df0);
-        lamb[d] += Lamb * dd0;
-        lamb[(d + 1) % 3] += Lamb * de0;
-        lamb[(d + 2) % 3] += Lamb * df0;
-      }
-      // nu_d(n) = |Delta2| / Sigma with p(n-e), p(n), p(n+e): from the
-      // pre-pass, Delta2 / Sigma (signed) and 1 / Sigma
-      const double ns = Wk[(W_NU + d) * fe + n], iSg = Wk[(W_IS + d) * fe + n];
-      const double sd = sgn(ns) * iSg, sv = fabs(ns) * iSg;
-      pb += nub * (-2.0 * sd - 2.0 * sv);
-      cpw = nub * (sd - sv);  // weight of p(n - e) and p(n + e)
-    }
-    Wk[(W_CP + d) * fe + n] = cpw;
-  }
-  if (on_axis) {
-    Wk[W_PP * fe + n] += pb;
-    return;
-  }
-  if (!any) return;
-  // lam_e = |U_e| + c |m_e|
-  double cb = 0.0;
-  for (int e = 0; e < 3; ++e) {
-    if (lamb[e] == 0.0) continue;
-    const double Ueb = sgn(r0.U[e]) * lamb[e];
-    cb += r0.nrm[e] * lamb[e];
-    ub[0] += Ueb * M[(3 * e) * fe + n];
-    ub[1] += Ueb * M[(3 * e + 1) * fe + n];
-    ub[2] += Ueb * M[(3 * e + 2) * fe + n];
-  }
-  // c = sqrt(gamma p / rho)
-  if (cb != 0.0) {
-    const double ir2 = rcp_nr(2.0 * q.rho);
-    pb += cb * P.gamma * rcp_nr(r0.c) * ir2;
-    rb -= cb * r0.c * ir2;
-  }
-  Wk[W_PRHO * fe + n] += rb;
-  Wk[W_PU * fe + n] += ub[0];
-  Wk[W_PV * fe + n] += ub[1];
-  Wk[W_PW * fe + n] += ub[2];
-  Wk[W_PP * fe + n] += pb;
-}
+      lds_barrier();
 
-// ---------------------------------------------------------------------------
-// Pass 2
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool in_b1(const Layout& L, int i, int j, int k) {
-  return i >= -1 && i <= L.ni && j >= -1 && j <= L.nj && k >= -1 && k <= L.nk;
+      // ---- C ----
+      prims(P, qn, up1, rp1);  // plane t+1
+      double Wp[5];
+      Wset(in_ij, t + 1, bn, Jn, Wp);
+      double m[9], J;
+      read_metric_rows(&mbw[wave][0][ty & 1][tx], m, J);
+      const char* const msrc = (const char*)(kq->A.M + lane_el + (long long)clampi(t + 1, -2, L.nk + 1) * L.sk);
+      const unsigned on = off(col, t + 2);
+      auto load_ahead = [&](int q) {
+        if (t < ke) {
+          copy_to_lds(msrc + q * fstep2, mdst + q * 128);
+          qn[q] = ldo(kq->Q + sb + q * fe, on);
+          bn[q] = ldo(kq->qb + sb + q * fe, on);
+          if (q == 4) Jn = ldo(kq->A.M + sb + 9 * fe, on);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      double g[4][3];
+      {
+        const double(*F[4])[EX] = {su, sv, sw, st};
+        const double Jh = 0.5 * J;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const double dx = F[q][ey][ex + 1] - F[q][ey][ex - 1];
+          const double dy = F[q][ey + 1][ex] - F[q][ey - 1][ex];
+          const double dz = up1[q] - um1[q];
+#pragma unroll
+          for (int x = 0; x < 3; ++x) g[q][x] = Jh * (m[x] * dx + m[3 + x] * dy + m[6 + x] * dz);
+        }
+      }
+      load_ahead(0);
+      const double uu[3] = {su[ey][ex], sv[ey][ex], sw[ey][ex]}, T = st[ey][ex], rho = rc;
+      const double S11 = g[0][0], S22 = g[1][1], S33 = g[2][2];
+      const double S12 = 0.5 * (g[0][1] + g[1][0]), S13 = 0.5 * (g[0][2] + g[2][0]), S23 = 0.5 * (g[1][2] + g[2][1]);
+      const double skk3 = (S11 + S22 + S33) * (1.0 / 3.0);
+      const double th = T * P.inv_Tref;
+      const double ithS = rcp_nr(th + P.S);
+      const double mu = P.mu_ref * P.one_plus_S * th * sqrt_pos(th) * ithS;
+      double mus = 0.0, Smag = 0.0, cd2 = 0.0, ss = 0.0, cid2 = 0.0;
+      if (P.sgs) {
+        ss = S11 * S11 + S22 * S22 + S33 * S33 + 2.0 * (S12 * S12 + S13 * S13 + S23 * S23);
+        Smag = sqrt_nn(2.0 * ss);
+        const double d2 = icbrt(J);  // (1/J)^(1/3)
+        cd2 = P.Cs2 * d2 * d2;
+        mus = rho * cd2 * Smag;
+        // isotropic SGS stress: sigma_kk / 3 = CI43 rho D^2 S:S, added to the
+        // pressure of the momentum and energy fluxes
+        cid2 = P.CI43 * d2 * d2;
+      }
+      const double mt2 = 2.0 * (mu + mus);
+      const double t11 = mt2 * (S11 - skk3), t22 = mt2 * (S22 - skk3), t33 = mt2 * (S33 - skk3);
+      const double t12 = mt2 * S12, t13 = mt2 * S13, t23 = mt2 * S23;
+      const double kap = mu * P.Cp_over_Pr + mus * P.Cp_over_Prsgs;
+      load_ahead(1);
+      // ---- reverse of the node fluxes ----
+      double rb = 0, ub[3] = {0, 0, 0}, pb = 0, qd[4] = {0, 0, 0, 0};
+      double tb11 = 0, tb22 = 0, tb33 = 0, tb12 = 0, tb13 = 0, tb23 = 0, thb[3] = {0, 0, 0};
+      {
+        const double p = rho * T * kq->Rg;
+        const double eh = p * kq->inv_gm1 + 0.5 * rho * (uu[0] * uu[0] + uu[1] * uu[1] + uu[2] * uu[2]) + p +
+                          rho * cid2 * ss;  // e + p + sigma_kk / 3
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          double Hb[5];
+#pragma unroll
+          for (int c = 0; c < 5; ++c)
+            Hb[c] = 0.5 * (d == 0   ? sW[c][ey][ex - 1] - sW[c][ey][ex + 1]
+                           : d == 1 ? sW[c][ey - 1][ex] - sW[c][ey + 1][ex]
+                                    : Wm[c] - Wp[c]);
+          const double mx = m[3 * d], my = m[3 * d + 1], mz = m[3 * d + 2];
+          const double U = mx * uu[0] + my * uu[1] + mz * uu[2];
+          // H_0 = rho U, H_{1+a} = Q_{1+a} U + m_a p - m . tau_a, H_4 = (e + p) U - m . Theta
+          const double Ub = rho * (Hb[0] + Hb[1] * uu[0] + Hb[2] * uu[1] + Hb[3] * uu[2]) + Hb[4] * eh;
+          rb += Hb[0] * U;
+          qd[0] += Hb[1] * U;
+          qd[1] += Hb[2] * U;
+          qd[2] += Hb[3] * U;
+          qd[3] += Hb[4] * U;
+          pb += Hb[1] * mx + Hb[2] * my + Hb[3] * mz + Hb[4] * U;
+          tb11 -= Hb[1] * mx;
+          tb22 -= Hb[2] * my;
+          tb33 -= Hb[3] * mz;
+          tb12 -= Hb[1] * my + Hb[2] * mx;
+          tb13 -= Hb[1] * mz + Hb[3] * mx;
+          tb23 -= Hb[2] * mz + Hb[3] * my;
+          thb[0] -= Hb[4] * mx;
+          thb[1] -= Hb[4] * my;
+          thb[2] -= Hb[4] * mz;
+          ub[0] += Ub * mx;
+          ub[1] += Ub * my;
+          ub[2] += Ub * mz;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      load_ahead(2);
+      // Theta_x = u_a tau_ax + kappa dT/dx
+      ub[0] += thb[0] * t11 + thb[1] * t12 + thb[2] * t13;
+      ub[1] += thb[0] * t12 + thb[1] * t22 + thb[2] * t23;
+      ub[2] += thb[0] * t13 + thb[1] * t23 + thb[2] * t33;
+      tb11 += uu[0] * thb[0];
+      tb22 += uu[1] * thb[1];
+      tb33 += uu[2] * thb[2];
+      tb12 += uu[0] * thb[1] + uu[1] * thb[0];
+      tb13 += uu[0] * thb[2] + uu[2] * thb[0];
+      tb23 += uu[1] * thb[2] + uu[2] * thb[1];
+      const double kapb = thb[0] * g[3][0] + thb[1] * g[3][1] + thb[2] * g[3][2];
+      // tau = 2 (mu + mu_sgs) (S - delta S_kk / 3); the off-diagonal adjoints
+      // are those of the pair (12, 21), ...
+      const double mtb = 2.0 * ((S11 - skk3) * tb11 + (S22 - skk3) * tb22 + (S33 - skk3) * tb33 + S12 * tb12 +
+                                S13 * tb13 + S23 * tb23);
+      const double trb = (tb11 + tb22 + tb33) * (1.0 / 3.0);
+      double Sb11 = mt2 * (tb11 - trb), Sb22 = mt2 * (tb22 - trb), Sb33 = mt2 * (tb33 - trb);
+      double Sb12 = mt2 * tb12, Sb13 = mt2 * tb13, Sb23 = mt2 * tb23;
+      const double mub = mtb + kapb * P.Cp_over_Pr;
+      if (P.sgs) {
+        const double musb = mtb + kapb * P.Cp_over_Prsgs;
+        rb += musb * cd2 * Smag + pb * cid2 * ss;
+        double sb2 = 2.0 * pb * rho * cid2;
+        if (Smag > 0.0) sb2 += 2.0 * musb * rho * cd2 * rcp_nr(Smag);
+        Sb11 += S11 * sb2;
+        Sb22 += S22 * sb2;
+        Sb33 += S33 * sb2;
+        Sb12 += 2.0 * S12 * sb2;
+        Sb13 += 2.0 * S13 * sb2;
+        Sb23 += 2.0 * S23 * sb2;
+      }
+      // Sutherland: dmu/dT = mu (3/(2 th) - 1/(th + S)) / T_ref
+      double Tb = mub * mu * (1.5 * rcp_nr(th) - ithS) * P.inv_Tref;
+      load_ahead(3);
+      // gradient-stencil weights (half of them: the halves of the central
+      // differences): a_{q,d} = J/2 m_d . gbar_q, gbar_3 = kappa Theta-bar
+      double aw[4][3];
+      {
+        const double Jh = 0.5 * J, kh = kap;
+        const double G[4][3] = {{Sb11, 0.5 * Sb12, 0.5 * Sb13},
+                                {0.5 * Sb12, Sb22, 0.5 * Sb23},
+                                {0.5 * Sb13, 0.5 * Sb23, Sb33},
+                                {kh * thb[0], kh * thb[1], kh * thb[2]}};
+        const bool act = b1_ij && t >= -1 && t <= L.nk;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            const double x = Jh * (m[3 * d] * G[q][0] + m[3 * d + 1] * G[q][1] + m[3 * d + 2] * G[q][2]);
+            aw[q][d] = act ? x : 0.0;
+          }
+        if (!act) {
+          rb = pb = Tb = 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) ub[c] = 0.0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) qd[c] = 0.0;
+        }
+      }
+      load_ahead(4);
+      if (!xh) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sa[q][ty][tx - 1] = aw[q][1];
+      }
+      // zeta: the weights of plane t complete plane t-1, those of t-1 open plane t
+      double dphi[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        pf[q < 3 ? 1 + q : 5] -= aw[q][2];
+        dphi[q] = a2[q] + (lane_prev(aw[q][0]) - lane_next(aw[q][0]));
+        a2[q] = aw[q][2];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // finish plane t-1: map to conserved variables
+      double o[5];
+      {
+        const double ir = rcp_nr(rm1);
+        const bool any = pf[0] != 0.0 || pf[1] != 0.0 || pf[2] != 0.0 || pf[3] != 0.0 || pf[4] != 0.0 || pf[5] != 0.0;
+        const double pt = pf[4] + pf[5] * P.inv_R * ir, gp = P.gm1 * pt;
+        const double ut = um1[0] * um1[0] + um1[1] * um1[1] + um1[2] * um1[2];
+        o[0] = pf[0] - pf[5] * um1[3] * ir + 0.5 * gp * ut - (pf[1] * um1[0] + pf[2] * um1[1] + pf[3] * um1[2]) * ir;
+        o[1] = pf[6] + pf[1] * ir - gp * um1[0];
+        o[2] = pf[7] + pf[2] * ir - gp * um1[1];
+        o[3] = pf[8] + pf[3] * ir - gp * um1[2];
+        o[4] = pf[9] + gp;
+        // (nodes without any adjoint skip the map: unused ghost corners may hold anything)
+        o[0] = any ? o[0] : 0.0;
+#pragma unroll
+        for (int c = 1; c < 5; ++c) o[c] = any ? o[c] : pf[5 + c];
+      }
+      lds_barrier();
+
+      // ---- E ----
+      if (out_ok) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dphi[q] += sa[q][ty - 1][tx - 1] - sa[q][ty + 1][tx - 1];
+      }
+      pf[0] = rb;
+      pf[1] = ub[0] + dphi[0];
+      pf[2] = ub[1] + dphi[1];
+      pf[3] = ub[2] + dphi[2];
+      pf[4] = pb;
+      pf[5] = Tb + dphi[3];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) pf[6 + c] = qd[c];
+      um1[0] = su[ey][ex]; um1[1] = sv[ey][ex]; um1[2] = sw[ey][ex]; um1[3] = st[ey][ex];
+      rm1 = rc;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        Wm[c] = sW[c][ey][ex];
+        Wc[c] = Wp[c];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm<0>();  // the loads of this plane, before the stores (see les_stage.hip)
+      if (out_ok && t > kb) {
+        const unsigned on1 = col + (unsigned)(t - 1 - kr) * sk;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) sto(kq->Wk + (W_FL + c) * fe + sb, on1, o[c]);
+      }
+      // (the next B overwrites LDS that this plane's C read: every wave is past
+      // the barrier above; E reads only the eta weights, next written after
+      // the next plane's first barrier, and the thread's own node)
+    }
+  }
 }
 
 // Does interior node (i, j, k) have ghost images: a periodic image along an
@@ -568,126 +515,499 @@ __device__ __forceinline__ bool has_images(const AdjK& A, int i, int j, int k) {
   return false;
 }
 
-// Last steps at an interior node whose adjoint q is complete: in the
+// Last step at an interior node whose adjoint q is complete: in the
 // Runge-Kutta reverse, fbar[c][k][j] += fw q_c on the source plane (fbar
-// non-null, on_f) and, after the last stage, qfin = acc + q (qfin non-null).
-__device__ __forceinline__ void finish_node(const Layout& L, long long n, int j, int k, const double q[5],
-                                            const double* __restrict__ acc, double* __restrict__ fbar, bool on_f,
-                                            double fw, double* __restrict__ qfin, int c0 = 0, int c1 = 5) {
+// non-null, on_f).
+__device__ __forceinline__ void finish_node(const Layout& L, int j, int k, const double q[5], double* __restrict__ fbar,
+                                            bool on_f, double fw, int c0 = 0, int c1 = 5) {
   if (fbar && on_f)
     for (int c = c0; c < c1; ++c) fbar[((long long)c * L.nk + k) * L.nj + j] += fw * q[c];
-  if (qfin)
-    for (int c = c0; c < c1; ++c) qfin[c * L.fe + n] = acc[c * L.fe + n] + q[c];
 }
 
-// Pass 2 runs over B = R_i x R_j x R_k, R_d = [lo_d, hi_d]: the ghost layers
-// are included along a periodic axis and on the active faces of a Dirichlet
-// axis (frozen Dirichlet ghosts carry no dependence).  An interior node
-// writes its gather to qout (and, in the Runge-Kutta reverse, does
-// acc += accsrc); a ghost node -- a periodic image or a face ghost of an
-// interior node -- writes it to W_GG for pass 3.
-__global__ void __launch_bounds__(256) k_adj_gather(AdjK A, const double* __restrict__ Q, double* __restrict__ Wk,
-                                                    double* __restrict__ qout, double* __restrict__ acc,
-                                                    const double* __restrict__ accsrc, double* __restrict__ fbar,
-                                                    int i_f, double fw, double* __restrict__ qfin) {
-  const Layout& L = A.L;
-  const Phys& P = A.P;
-  const long long fe = L.fe;
-  const unsigned ri = A.hi[0] - A.lo[0] + 1, rj = A.hi[1] - A.lo[1] + 1, rk = A.hi[2] - A.lo[2] + 1;
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ri * rj * rk) return;
-  const int i = (int)(t % ri) + A.lo[0];
-  const int j = (int)((t / ri) % rj) + A.lo[1];
-  const int k = (int)(t / (ri * rj)) + A.lo[2];
-  const long long n = L.at(i, j, k);
-  const bool b1 = in_b1(L, i, j, k);
+// ---------------------------------------------------------------------------
+// Dissipation pass: the adjoint of the Turkel-Vatsa faces, complete at every
+// output node, added to the flux pass's part.
+//
+// For the face (a, b = a + e_d) used by an interior residual,
+// D = Lf (eps2 dQ - eps4 d3Q) is reversed with Dbar = W(b) - W(a):
+//   - directly to the four states of its stencil: +-F and +-G with
+//     F = Lf (eps2 + 3 eps4) Dbar, G = Lf eps4 Dbar;
+//   - through the face mean Lf: half of sum_c Dbar_c (eps2 dQ - eps4 d3Q)_c to
+//     Lambda_d of either end, and by V_d = dLambda_d / dQ to the end's state;
+//   - through eps2 and eps4 to the sensor of the end that wins the maximum (a
+//     on ties; max(0, k4 - eps2) follows 0 on ties), and from
+//     nu = |p+ - 2p + p-| / Sigma to p at the end and its two neighbours.
+// An output node therefore depends on the faces n-2e .. n+e of each line and
+// on states up to three nodes away: blocks of 32 x 16 threads own a patch
+// whose inner 28 x 12 nodes are the tile, march in k like the stage kernel and
+// evaluate every face of the patch once.  Per plane t
+//   B  stores Q, p and W of the patch (Q, p also of one ring along the axes);
+//   C  forms the radii, sensors and V_d of the plane's nodes and the whole xi
+//      direction (a patch row is 32 lanes: neighbours by lane shifts), then the
+//      zeta face (t-1, t) from registers;
+//   D  evaluates the eta faces (one per node and row) into LDS;
+//   E  gathers the eta faces, and stores plane t-2, which the zeta face
+//      completed.
+// One read of Q, the metrics, Rbar and the flux part and one write, instead of
+// two passes that wrote and re-read 45 fields through the caches.  The xi
+// faces and V_d stay in registers; V_1 and the eta faces go through LDS, and
+// the loads of the next plane are issued after the zeta face, because the 512
+// threads' 256 registers do not hold them beside it (with all of it in
+// registers: 183 spills and 300 us on the 128 x 64 x 64 jet).  Bound by the
+// FP64 issue rate, a patch having 1.5 times its tile's nodes: 97 us on that
+// jet and 138 us on the 128 x 64 x 121 O-grid, where the passes replaced took
+// 199 and 404 us (with the flux pass: 269 to 147 and 536 to 219 us).
+// ---------------------------------------------------------------------------
+constexpr int DTX = BX - 4, DTY = BY - 4;  // output tile of the dissipation pass
+constexpr int DNH = 2 * DTX + 2 * DTY;     // ring nodes
 
-  double rb = 0, ub[3] = {0, 0, 0}, pb = 0, Tb = 0;
-  double out[5] = {0, 0, 0, 0, 0};
-  if (b1) {
-    rb = Wk[W_PRHO * fe + n];
-    ub[0] = Wk[W_PU * fe + n];
-    ub[1] = Wk[W_PV * fe + n];
-    ub[2] = Wk[W_PW * fe + n];
-    pb = Wk[W_PP * fe + n];
-    Tb = Wk[W_PT * fe + n];
-    for (int a = 0; a < 4; ++a) out[1 + a] += Wk[(W_QD1 + a) * fe + n];
+// Keeps the computation of x before this point (the compiler would sink it to
+// the use, past a barrier, with all of its inputs alive).
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
+
+struct DissArgs {
+  TileArgs t;
+  double* qout;
+  double* fbar;
+  double fw;
+  int i_f;
+};
+
+// eps2, eps4 and the reversed sensor part of one face; e2b is the adjoint of
+// eps2 (with eps4's share where it is active)
+__device__ __forceinline__ void face_rev(const Phys& P, double La, double Lb, double nsa, double nsb,
+                                         const double qam[5], const double qa[5], const double qb[5],
+                                         const double qbp[5], const double Db[5], bool ok, double F[5], double G[5],
+                                         double& LH, double& NA, double& NB) {
+  const double na = fabs(nsa), nb = fabs(nsb);
+  const bool aw = na >= nb;
+  const double e2 = P.k2 * (aw ? na : nb);
+  const double e4r = P.k4 - e2;
+  const bool act = !(0.0 >= e4r);
+  const double e4 = act ? e4r : 0.0;
+  const double Lf = 0.5 * (La + Lb);
+  double s1 = 0.0, s3 = 0.0;
+  const double wf = Lf * (e2 + 3.0 * e4), wg = Lf * e4;
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {
+    const double d1 = qb[c] - qa[c];
+    const double d3 = qbp[c] - 3.0 * qb[c] + 3.0 * qa[c] - qam[c];
+    s1 += Db[c] * d1;
+    s3 += Db[c] * d3;
+    F[c] = ok ? wf * Db[c] : 0.0;
+    G[c] = ok ? wg * Db[c] : 0.0;
   }
-  // gradient-stencil and sensor weights of the neighbours
-  for (int d = 0; d < 3; ++d) {
-    const int di = d == 0, dj = d == 1, dk = d == 2;
-    const long long s = dstr(L, d);
-    const bool lo = in_b1(L, i - di, j - dj, k - dk), hi = in_b1(L, i + di, j + dj, k + dk);
-    double phib[4] = {0, 0, 0, 0};
-    for (int qq = 0; qq < 4; ++qq) {
-      const double* a = Wk + (W_A + 3 * qq + d) * fe;
-      phib[qq] = 0.5 * ((lo ? a[n - s] : 0.0) - (hi ? a[n + s] : 0.0));
+  const double e2b = P.k2 * Lf * (act ? s1 + s3 : s1);
+  LH = ok ? 0.5 * (e2 * s1 - e4 * s3) : 0.0;
+  NA = ok && aw ? e2b : 0.0;
+  NB = ok && !aw ? e2b : 0.0;
+}
+
+// HALF: the anisotropy exponent is 1/2 (no pow in that instantiation)
+template <bool HALF>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) k_adj_diss(DissArgs a) {
+  __shared__ double sq[5][EY][EX], sp[EY][EX];
+  __shared__ double sW[5][BY][BX];
+  __shared__ double ly[BY][DTX], ny[BY][DTX], cy[BY][DTX];  // eta radius, signed sensor, 1 / Sigma; columns 2..DTX+1
+  __shared__ double fF[5][BY - 1][DTX], fG[5][BY - 1][DTX], fL[BY - 1][DTX], fA[BY - 1][DTX], fB[BY - 1][DTX];
+  __shared__ double sV[5][BY][DTX];  // V_1 of the plane
+  __shared__ double mbw[NW][10][2][BX];
+  const TileArgs& ta = a.t;
+  const Layout& L = ta.A.L;
+  typedef __attribute__((address_space(4))) const DissArgs CArgs;
+  CArgs* const ka = (CArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  const long long fe = L.fe;
+  const int hb = blockIdx.x;
+  const int v = (hb % ta.nxcd) * ta.per_xcd + hb / ta.nxcd;
+  if (v >= ta.nblocks) return;
+  const int tid = threadIdx.x;
+  const int tx = tid % BX, ty = tid / BX, ex = tx + 1, ey = ty + 1, cx = tx - 2;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const bool cx_ok = tx >= 2 && tx < BX - 2, ry_ok = ty >= 2 && ty < BY - 2;
+  const unsigned sk = (unsigned)L.sk;
+  const double coef = ta.coef;
+  const int axis = ta.A.axis;
+  int hx2 = 0, hy2 = 0;  // ring slot of helper thread tid < DNH
+  {
+    const int h = tid;
+    if (h < DTY) { hx2 = 0; hy2 = 3 + h; }
+    else if (h < 2 * DTY) { hx2 = EX - 1; hy2 = 3 + h - DTY; }
+    else if (h < 2 * DTY + DTX) { hy2 = 0; hx2 = 3 + h - 2 * DTY; }
+    else if (h < DNH) { hy2 = EY - 1; hx2 = 3 + h - 2 * DTY - DTX; }
+  }
+  for (int wq = v; wq < ta.nseg; wq += ta.nblocks) {
+    const int ntiles = ta.ntx * ta.nty;
+    const int ch = wq / ntiles, tile = wq % ntiles;
+    const int kb = ta.A.lo[2] + ch * ta.kc, ke = min(ta.A.hi[2] + 1, kb + ta.kc);  // output planes
+    // (tiles start one node before the output box in i, so that row copies are
+    // 16-byte aligned)
+    const int i = ta.A.lo[0] - 3 + (tile % ta.ntx) * DTX + tx, j = ta.A.lo[1] - 2 + (tile / ta.ntx) * DTY + ty;
+    const bool ii = i >= 0 && i < L.ni, jj = j >= 0 && j < L.nj;
+    const bool in_ij = ii && jj && !(axis && j == 0);               // W may be nonzero
+    const bool b1_ij = i >= -1 && i <= L.ni && j >= -1 && j <= L.nj;  // radii and sensors exist
+    const bool fx_ij = jj && i >= -1 && i < L.ni && tx < BX - 1;     // xi face (i, i + 1)
+    const bool fy_ij = ii && j >= -1 && j < L.nj && ty < BY - 1 && cx_ok;
+    const bool out_ok = cx_ok && ry_ok && i >= ta.A.lo[0] && i <= ta.A.hi[0] && j <= ta.A.hi[1];
+    const int hi = i - tx + hx2 - 1, hj = j - ty + hy2 - 1;
+    const int kr = kb - 4;
+    const long long sb = (long long)kr * L.sk;
+    const unsigned col = (unsigned)((long long)clampi(i, -2, L.ni + 1) + (long long)clampi(j, -2, L.nj + 1) * L.sj + L.o);
+    const unsigned hcol =
+        (unsigned)((long long)clampi(hi, -2, L.ni + 1) + (long long)clampi(hj, -2, L.nj + 1) * L.sj + L.o);
+    auto off = [&](unsigned c, int k) { return c + (unsigned)(clampi(k, -2, L.nk + 1) - kr) * sk; };
+    const int fsel = lane >> 5, rsel = (lane / 16) % 2, pr = lane % 16;
+    int icp = i - tx + 2 * pr;
+    if (icp > L.ni) icp = L.ni - ((LEAD + L.ni) & 1);
+    const int jcp = clampi(j - ty + 2 * wave + rsel, -2, L.nj + 1);
+    const long long lane_el = (long long)fsel * fe + L.o + icp + (long long)jcp * L.sj;
+    const long long fstep2 = 2 * fe * (long long)sizeof(double);
+    double* const mdst = &mbw[wave][0][0][0];
+
+    double qm2[5], qm1[5], qw[5], qa[5], qn[5];  // Q at t-2, t-1, t (at B), t+1 and t+2 (in flight)
+    double hq[5];                                // ring node, next plane
+    double bn[5], Jn;                            // Rbar and J of the next plane (in flight)
+    double Wm[5], Wc[5];                         // W at t-1, t (at B)
+    double pm1, pc, pp1;                         // p at t-1, t, t+1
+    double L2 = 0, ns2 = 0, iS2 = 0, nbz = 0;    // plane t-1: zeta radius, sensor, 1 / Sigma, sensor adjoint of its lower face
+    double V2[5], Gz[5], om1[5], om2[5], pb1 = 0, pb2 = 0;  // V_2 at t-1; G of the last zeta face; planes t-1, t-2
+    auto load5 = [&](const double* f, unsigned o, double x[5]) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) x[c] = ldo(f + sb + c * fe, o);
+    };
+    auto Wset = [&](int k, double W[5]) {
+      const bool ok = in_ij && k >= 0 && k < L.nk;
+      const double s = coef * Jn;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) W[c] = ok ? s * bn[c] : 0.0;
+    };
+    auto pres = [&](const Phys& P, const double q[5]) {
+      return P.gm1 * (q[4] - 0.5 * (q[1] * q[1] + q[2] * q[2] + q[3] * q[3]) * rcp_nr(q[0]));
+    };
+    {
+      CArgs* kp4 = ka;
+      asm volatile("" : "+s"(kp4));
+      const DissArgs* kp = (const DissArgs*)kp4;
+      const char* msrc = (const char*)(kp->t.A.M + lane_el + (long long)clampi(kb - 2, -2, L.nk + 1) * L.sk);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) copy_to_lds(msrc + q * fstep2, mdst + q * 128);
+      load5(kp->t.Q, off(col, kb - 3), qm1);
+      load5(kp->t.Q, off(col, kb - 2), qw);
+      load5(kp->t.Q, off(col, kb - 1), qa);
+      if (tid < DNH) load5(kp->t.Q, off(hcol, kb - 2), hq);
+      load5(kp->t.qb, off(col, kb - 2), bn);
+      Jn = ldo(kp->t.A.M + sb + 9 * fe, off(col, kb - 2));
+      pm1 = pres(kp->t.A.P, qm1);
+      pp1 = pres(kp->t.A.P, qw);
+      Wset(kb - 2, Wc);
+      wait_vm<0>();
     }
-    ub[0] += phib[0];
-    ub[1] += phib[1];
-    ub[2] += phib[2];
-    Tb += phib[3];
-    const double* cp = Wk + (W_CP + d) * fe;
-    pb += (lo ? cp[n - s] : 0.0) + (hi ? cp[n + s] : 0.0);
-  }
-  // primitive adjoint -> conserved variables (nodes without any adjoint skip
-  // the map, so unused ghost corners are never read)
-  if (rb != 0.0 || ub[0] != 0.0 || ub[1] != 0.0 || ub[2] != 0.0 || pb != 0.0 || Tb != 0.0) {
-  const Prim q = prim_at(Q, fe, n, P);
-  const double ir = rcp_nr(q.rho);
-  pb += Tb * P.inv_R * ir;
-  rb -= Tb * q.T * ir;
-  out[4] += P.gm1 * pb;
-  out[1] -= P.gm1 * q.u * pb;
-  out[2] -= P.gm1 * q.v * pb;
-  out[3] -= P.gm1 * q.w * pb;
-  out[0] += P.gm1 * 0.5 * (q.u * q.u + q.v * q.v + q.w * q.w) * pb;
-  out[1] += ub[0] * ir;
-  out[2] += ub[1] * ir;
-  out[3] += ub[2] * ir;
-  out[0] -= (ub[0] * q.u + ub[1] * q.v + ub[2] * q.w) * ir;
-  out[0] += rb;
-  }
-  // dissipation faces whose five-point stencil contains this node:
-  //   face a = n-e (node is b):    +(A2 + 3 A4) Dbar
-  //   face a = n   (node is a):    -(A2 + 3 A4) Dbar
-  //   face a = n-2e (node is b+e): -A4 Dbar
-  //   face a = n+e (node is a-e):  +A4 Dbar
-  for (int d = 0; d < 3; ++d) {
-    const int di = d == 0, dj = d == 1, dk = d == 2;
-    const long long s = dstr(L, d);
-    const int off[4] = {-1, 0, -2, 1};
-    for (int r = 0; r < 4; ++r) {
-      const int ai = i + off[r] * di, aj = j + off[r] * dj, ak = k + off[r] * dk;
-      if (!face_ok(L, d, ai, aj, ak)) continue;
-      const long long an = n + off[r] * s;
-      const double A2 = Wk[(W_A2 + d) * fe + an], A4 = Wk[(W_A4 + d) * fe + an];
-      double w = r == 0 ? (A2 + 3.0 * A4) : (r == 1 ? -(A2 + 3.0 * A4) : (r == 2 ? -A4 : A4));
-      if (A.axis && d == 1 && aj == 0) {
-        // the face between the axis and j = 1: d3 = Q(2) - 2 Q(1) + Q(0)
-        // (the cross-axis value linearly extrapolated), so the axis node
-        // takes -(A2 + A4), node j = 1 takes A2 + 2 A4 and the ghost below
-        // the axis nothing
-        w = r == 0 ? (A2 + 2.0 * A4) : (r == 1 ? -(A2 + A4) : (r == 2 ? -A4 : 0.0));
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      qm2[c] = qm1[c];
+      Wm[c] = V2[c] = Gz[c] = om1[c] = om2[c] = qn[c] = 0.0;
+    }
+
+    for (int t = kb - 2; t <= ke + 1; ++t) {
+      CArgs* kq4 = ka;
+      asm volatile("" : "+s"(kq4));
+      const DissArgs* kq = (const DissArgs*)kq4;
+      const Phys& P = kq->t.A.P;
+      const bool inner = t >= kb && t < ke && t >= 0 && t < L.nk;  // in-plane faces of output nodes
+      // (LDS addresses are formed again in each plane: kept over the loop they
+      // would spill)
+      int tl = tid;
+      asm volatile("" : "+v"(tl));
+      const int tx = tl % BX, ty = tl / BX, ex = tx + 1, ey = ty + 1, cx = tx - 2;
+      // ---- B ----
+      pc = pp1;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sq[c][ey][ex] = qw[c];
+      sp[ey][ex] = pc;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sW[c][ty][tx] = Wc[c];
+      if (tid < DNH) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) sq[c][hy2][hx2] = hq[c];
+        sp[hy2][hx2] = pres(P, hq);
       }
-      if (w == 0.0) continue;
-      // Dbar of the face, stored by the face pass
-      for (int c = 0; c < 5; ++c) out[c] += w * Wk[(W_DB + 5 * d + c) * fe + an];
+      lds_barrier();
+
+      // ---- C ----
+      pp1 = pres(P, qa);
+      double m[9], J;
+      read_metric_rows(&mbw[wave][0][ty & 1][tx], m, J);
+      const char* const msrc = (const char*)(kq->t.A.M + lane_el + (long long)clampi(t + 1, -2, L.nk + 1) * L.sk);
+      const unsigned on = off(col, t + 2), ob = off(col, t + 1), oh = off(hcol, t + 1);
+      auto load_ahead = [&](int q) {
+        if (t <= ke) {
+          copy_to_lds(msrc + q * fstep2, mdst + q * 128);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      load_ahead(0);
+      const bool b1 = b1_ij && t >= -1 && t <= L.nk;
+      const bool rad = b1 && !(axis && j <= 0);  // (on and below the polar axis the radii are constants, 0)
+      double oc[5] = {0, 0, 0, 0, 0}, pbc = 0.0;  // plane t: conserved and pressure adjoint
+      double Lam0, Lam1, Lam2, V0[5], V2n[5];
+      {
+        // radii, Lambda_d and V_d = dLambda_d / dQ
+        const double rho = sq[0][ey][ex], ir = rcp_nr(rho);
+        const double u[3] = {sq[1][ey][ex] * ir, sq[2][ey][ex] * ir, sq[3][ey][ex] * ir};
+        const double c2 = P.gamma * pc * ir;
+        const double cs = sqrt_pos(c2);
+        double lam[3], sg[3], nrm[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          const double mx = m[3 * e], my = m[3 * e + 1], mz = m[3 * e + 2];
+          const double U = mx * u[0] + my * u[1] + mz * u[2];
+          nrm[e] = sqrt_pos(mx * mx + my * my + mz * mz);
+          lam[e] = fabs(U) + cs * nrm[e];
+          sg[e] = sgn(U);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        double w[3][3], Lam[3];  // w[d][e] = dLambda_d / dlam_e
+        if (HALF) {
+          const double s0 = sqrt_pos(lam[0]), s1 = sqrt_pos(lam[1]), s2 = sqrt_pos(lam[2]);
+          const double h0 = 0.5 * rcp_nr(s0), h1 = 0.5 * rcp_nr(s1), h2 = 0.5 * rcp_nr(s2);
+          Lam[0] = lam[0] + s0 * (s1 + s2);
+          Lam[1] = lam[1] + s1 * (s2 + s0);
+          Lam[2] = lam[2] + s2 * (s0 + s1);
+          w[0][0] = 1.0 + (s1 + s2) * h0; w[0][1] = s0 * h1; w[0][2] = s0 * h2;
+          w[1][1] = 1.0 + (s2 + s0) * h1; w[1][2] = s1 * h2; w[1][0] = s1 * h0;
+          w[2][2] = 1.0 + (s0 + s1) * h2; w[2][0] = s2 * h0; w[2][1] = s2 * h1;
+        } else {
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            Lam[d] = aniso_d(lam[d], lam[(d + 1) % 3], lam[(d + 2) % 3], P, w[d][d], w[d][(d + 1) % 3], w[d][(d + 2) % 3]);
+        }
+        Lam0 = rad ? Lam[0] : 0.0;
+        Lam1 = rad ? Lam[1] : 0.0;
+        Lam2 = rad ? Lam[2] : 0.0;
+        const double ir2 = 0.5 * ir, kp = P.gamma * rcp_nr(cs) * ir2, ke2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+#pragma unroll
+        for (int dd = 0; dd < 3; ++dd) {
+          const int d = (dd + 1) % 3;
+          double V[5];
+          // lam_e = |U_e| + c |m_e|, c = sqrt(gamma p / rho)
+          const double w0 = w[d][0] * sg[0], w1 = w[d][1] * sg[1], w2 = w[d][2] * sg[2];
+          const double ux = w0 * m[0] + w1 * m[3] + w2 * m[6];
+          const double uy = w0 * m[1] + w1 * m[4] + w2 * m[7];
+          const double uz = w0 * m[2] + w1 * m[5] + w2 * m[8];
+          const double cb = w[d][0] * nrm[0] + w[d][1] * nrm[1] + w[d][2] * nrm[2];
+          const double gp = P.gm1 * cb * kp;
+          V[0] = rad ? 0.5 * gp * ke2 - cb * cs * ir2 - (ux * u[0] + uy * u[1] + uz * u[2]) * ir : 0.0;
+          V[1] = rad ? ux * ir - gp * u[0] : 0.0;
+          V[2] = rad ? uy * ir - gp * u[1] : 0.0;
+          V[3] = rad ? uz * ir - gp * u[2] : 0.0;
+          V[4] = rad ? gp : 0.0;
+#pragma unroll
+          for (int c = 0; c < 5; ++c) {
+            if (d == 0) V0[c] = V[c];
+            if (d == 1 && cx_ok) sV[c][ty][cx] = V[c];
+            if (d == 2) V2n[c] = V[c];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      load_ahead(1);
+      // ---- xi direction ----
+      if (inner) {
+        const double pa = sp[ey][ex + 1], pz = sp[ey][ex - 1];
+        const double iS = b1 ? rcp_nr(pa + 2.0 * pc + pz) : 0.0;
+        const double ns = b1 ? (pa - 2.0 * pc + pz) * iS : 0.0;
+        double F[5], G[5], LH, NA, NB;
+        {
+          double q_b[5], q_c[5], q_d[5], q_e[5], Db[5];
+          const double Ln = lane_next(Lam0), nn = lane_next(ns);
+          const int xn = tx < BX - 1 ? tx + 1 : tx, e2 = ex < EX - 2 ? ex + 2 : ex;
+#pragma unroll
+          for (int c = 0; c < 5; ++c) {
+            q_b[c] = sq[c][ey][ex - 1]; q_c[c] = sq[c][ey][ex];
+            q_d[c] = sq[c][ey][ex + 1]; q_e[c] = sq[c][ey][e2];
+            Db[c] = sW[c][ty][xn] - sW[c][ty][tx];
+          }
+          face_rev(P, Lam0, Ln, ns, nn, q_b, q_c, q_d, q_e, Db, fx_ij, F, G, LH, NA, NB);
+        }
+        const double Lb = lane_prev(LH) + LH, nub = lane_prev(NB) + NA;
+        const double sd = sgn(ns) * iS, sv = fabs(ns) * iS, cp = nub * (sd - sv);
+        pbc += -2.0 * nub * (sd + sv) + lane_prev(cp) + lane_next(cp);
+#pragma unroll
+        for (int c = 0; c < 5; ++c)
+          oc[c] += Lb * V0[c] + lane_prev(F[c] - lane_prev(G[c])) - (F[c] - lane_next(G[c]));
+        __builtin_amdgcn_sched_barrier(0);
+        if (cx_ok) {
+          const double qa1 = sp[ey + 1][ex], qz1 = sp[ey - 1][ex];
+          const double jS = b1 ? rcp_nr(qa1 + 2.0 * pc + qz1) : 0.0;
+          ly[ty][cx] = Lam1;
+          ny[ty][cx] = b1 ? (qa1 - 2.0 * pc + qz1) * jS : 0.0;
+          cy[ty][cx] = jS;
+        }
+      }
+      load_ahead(2);
+      // ---- zeta face (t-1, t) ----
+      {
+        const double iS = b1 ? rcp_nr(pp1 + 2.0 * pc + pm1) : 0.0;
+        const double ns = b1 ? (pp1 - 2.0 * pc + pm1) * iS : 0.0;
+        double F[5], G[5], LH, NA, NB;
+        {
+          double qc[5], Db[5];
+#pragma unroll
+          for (int c = 0; c < 5; ++c) {
+            qc[c] = sq[c][ey][ex];
+            Db[c] = sW[c][ty][tx] - Wm[c];
+          }
+          const bool ok = ii && jj && t >= 0 && t <= L.nk && t > kb - 2;
+          face_rev(P, L2, Lam2, ns2, ns, qm2, qm1, qc, qa, Db, ok, F, G, LH, NA, NB);
+        }
+        const double nub = nbz + NA, sd = sgn(ns2) * iS2, sv = fabs(ns2) * iS2, cp = nub * (sd - sv);
+        pb2 += cp;
+        pb1 -= 2.0 * nub * (sd + sv);
+        pbc += cp;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          om2[c] += G[c];
+          om1[c] += LH * V2[c] - F[c];
+          oc[c] += LH * V2n[c] + F[c] - Gz[c];
+          Gz[c] = G[c];
+          V2[c] = V2n[c];
+        }
+        nbz = NB;
+        L2 = Lam2;
+        ns2 = ns;
+        iS2 = iS;
+      }
+      load_ahead(3);
+      load_ahead(4);
+      // plane t-2 is complete: the pressure adjoint to conserved variables
+      double o[5];
+      {
+        const double ir = rcp_nr(qm2[0]), g = P.gm1 * pb2;
+        const double u = qm2[1] * ir, vv = qm2[2] * ir, w = qm2[3] * ir;
+        const bool any = pb2 != 0.0;  // (unused ghost corners may hold anything)
+        o[0] = om2[0] + (any ? 0.5 * g * (u * u + vv * vv + w * w) : 0.0);
+        o[1] = om2[1] - (any ? g * u : 0.0);
+        o[2] = om2[2] - (any ? g * vv : 0.0);
+        o[3] = om2[3] - (any ? g * w : 0.0);
+        o[4] = om2[4] + g;
+      }
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        pin(o[c]);
+        pin(om1[c]);
+        pin(oc[c]);
+        pin(Gz[c]);
+      }
+      pin(pb1);
+      pin(pbc);
+      pin(nbz);
+      if (tid < DNH) load5(kq->t.Q, oh, hq);
+      load5(kq->t.Q, on, qn);
+      load5(kq->t.qb, ob, bn);
+      Jn = ldo(kq->t.A.M + sb + 9 * fe, ob);
+      __builtin_amdgcn_sched_barrier(0);
+      lds_barrier();
+
+      // ---- D: eta faces (ty, ty + 1) ----
+      if (inner && ty < BY - 1 && cx_ok) {
+        double q_b[5], q_c[5], q_d[5], q_e[5], Db[5], F[5], G[5], LH, NA, NB;
+        const bool axf = axis && j == 0;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          q_c[c] = sq[c][ey][ex];
+          q_d[c] = sq[c][ey + 1][ex];
+          q_e[c] = sq[c][ey + 2][ex];
+          // the face between the axis and j = 1 takes the cross-axis value by
+          // linear extrapolation: d3 = Q(2) - 2 Q(1) + Q(0)
+          q_b[c] = sq[c][ey - 1][ex];
+          Db[c] = sW[c][ty + 1][tx] - sW[c][ty][tx];
+        }
+        if (axf) {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) q_b[c] = 2.0 * q_c[c] - q_d[c];
+        }
+        face_rev(P, ly[ty][cx], ly[ty + 1][cx], ny[ty][cx], ny[ty + 1][cx], q_b, q_c, q_d, q_e, Db, fy_ij, F, G, LH, NA,
+                 NB);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          fF[c][ty][cx] = F[c];
+          fG[c][ty][cx] = G[c];
+        }
+        fL[ty][cx] = LH;
+        fA[ty][cx] = NA;
+        fB[ty][cx] = NB;
+      }
+      // what plane t-2's store needs
+      const int k = t - 2;
+      const bool st = out_ok && k >= kb;  // (k < ke always)
+      const bool own = ii && jj && k >= 0 && k < L.nk;
+      const unsigned ot = st ? col + (unsigned)(k - kr) * sk : col + 4 * sk;
+      double fl[5];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) fl[c] = ldo(kq->t.Wk + (W_FL + c) * fe + sb, ot);
+      lds_barrier();
+
+      // ---- E: gather of the eta faces ----
+      if (inner && cx_ok && ry_ok) {
+        // faces below (ty - 1, ty) and above (ty, ty + 1), and one further on
+        // either side
+        const double Lb = fL[ty - 1][cx] + fL[ty][cx];
+        const double n0 = fB[ty - 1][cx] + fA[ty][cx], nm = fB[ty - 2][cx] + fA[ty - 1][cx];
+        const double np = fB[ty][cx] + fA[ty + 1][cx];
+        auto cpw = [&](int r, double nub, double f) {  // nub times (sd - sv) or -2 (sd + sv) of row r's sensor
+          const double ns = ny[r][cx], iS = cy[r][cx];
+          const double sd = sgn(ns) * iS, sv = fabs(ns) * iS;
+          return f == 1.0 ? nub * (sd - sv) : -2.0 * nub * (sd + sv);
+        };
+        pbc += cpw(ty, n0, 0.0) + cpw(ty - 1, nm, 1.0) + cpw(ty + 1, np, 1.0);
+        // the face between the axis and j = 1: the axis node takes
+        // -(A2 + A4) Dbar, node j = 1 takes (A2 + 2 A4) Dbar and the ghost
+        // below the axis nothing
+        const double x1 = axis && j == 1 ? 1.0 : 0.0, x0 = axis && j == 0 ? 2.0 : 0.0, xg = axis && j == -1 ? 0.0 : 1.0;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          oc[c] += Lb * sV[c][ty][cx] + (fF[c][ty - 1][cx] - x1 * fG[c][ty - 1][cx]) - (fF[c][ty][cx] - x0 * fG[c][ty][cx]) -
+                   fG[c][ty - 2][cx] + xg * fG[c][ty + 1][cx];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        om2[c] = om1[c];
+        om1[c] = oc[c];
+        qm2[c] = qm1[c];
+        qm1[c] = sq[c][ey][ex];
+        Wm[c] = sW[c][ty][tx];
+        qw[c] = qa[c];
+        qa[c] = qn[c];
+      }
+      pb2 = pb1;
+      pb1 = pbc;
+      pm1 = pc;
+      Wset(t + 1, Wc);
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm<0>();  // all loads of this plane, before the stores (see les_stage.hip)
+      if (st) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) o[c] += fl[c];
+        if (own) {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) sto(kq->qout + c * fe + sb, ot, o[c]);
+          // (the fold finishes the nodes with images)
+          if (kq->fbar && i == kq->i_f && !has_images(kq->t.A, i, j, k)) {
+#pragma unroll
+            for (int c = 0; c < 5; ++c) kq->fbar[((long long)c * L.nk + k) * L.nj + j] += kq->fw * o[c];
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) sto(kq->t.Wk + (W_GG + c) * fe + sb, ot, o[c]);
+        }
+      }
     }
-  }
-  if (interior(L, i, j, k)) {
-    for (int c = 0; c < 5; ++c) qout[c * fe + n] = out[c];
-    if (acc)
-      for (int c = 0; c < 5; ++c) acc[c * fe + n] += accsrc[c * fe + n];
-    // nodes without periodic images are final here; pass 3 finishes the rest
-    if (!has_images(A, i, j, k)) finish_node(L, n, j, k, out, acc, fbar, i == i_f, fw, qfin);
-  } else {
-    for (int c = 0; c < 5; ++c) Wk[(W_GG + c) * fe + n] = out[c];
   }
 }
 
 // ---------------------------------------------------------------------------
-// Pass 3: add the periodic ghost images' gathers to their interior nodes:
+// Fold: add the periodic ghost images' adjoints to their interior nodes:
 // qout(n) += W_GG over the images of n (at x + n_d for x <= 1 and at x - n_d
 // for x >= n_d - 2 along each periodic axis, all combinations, in a fixed
 // order).  Only nodes in the band {x <= 1 or x >= n_d - 2} of some periodic
@@ -698,8 +1018,7 @@ __global__ void __launch_bounds__(256) k_adj_gather(AdjK A, const double* __rest
 __device__ __forceinline__ int band_coord(unsigned u, int n) { return n <= 4 ? (int)u : (u < 2 ? (int)u : n - 4 + (int)u); }
 
 __global__ void __launch_bounds__(256) k_adj_fold(AdjK A, const double* __restrict__ Wk, double* __restrict__ qout,
-                                                  const double* __restrict__ acc, double* __restrict__ fbar, int i_f,
-                                                  double fw, double* __restrict__ qfin) {
+                                                  double* __restrict__ fbar, int i_f, double fw) {
   const Layout& L = A.L;
   const int nn[3] = {L.ni, L.nj, L.nk};
   const int bc[3] = {A.bc0, A.bc1, A.bc2};
@@ -758,10 +1077,10 @@ __global__ void __launch_bounds__(256) k_adj_fold(AdjK A, const double* __restri
     qout[c * L.fe + n0] = s;
     q[c] = s;
   }
-  finish_node(L, n0, j, k, q, acc, fbar, i == i_f, fw, qfin);
+  finish_node(L, j, k, q, fbar, i == i_f, fw);
 }
 
-// Pass 3 when an axis is superposed or a boundary face is active: every
+// Fold when an axis is superposed or a boundary face is active: every
 // interior node with images adds, in a fixed order, the gathers of its
 // periodic images (period p along each periodic axis) and pulls back those
 // of its face ghosts through the face rule: qbar(r) += (dG/dq_r)^T Gbar for
@@ -826,8 +1145,7 @@ __device__ inline bool face_node(const AdjK& A, long long x, int id[3]) {
 template <bool FACES>
 __global__ void __launch_bounds__(256) k_adj_fold_general(AdjK A, const double* __restrict__ Q,
                                                           const double* __restrict__ Wk, double* __restrict__ qout,
-                                                          const double* __restrict__ acc, double* __restrict__ fbar,
-                                                          int i_f, double fw, double* __restrict__ qfin,
+                                                          double* __restrict__ fbar, int i_f, double fw,
                                                           long long slots) {
   const Layout& L = A.L;
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -943,27 +1261,7 @@ __global__ void __launch_bounds__(256) k_adj_fold_general(AdjK A, const double* 
     }
   }
   for (int c = c0; c < c1; ++c) qout[c * fe + n0] = s[c];
-  finish_node(L, n0, j, k, s, acc, fbar, i == i_f, fw, qfin, c0, c1);
-}
-
-// Start of the Runge-Kutta reverse (interior): qcur = Qbar, acc = 0, and
-// fbar[c][k][j] += w Qbar_c on the source plane (fbar non-null).
-__global__ void __launch_bounds__(256) k_adj_init(Layout L, const double* __restrict__ Qbar, double* __restrict__ qcur,
-                                                  double* __restrict__ acc, double* __restrict__ fbar, int i_f,
-                                                  double w) {
-  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-  const unsigned ni = L.ni, nij = (unsigned)L.ni * L.nj;
-  if (t >= nij * (unsigned)L.nk) return;
-  const int i = (int)(t % ni);
-  const int j = (int)((t % nij) / ni);
-  const int k = (int)(t / nij);
-  const long long n = L.at(i, j, k);
-  for (int c = 0; c < 5; ++c) {
-    const double q = Qbar[c * L.fe + n];
-    qcur[c * L.fe + n] = q;
-    acc[c * L.fe + n] = 0.0;
-    if (fbar && i == i_f) fbar[((long long)c * L.nk + k) * L.nj + j] += w * q;
-  }
+  finish_node(L, j, k, s, fbar, i == i_f, fw, c0, c1);
 }
 
 // Reverse of the centerline condition, one wave per (i, variable): the
@@ -996,19 +1294,34 @@ __global__ void __launch_bounds__(256) k_adj_source(Layout L, const double* __re
   for (int c = 0; c < 5; ++c) fbar[((long long)c * L.nk + k) * L.nj + j] += w * q[c * L.fe + n];
 }
 
+// Adjoints of the six stage states of a step (5 fields each).
+struct Terms {
+  double* p[6];
+};
+
+// Qbar = the sum of the stages' adjoints, in order from Qbar itself (p[0]) to
+// the last stage's, on the interior; blockIdx.y is the component.  Bound by
+// memory: 6 reads and 1 write a component and step, where a running sum kept
+// by every stage took 10 reads and 5 writes and a copy of Qbar (24 us on the
+// 128 x 64 x 64 jet; taken inside the last stage's dissipation pass, whose few
+// waves wait for the loads, it cost 115).
+__global__ void __launch_bounds__(256) k_adj_sum(Layout L, Terms z) {
+  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
+  const unsigned ni = L.ni, nij = (unsigned)L.ni * L.nj;
+  if (t >= nij * (unsigned)L.nk) return;
+  const long long n = L.at((int)(t % ni), (int)((t % nij) / ni), (int)(t / nij)) + blockIdx.y * L.fe;
+  double x = z.p[0][n];
+#pragma unroll
+  for (int m = 1; m < 6; ++m) x += z.p[m][n];
+  z.p[0][n] = x;
+}
+
 inline unsigned nb(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// qout = (dR/dQ|Q)^T (coef * qb) on the interior; with acc non-null also
-// acc += qb (the gather pass is the last one that reads qb); fbar, qfin: see
-// finish_node.
+// qout = (dR/dQ|Q)^T (coef * qb) on the interior; fbar: see finish_node.
 hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const double* qb, double coef, double* Wk,
-                        double* qout, double* acc = nullptr, double* fbar = nullptr, int i_f = -1, double fw = 0.0,
-                        double* qfin = nullptr) {
+                        double* qout, double* fbar = nullptr, int i_f = -1, double fw = 0.0) {
   const Layout& L = A.L;
-  const long long nB1 = (long long)(L.ni + 2) * (L.nj + 2) * (L.nk + 2);
-  const long long nFace = (long long)(L.ni + 1) * L.nj * L.nk + (long long)L.ni * (L.nj + 1) * L.nk +
-                         (long long)L.ni * L.nj * (L.nk + 1);
-  const long long nB = (long long)(A.hi[0] - A.lo[0] + 1) * (A.hi[1] - A.lo[1] + 1) * (A.hi[2] - A.lo[2] + 1);
   const long long nIn = (long long)L.ni * L.nj * L.nk;
   long long nBand = 0;
   {
@@ -1021,19 +1334,34 @@ hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const dou
     }
     nBand = bs[2] * nn[1] * nn[0] + cs[2] * bs[1] * nn[0] + cs[2] * cs[1] * bs[0];
   }
-  k_adj_flux<<<nb(nB1, 256), 256, 0, s>>>(A, Q, qb, coef, Wk);
-  k_adj_face<<<nb(nFace, 256), 256, 0, s>>>(A, Q, qb, coef, Wk);
-  k_adj_dnode<<<nb(nB1, 256), 256, 0, s>>>(A, Q, Wk);
-  k_adj_gather<<<nb(nB, 256), 256, 0, s>>>(A, Q, Wk, qout, acc, qb, fbar, i_f, fw, qfin);
-  if (A.general)
-  {
-    k_adj_fold_general<false><<<nb(nIn, 256), 256, 0, s>>>(A, Q, Wk, qout, acc, fbar, i_f, fw, qfin, 0);
+  // blocks over tiles of tx x ty output nodes, whose first column lies `lead`
+  // before the output box
+  auto tiles = [&](int tx, int ty, int lead) {
+    TileArgs ta{A, Q, qb, coef, A.P.gamma_R / A.P.gamma, 1.0 / A.P.gm1, Wk, 0, 0, 0, 0, 0, 0, A.mach.xcds};
+    ta.ntx = (A.hi[0] - A.lo[0] + lead + tx) / tx;
+    ta.nty = (A.hi[1] - A.lo[1] + ty) / ty;
+    const int nkt = A.hi[2] - A.lo[2] + 1;
+    const Schedule sch = segment_schedule((long long)ta.ntx * ta.nty, nkt, A.mach.cus, segment_kmax(L));
+    ta.kc = sch.kc;
+    ta.nblocks = sch.nblocks;
+    ta.nseg = ta.ntx * ta.nty * ((nkt + sch.kc - 1) / sch.kc);
+    ta.per_xcd = (sch.nblocks + ta.nxcd - 1) / ta.nxcd;
+    return ta;
+  };
+  const TileArgs tf = tiles(TX, TY, 0);
+  k_adj_flux<<<tf.per_xcd * tf.nxcd, NT, 0, s>>>(tf);
+  const DissArgs td{tiles(DTX, DTY, 1), qout, fbar, fw, i_f};
+  if (A.P.alpha_half)
+    k_adj_diss<true><<<td.t.per_xcd * td.t.nxcd, NT, 0, s>>>(td);
+  else
+    k_adj_diss<false><<<td.t.per_xcd * td.t.nxcd, NT, 0, s>>>(td);
+  if (A.general) {
+    k_adj_fold_general<false><<<nb(nIn, 256), 256, 0, s>>>(A, Q, Wk, qout, fbar, i_f, fw, 0);
     const long long slots = face_node_slots(A);
     if (slots > 0)
-      k_adj_fold_general<true><<<nb(5 * slots, 256), 256, 0, s>>>(A, Q, Wk, qout, acc, fbar, i_f, fw, qfin, slots);
-  }
-  else if (nBand > 0)
-    k_adj_fold<<<nb(nBand, 256), 256, 0, s>>>(A, Wk, qout, acc, fbar, i_f, fw, qfin);
+      k_adj_fold_general<true><<<nb(5 * slots, 256), 256, 0, s>>>(A, Q, Wk, qout, fbar, i_f, fw, slots);
+  } else if (nBand > 0)
+    k_adj_fold<<<nb(nBand, 256), 256, 0, s>>>(A, Wk, qout, fbar, i_f, fw);
   return hipGetLastError();
 }
 
@@ -1061,9 +1389,6 @@ hipError_t run_adjoint_step(hipStream_t s, const AdjArgs& a, const double* ckpt,
   const Layout& L = a.L;
   const long long fe = L.fe;
   const long long nIn = (long long)L.ni * L.nj * L.nk;
-  double* qcur = work + (long long)W_Q1 * fe;
-  double* qnext = work + (long long)(W_Q1 + 5) * fe;
-  double* acc = work + (long long)W_ACC * fe;
   // With the polar axis every stage input and the step's result pass
   // through the centerline condition C (linear): Q^{n+1} = C(Z_5) and the
   // stage input of stage l > 1 is C(Z_l) for the raw stage output Z_l, so
@@ -1074,29 +1399,33 @@ hipError_t run_adjoint_step(hipStream_t s, const AdjArgs& a, const double* ckpt,
   const bool want_f = fbar && a.i_f >= 0;
   hipError_t e = hipSuccess;
   if (A.axis && (e = launch_axis_avg_adjoint(s, L, Qbar)) != hipSuccess) return e;
-  // qcur = Qbar, acc = 0, fbar += alpha_5 dt Qbar (interior)
-  k_adj_init<<<nb(nIn, 256), 256, 0, s>>>(L, Qbar, qcur, acc, want_f ? fbar : nullptr, a.i_f, rk_alpha(4) * dt);
+  // fbar += alpha_5 dt Qbar
+  if (want_f) k_adj_source<<<nb((long long)L.nj * L.nk, 256), 256, 0, s>>>(L, Qbar, fbar, a.i_f, rk_alpha(4) * dt);
+  // Every stage's result has a buffer of its own and the sum is taken once.
+  Terms z;
+  z.p[0] = Qbar;
+  for (int m = 1; m < 6; ++m) z.p[m] = work + (long long)(W_Z + 5 * (m - 1)) * fe;
   for (int l = 4; l >= 0; --l) {
     const double al = rk_alpha(l) * dt;
-    // qbar_{l-1} = (dR/dQ|Q^(l-1))^T (-alpha_l dt qbar_l), acc += qbar_l,
-    // fbar += alpha_{l-1} dt qbar_{l-1}; after the last stage Qbar = acc +
-    // qbar_0
+    // qbar_{l-1} = (dR/dQ|Q^(l-1))^T (-alpha_l dt qbar_l),
+    // fbar += alpha_{l-1} dt qbar_{l-1}
     const double* Ql = ckpt + (long long)l * 5 * fe;
+    double* const qnext = z.p[5 - l];
     const bool f_next = want_f && l > 0;
     const bool f_here = f_next && !A.axis;
-    e = residual_vjp(s, A, Ql, qcur, -al, work, qnext, acc, f_here ? fbar : nullptr, a.i_f,
-                     f_here ? rk_alpha(l - 1) * dt : 0.0, l == 0 ? Qbar : nullptr);
+    e = residual_vjp(s, A, Ql, z.p[4 - l], -al, work, qnext, f_here ? fbar : nullptr, a.i_f,
+                     f_here ? rk_alpha(l - 1) * dt : 0.0);
     if (e != hipSuccess) return e;
-    if (A.axis) {
-      e = launch_axis_avg_adjoint(s, L, l == 0 ? Qbar : qnext);
+    if (A.axis && l > 0) {
+      e = launch_axis_avg_adjoint(s, L, qnext);
       if (e != hipSuccess) return e;
       if (f_next) k_adj_source<<<nb((long long)L.nj * L.nk, 256), 256, 0, s>>>(L, qnext, fbar, a.i_f,
                                                                                 rk_alpha(l - 1) * dt);
     }
-    double* tmp = qcur;
-    qcur = qnext;
-    qnext = tmp;
   }
+  k_adj_sum<<<dim3(nb(nIn, 256), 5), 256, 0, s>>>(L, z);
+  // (the centerline condition of the step's input acts on the sum)
+  if (A.axis && (e = launch_axis_avg_adjoint(s, L, Qbar)) != hipSuccess) return e;
   return hipGetLastError();
 }
 

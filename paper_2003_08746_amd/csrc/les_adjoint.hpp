@@ -2,6 +2,7 @@
 #pragma once
 #include "les_common.hpp"
 #include "les_faces.hpp"
+#include "les_tile.hpp"
 
 namespace les {
 
@@ -13,6 +14,7 @@ struct AdjArgs {
   int i_f;
   Faces F;            // boundary faces of the Dirichlet directions
   int axis;           // bc1 == 3: j = 0 is the O-grid's polar axis
+  Machine mach;
 };
 
 // Device work elements (doubles) needed by run_adjoint_step.

@@ -126,17 +126,6 @@ struct Smem {
   T dy[sizeof(T) == 8 ? 5 : 0][BY - 1][TX];  // FP64: dissipation of the eta face above patch rows 0..BY-2
 };
 
-// Global accesses use a uniform (scalar) base per field plus a 32-bit
-// per-thread byte offset, so that each access needs one VGPR for its address.
-template <class X>
-__device__ __forceinline__ X ldo(const X* base, unsigned off) {
-  return *(const X*)((const char*)base + (size_t)(off * (unsigned)sizeof(X)));
-}
-template <class X>
-__device__ __forceinline__ void sto(X* base, unsigned off, X v) {
-  *(X*)((char*)base + (size_t)(off * (unsigned)sizeof(X))) = v;
-}
-
 template <class T, class QI>
 __device__ __forceinline__ void load_q(const QI* __restrict__ Q, long long fe, unsigned off, T q[5]) {
 #pragma unroll
@@ -188,60 +177,13 @@ __device__ __forceinline__ void norm_wave(const double s2[5], const double sm[5]
 // with no barrier.  One asynchronous global->LDS copy moves 16 bytes (two
 // doubles) per lane: lanes 0-31 the 64 nodes of field f (row after row),
 // lanes 32-63 the same for field f+1; they land contiguously at [f][r][col]
-// of the block.  src is the lane's
-// byte address for field (lane >> 5); fstep2 is two fields in bytes.  With
-// an odd field count the last copy uses lanes 0-31 only.
+// of the block.  src is the lane's byte address for field (lane >> 5); fstep2
+// is two fields in bytes.
 template <int NF>
-__device__ __forceinline__ void dma_rows(const char* src, long long fstep2, double* dst, int lane) {
+__device__ __forceinline__ void dma_rows(const char* src, long long fstep2, double* dst) {
+  static_assert(NF % 2 == 0, "two fields per copy");
 #pragma unroll
-  for (int q = 0; q < NF / 2; ++q)
-    __builtin_amdgcn_global_load_lds((const void*)(src + q * fstep2),
-                                     (__attribute__((address_space(3))) void*)(dst + q * 128), 16, 0, 0);
-  if (NF & 1) {
-    if (lane < 32)
-      __builtin_amdgcn_global_load_lds((const void*)(src + (NF / 2) * fstep2),
-                                       (__attribute__((address_space(3))) void*)(dst + (NF / 2) * 128), 16, 0, 0);
-  }
-}
-
-// s_waitcnt vmcnt(N): all but the N most recent vector memory operations of
-// this wave have completed (expcnt and lgkmcnt left unconstrained)
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-// s_waitcnt lgkmcnt(0): this wave's LDS reads have returned
-__device__ __forceinline__ void wait_lgkm_all() { __builtin_amdgcn_s_waitcnt(0xC07F); }
-
-// Block barrier for LDS data only: release/acquire at workgroup scope for
-// the local address space, so the wave waits for its own LDS operations but
-// not for outstanding global loads, stores or global->LDS copies (which a
-// full __syncthreads drains).
-__device__ __forceinline__ void lds_barrier() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  __builtin_amdgcn_s_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// The value of the lane before / after this one (DPP wave shifts by one lane;
-// the end lanes read 0).
-__device__ __forceinline__ float lane_prev(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_next(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double lane_prev(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double lane_next(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
+  for (int q = 0; q < NF / 2; ++q) copy_to_lds(src + q * fstep2, dst + q * 128);
 }
 
 // Optional paths of the stage kernel (template bit mask EXT)
@@ -381,7 +323,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int jcp = min(j0 - 1 + RPW * wave + rsel, L.nj);
     const long long lane_el = (long long)fsel * fe + L.o + icp + (long long)jcp * L.sj;
     const long long fstep2 = 2 * fe * (long long)sizeof(double);
-    dma_rows<10>((const char*)(kp->M + lane_el + (long long)(kb - 1) * L.sk), fstep2, &mbw[wave][0][0][0], lane);
+    dma_rows<10>((const char*)(kp->M + lane_el + (long long)(kb - 1) * L.sk), fstep2, &mbw[wave][0][0][0]);
     load_q<T>(Qs, fe, qcol, qm1);
     load_q<T>(Qs, fe, qcol + sk, qw);
     load_q<T>(Qs, fe, qcol + 2 * sk, qa);
@@ -436,28 +378,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       double Jn = 0.0;
       T mt[9];
       {
-        // (read by hand, with the wait for the reads in the same block: the
-        // compiler would wait for every outstanding copy, load and store of
-        // the wave before an LDS read of a block that copies write; the
-        // copies of this plane were waited for above.  The reads are done
-        // before the next plane's copies overwrite the block.)
-        typedef double d2 __attribute__((ext_vector_type(2)));
-        d2 m0, m1, m2, m3, m4;
-        const unsigned la =
-            (unsigned)(uintptr_t)(__attribute__((address_space(3))) const double*)&mbw[wave][0][ty1][tx];
-        asm volatile(
-            "ds_read2st64_b64 %0, %5 offset0:0 offset1:1\n"
-            "ds_read2st64_b64 %1, %5 offset0:2 offset1:3\n"
-            "ds_read2st64_b64 %2, %5 offset0:4 offset1:5\n"
-            "ds_read2st64_b64 %3, %5 offset0:6 offset1:7\n"
-            "ds_read2st64_b64 %4, %5 offset0:8 offset1:9\n"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(m0), "=&v"(m1), "=&v"(m2), "=&v"(m3), "=&v"(m4)
-            : "v"(la)
-            : "memory");
-        mt[0] = (T)m0.x; mt[1] = (T)m0.y; mt[2] = (T)m1.x; mt[3] = (T)m1.y; mt[4] = (T)m2.x;
-        mt[5] = (T)m2.y; mt[6] = (T)m3.x; mt[7] = (T)m3.y; mt[8] = (T)m4.x;
-        Jn = m4.y;
+        double md[9];
+        read_metric_rows(&mbw[wave][0][ty1][tx], md, Jn);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) mt[c] = (T)md[c];
       }
       const char* const msrc = (const char*)(kq->M + lane_el + (long long)(t + 1) * L.sk);
       double* const mdst = &mbw[wave][0][0][0];
@@ -476,8 +400,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
           if (q == 0) {
             if (h_ok) load_q<T>(Qs, fe, hcol + (unsigned)(t + 1 - kr) * sk, hq);
           } else {
-            __builtin_amdgcn_global_load_lds((const void*)(msrc + (q - 1) * fstep2),
-                                             (__attribute__((address_space(3))) void*)(mdst + (q - 1) * 128), 16, 0, 0);
+            copy_to_lds(msrc + (q - 1) * fstep2, mdst + (q - 1) * 128);
             qn[q - 1] = (T)ldo(Qs + (q - 1) * fe, qoff2);
           }
         }
@@ -792,13 +715,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 }  // namespace
 
-// The most planes one segment may march: its per-thread element offsets,
-// taken from plane kb - 2, reach kc + 6 planes and must stay below 2^29
-// (32-bit byte offsets of doubles).  0 when even one plane is too large.
-int stage_kmax(const Layout& L) {
-  const long long k = (1LL << 29) / L.sk - 6;
-  return k < 1 ? 0 : (k > (1 << 30) ? (1 << 30) : (int)k);
-}
+int stage_kmax(const Layout& L) { return segment_kmax(L); }
 
 namespace {
 
@@ -857,35 +774,13 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
 
 }  // namespace
 
-// The schedule of a layout: (k chunk, tile) segments round robin over one
-// persistent block per CU.  A segment of n planes runs n + 2 iterations (the
-// planes below and above it) and about one more for its start, so the time of
-// a launch is that of its slowest block, block 0: the sum of n + 3 over its
-// segments.  The number of chunks with the smallest sum is taken, the fewest
-// on ties.  (Against contiguous ranges of at least 8 tile-planes per block,
-// which could straddle two tiles, as used before; FP64 stage: 32^3 52 -> 18 us,
-// 64^3 49 -> 32, 128 x 64 x 64 49 -> 45, 256 x 128 x 128 267 -> 262,
-// 400 x 250 x 250 1992 -> 1313, O-grid 256 x 128 x 361 784 -> 700,
-// 800 x 500 x 500 10.95 -> 10.55 ms; mixed 75 x 61 x 47 45 -> 23 us.)
-Schedule stage_schedule(const Layout& L, const Machine& m) {
-  const long long ntiles = (long long)((L.ni + TX - 1) / TX) * ((L.nj + TY - 1) / TY);
-  const int slots = m.cus * BPC, kmax = stage_kmax(L);
+Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax) {
   Schedule best;
-  if (const char* env = getenv("LES_SEG")) {
-    const int seg = atoi(env);
-    if (seg > 0) {  // chunks of seg planes, one block per seg tile-planes
-      best.kc = seg < L.nk ? seg : L.nk;
-      if (best.kc > kmax) best.kc = kmax;
-      const long long nseg = ntiles * ((L.nk + best.kc - 1) / best.kc), nb = (ntiles * L.nk + seg - 1) / seg;
-      best.nblocks = (int)(nseg < nb ? nseg : nb);
-      return best;
-    }
-  }
   long long cost = -1;
-  for (int n = (L.nk + kmax - 1) / kmax; n <= L.nk; ++n) {
-    const int kc = (L.nk + n - 1) / n;
-    if ((L.nk + kc - 1) / kc != n) continue;  // the same chunks as fewer of them
-    const int last = L.nk - (n - 1) * kc;
+  for (int n = (nk + kmax - 1) / kmax; n <= nk; ++n) {
+    const int kc = (nk + n - 1) / n;
+    if ((nk + kc - 1) / kc != n) continue;  // the same chunks as fewer of them
+    const int last = nk - (n - 1) * kc;
     const long long nseg = ntiles * n, nb = nseg < slots ? nseg : slots;
     const long long rounds = (nseg + nb - 1) / nb, full = (ntiles * (n - 1) + nb - 1) / nb;
     const long long c = full * kc + (rounds - full) * last + rounds * 3;
@@ -897,6 +792,28 @@ Schedule stage_schedule(const Layout& L, const Machine& m) {
     if (rounds * 3 > cost) break;  // more chunks only add starts
   }
   return best;
+}
+
+// Segments round robin over one persistent block per CU.  (Against contiguous
+// ranges of at least 8 tile-planes per block, which could straddle two tiles,
+// as used before; FP64 stage: 32^3 52 -> 18 us, 64^3 49 -> 32,
+// 128 x 64 x 64 49 -> 45, 256 x 128 x 128 267 -> 262, 400 x 250 x 250
+// 1992 -> 1313, O-grid 256 x 128 x 361 784 -> 700, 800 x 500 x 500
+// 10.95 -> 10.55 ms; mixed 75 x 61 x 47 45 -> 23 us.)
+Schedule stage_schedule(const Layout& L, const Machine& m) {
+  const long long ntiles = (long long)((L.ni + TX - 1) / TX) * ((L.nj + TY - 1) / TY);
+  if (const char* env = getenv("LES_SEG")) {
+    const int seg = atoi(env);
+    if (seg > 0) {  // chunks of seg planes, one block per seg tile-planes
+      Schedule s;
+      s.kc = seg < L.nk ? seg : L.nk;
+      if (s.kc > stage_kmax(L)) s.kc = stage_kmax(L);
+      const long long nseg = ntiles * ((L.nk + s.kc - 1) / s.kc), nb = (ntiles * L.nk + seg - 1) / seg;
+      s.nblocks = (int)(nseg < nb ? nseg : nb);
+      return s;
+    }
+  }
+  return segment_schedule(ntiles, L.nk, m.cus * BPC, stage_kmax(L));
 }
 
 hipError_t launch_stage_fp64(hipStream_t s, const StageArgs& a, const double* Qin, const double* Q0, double* Qout,

@@ -1,23 +1,9 @@
 // les_stage.hpp -- launchers of the fused Runge-Kutta stage kernels.
 #pragma once
 #include "les_common.hpp"
+#include "les_tile.hpp"
 
 namespace les {
-
-// The device's compute-unit and XCD (accelerator complex die) counts: the
-// persistent stage kernel runs one block per CU and maps consecutive blocks
-// to one XCD (each XCD has its own L2).
-struct Machine {
-  int cus = 256;
-  int xcds = 8;
-};
-
-// Work of the persistent blocks: (k chunk, tile) segments of kc planes, taken
-// round robin by nblocks blocks (fixed per context).
-struct Schedule {
-  int kc = 0;
-  int nblocks = 0;
-};
 
 struct StageArgs {
   Layout L;
@@ -43,7 +29,7 @@ int stage_kmax(const Layout& L);
 // One FP64 stage: Qout = Q0 - alpha dt R(Qin) on the interior (Qin's ghosts
 // already filled).  dtp (device) overrides dt when non-null.  part: norm
 // partials (or null).  cpart (or null): per-block minima of the local CFL
-// bound of the updated state (one double per block; not together with part, ten).
+// bound of the updated state (one double per block; not together with part).
 // Q0 and Qout may alias.
 hipError_t launch_stage_fp64(hipStream_t s, const StageArgs& a, const double* Qin, const double* Q0, double* Qout,
                              const double* dtp, double dt, double alpha, double* part, double* cpart);

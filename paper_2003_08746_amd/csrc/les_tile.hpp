@@ -1,0 +1,121 @@
+// les_tile.hpp -- building blocks of the tiled gfx950 kernels that march a
+// 32 x 16 patch of nodes in k (the stage kernel and the fused adjoint):
+// patch geometry, asynchronous row copies, counted waits, LDS-only barriers,
+// lane shifts and the schedule of (k chunk, tile) segments.
+#pragma once
+#include "les_common.hpp"
+
+namespace les {
+
+// The device's compute-unit and XCD (accelerator complex die) counts: the
+// persistent kernels run one block per CU and map consecutive blocks to one
+// XCD (each XCD has its own L2).
+struct Machine {
+  int cus = 256;
+  int xcds = 8;
+};
+
+// Work of the persistent blocks: (k chunk, tile) segments of kc planes, taken
+// round robin by nblocks blocks.
+struct Schedule {
+  int kc = 0;
+  int nblocks = 0;
+};
+
+// The schedule of nk planes of ntiles tiles on `slots` resident blocks, at
+// most kmax planes per segment.  A segment of n planes runs n + 2 iterations
+// (the planes below and above it) and about one more for its start, so the
+// time of a launch is that of its slowest block, block 0: the sum of n + 3
+// over its segments.  The number of chunks with the smallest sum is taken,
+// the fewest on ties.
+Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax);
+
+// The most planes one segment may march: its per-thread element offsets,
+// taken from two planes below it, reach kc + 6 planes and must stay below
+// 2^29 (32-bit byte offsets of doubles).  0 when even one plane is too large.
+inline int segment_kmax(const Layout& L) {
+  const long long k = (1LL << 29) / L.sk - 6;
+  return k < 1 ? 0 : (k > (1 << 30) ? (1 << 30) : (int)k);
+}
+
+// Global accesses use a uniform (scalar) base per field plus a 32-bit
+// per-thread byte offset, so that each access needs one VGPR for its address.
+template <class X>
+__device__ __forceinline__ X ldo(const X* base, unsigned off) {
+  return *(const X*)((const char*)base + (size_t)(off * (unsigned)sizeof(X)));
+}
+template <class X>
+__device__ __forceinline__ void sto(X* base, unsigned off, X v) {
+  *(X*)((char*)base + (size_t)(off * (unsigned)sizeof(X))) = v;
+}
+
+// One asynchronous global->LDS copy of 16 bytes (two doubles) per lane to 1 KB
+// of consecutive LDS (dst uniform; lane l's 16 bytes land at dst + 16 l).
+__device__ __forceinline__ void copy_to_lds(const char* src, double* dst) {
+  __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
+// s_waitcnt vmcnt(N): all but the N most recent vector memory operations of
+// this wave have completed (expcnt and lgkmcnt left unconstrained)
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
+}
+
+// Block barrier for LDS data only: release/acquire at workgroup scope for
+// the local address space, so the wave waits for its own LDS operations but
+// not for outstanding global loads, stores or global->LDS copies (which a
+// full __syncthreads drains).
+__device__ __forceinline__ void lds_barrier() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// The value of the lane before / after this one (DPP wave shifts by one lane;
+// the end lanes read 0).
+__device__ __forceinline__ float lane_prev(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_next(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_prev(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_next(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// The ten metric values of this thread's node from its wave's copied rows
+// (p = &block[0][row][column], fields 64 doubles apart).  Read by hand, with
+// the wait for the reads in the same block: the compiler would wait for
+// every outstanding copy, load and store of the wave before an LDS read of a
+// block that copies write.  The caller has waited for the copies; the reads
+// are done when this returns, so the block may be copied over.
+__device__ __forceinline__ void read_metric_rows(const double* p, double m[9], double& J) {
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  d2 m0, m1, m2, m3, m4;
+  const unsigned la = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const double*)p;
+  asm volatile(
+      "ds_read2st64_b64 %0, %5 offset0:0 offset1:1\n"
+      "ds_read2st64_b64 %1, %5 offset0:2 offset1:3\n"
+      "ds_read2st64_b64 %2, %5 offset0:4 offset1:5\n"
+      "ds_read2st64_b64 %3, %5 offset0:6 offset1:7\n"
+      "ds_read2st64_b64 %4, %5 offset0:8 offset1:9\n"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(m0), "=&v"(m1), "=&v"(m2), "=&v"(m3), "=&v"(m4)
+      : "v"(la)
+      : "memory");
+  m[0] = m0.x; m[1] = m0.y; m[2] = m1.x; m[3] = m1.y; m[4] = m2.x;
+  m[5] = m2.y; m[6] = m3.x; m[7] = m3.y; m[8] = m4.x;
+  J = m4.y;
+}
+
+}  // namespace les

@@ -108,6 +108,28 @@ def test_residual_adjoint_dot_product(orc, lesmi, name):
     s.close()
 
 
+@pytest.mark.parametrize("n,alpha", [((23, 8, 6), 0.5), ((24, 9, 7), 0.7), ((26, 10, 5), 0.5), ((27, 11, 9), 0.7)])
+def test_residual_adjoint_tile_edges(orc, lesmi, n, alpha):
+    """Periodic boxes whose output nodes (n + 4 an axis) just fill one tile of
+    the dissipation pass (28 x 12) or of the flux pass (30 x 14) and exceed it
+    by one row and column, for both forms of the anisotropic scaling.  The
+    bound is the one of the dot products above."""
+    case = _with_pressure_noise(
+        I.periodic_case(*n, I.wavy_grid(*n, L=(2.0, 1.5, 1.0), amp=0.1), I.smooth_state(*n, seed=21, amp=0.1),
+                        mu_ref=3e-3, alpha=alpha, sgs=1), 37)
+    print(f"[gpu] residual adjoint tiles {n}", flush=True)
+    m = orc.metrics(case)
+    v = _interior_rand(case, 1)
+    w = _interior_rand(case, 2, scale_by_field=False)
+    _, dR = orc.residual_tangent(case, m, case["Q"], v)
+    s = lesmi.Solver(case)
+    Qbar = s.download(s.residual_adjoint(s.upload(case["Q"]), s.upload(w)))
+    lhs, rhs = _dot(w, dR), _dot(Qbar, v)
+    scale = float(np.abs(I.interior(w) * I.interior(dR)).sum())
+    assert abs(lhs - rhs) <= 1e-12 * scale, (lhs, rhs, scale)
+    s.close()
+
+
 @pytest.mark.parametrize("name,i_f", [("jet61x29x23", 7), ("wavy5x6x7", 2), ("jet61x29x23_ci", 7)])
 def test_rk_step_adjoint_dot_product(orc, lesmi, name, i_f):
     """One RK step with forcing on plane i_f: <w, dQ^{n+1}> against
