@@ -172,7 +172,7 @@ typedef struct {
  * R_gas <= 0, Pr <= 0, negative k2/k4/mu_ref/CI, sgs outside 0..2, unknown
  * prec; LES_ERR_NOMEM when the block's arrays (20 FP64 fields of
  * field_elems doubles, 10 more FP32 ones when mixed) do not fit.  sgs = 2
- * allocates the dynamic closure's work arrays (27 fields) here too. */
+ * allocates the dynamic closure's work array (4 fields) here too. */
 int les_create(les_ctx **out, const les_grid *grid, const les_metrics *metrics,
                const les_flow_params *params, void *hip_stream);
 

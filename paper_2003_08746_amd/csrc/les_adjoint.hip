@@ -561,10 +561,6 @@ __device__ __forceinline__ void finish_node(const Layout& L, int j, int k, const
 constexpr int DTX = BX - 4, DTY = BY - 4;  // output tile of the dissipation pass
 constexpr int DNH = 2 * DTX + 2 * DTY;     // ring nodes
 
-// Keeps the computation of x before this point (the compiler would sink it to
-// the use, past a barrier, with all of its inputs alive).
-__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
-
 struct DissArgs {
   TileArgs t;
   double* qout;

@@ -153,8 +153,8 @@ static hipError_t bc_fill(les_ctx* c, double* Q) {
 // ghosts filled), when the context uses the dynamic closure.
 static hipError_t dyn_update(les_ctx* c, const double* Q64, const float* Q32) {
   if (c->P.sgs != 2) return hipSuccess;
-  return Q32 ? les::launch_dynamic_f32(c->s, c->L, c->bc, c->P, c->M, Q32, c->dynw, c->dyn)
-             : les::launch_dynamic(c->s, c->L, c->bc, c->P, c->M, Q64, c->dynw, c->dyn);
+  return Q32 ? les::launch_dynamic_f32(c->s, c->L, c->mach, c->bc, c->P, c->M, Q32, c->dynw, c->dyn)
+             : les::launch_dynamic(c->s, c->L, c->mach, c->bc, c->P, c->M, Q64, c->dynw, c->dyn);
 }
 
 // Resolve recorded event pairs into the running total (synchronises).

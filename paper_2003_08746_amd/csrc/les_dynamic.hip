@@ -13,18 +13,13 @@
 // ^ the test filter (weights 1/4, 1/2, 1/4 along each index), u~ and T~ the
 // test-filtered Favre velocity and temperature, D = (1/J)^(1/3).
 //
-// Three launches per evaluation:
-//   k_dyn_plane   per (i, j) tile and segment of k planes, marching in k:
-//                 the 23 grid-level fields of each plane (rho, rho u,
-//                 rho T, rho u u, rho u T on the whole padded box; the 9
-//                 strain and temperature-gradient products on [-1, n]^3)
-//                 computed into LDS and filtered along i and j there, then
-//                 along k in registers; written on [-1, n]^3;
-//   k_dyn_node    per interior column and segment of k: the test-filtered
-//                 Favre velocity and temperature gradients and the four
-//                 contractions at each node, summed over the segment's k
-//                 in ascending order;
-//   k_dyn_coef    per padded column: the segment sums added in ascending
+// Two launches per evaluation:
+//   k_dyn_fused   per (i, j) tile and chunk of k planes: the 23 grid-level
+//                 fields (rho, rho u, rho T, rho u u, rho u T and the 9 strain
+//                 and temperature-gradient products), the test filter along
+//                 i, j and k, the test-filtered gradients and the four
+//                 contractions, summed over the chunk's k in ascending order;
+//   k_dyn_coef    per padded column: the chunk sums added in ascending
 //                 order (a fixed order) and the clipped ratios; ghost
 //                 columns take the wrapped (periodic) or nearest interior
 //                 (Dirichlet) column, across the polar axis the ring column
@@ -33,9 +28,7 @@
 // direction).  On the polar axis (a node of zero volume) the strain and
 // temperature-gradient products are 0 and no contractions are formed.
 // The filter is separable and applied along i, then j, then k, each a
-// three-point sum evaluated left to right.  This is an optional model: its
-// passes move about 0.45 KB of HBM traffic per point and evaluation (the 23
-// filtered fields written once and read once).
+// three-point sum evaluated left to right.
 
 #include "les_dynamic.hpp"
 
@@ -44,248 +37,270 @@ namespace les {
 namespace {
 
 constexpr int NRAW = 23;
-// symmetric index pairs (a <= b) in the order of the raw fields
-__constant__ int kPair[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
+// symmetric index pairs (a <= b) in the order of the raw fields: 00 01 02 11 12 22
+__device__ constexpr int pair_a(int q) { return q < 3 ? 0 : (q < 5 ? 1 : 2); }
+__device__ constexpr int pair_b(int q) { return q < 3 ? q : (q < 5 ? q - 2 : 2); }
 
-// primitives (u, v, w, T) of a state node, in FP64
-template <class QI>
-__device__ inline void dyn_prims(const QI* Q, long long fe, long long n, const Phys& P, double& rho, double u[3],
-                                 double& T) {
-  rho = (double)Q[n];
-  for (int a = 0; a < 3; ++a) u[a] = (double)Q[(1 + a) * fe + n] / rho;
-  const double p = P.gm1 * ((double)Q[4 * fe + n] - 0.5 * rho * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]));
-  T = p / rho * P.inv_R;
-}
-
-// strain rate's deviatoric part and |S| = sqrt(2 S:S) from du[a][x]
-__device__ inline void dyn_strain(const double du[3][3], double Sd[3][3], double& mag) {
-  double S[3][3], ss = 0.0;
-  for (int a = 0; a < 3; ++a)
-    for (int x = 0; x < 3; ++x) {
-      S[a][x] = 0.5 * (du[a][x] + du[x][a]);
-      ss += S[a][x] * S[a][x];
-    }
-  const double tr = (S[0][0] + S[1][1] + S[2][2]) / 3.0;
-  for (int a = 0; a < 3; ++a)
-    for (int x = 0; x < 3; ++x) Sd[a][x] = S[a][x] - (a == x ? tr : 0.0);
-  mag = sqrt(2.0 * ss);
-}
-
-// chain rule: physical gradient from index-space differences d[e] (e = xi,
-// eta, zeta) and the node's metrics over J
-__device__ inline void dyn_chain(const double* M, long long fe, long long n, const double d[3], double g[3]) {
-  const double J = M[9 * fe + n];
-  for (int x = 0; x < 3; ++x) g[x] = J * (M[x * fe + n] * d[0] + M[(3 + x) * fe + n] * d[1] + M[(6 + x) * fe + n] * d[2]);
-}
-
-// Tile of k_dyn_plane: DPX x DPY threads hold the raw fields of the output
-// tile (DPX - 2) x (DPY - 2) and its one-node ring; a block marches DPK
-// output planes in k.  The primitives are formed once per node and plane on
-// the thread tile and one more ring (PPX x PPY) and shared through LDS.
-constexpr int DPX = 32, DPY = 16, DPK = 16;
-constexpr int DPTI = DPX - 2, DPTJ = DPY - 2;
-constexpr int PPX = DPX + 2, PPY = DPY + 2;
-
-__host__ __device__ inline long long dyn_plane_tiles(const Layout& L) {
-  return (long long)((L.ni + 2 + DPTI - 1) / DPTI) * ((L.nj + 2 + DPTJ - 1) / DPTJ);
-}
-inline long long dyn_plane_blocks(const Layout& L) { return dyn_plane_tiles(L) * ((L.nk + 2 + DPK - 1) / DPK); }
-
-// the primitives (rho, u, v, w, T) of node (i, j, k), zero off the padded box
-template <class QI>
-__device__ inline void dyn_prims_at(const Layout& L, const Phys& P, const QI* __restrict__ Q, int i, int j, int k,
-                                    double pr[5]) {
-  for (int c = 0; c < 5; ++c) pr[c] = 0.0;
-  if (i >= -2 && j >= -2 && k >= -2 && i <= L.ni + 1 && j <= L.nj + 1 && k <= L.nk + 1)
-    dyn_prims(Q, L.fe, L.at(i, j, k), P, pr[0], &pr[1], pr[4]);
-}
-
-// A double from the neighbouring lane of the wave (DPP wave shifts by one
-// lane): lane l reads lane l - 1 (shr) or l + 1 (shl); the end lanes read 0.
-__device__ inline double lane_prev(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-__device__ inline double lane_next(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-
-// V[q] = the test filter of raw field q (along i, then j, then k) at every
-// node of [-1, n]^3.  Each block owns a tile and a segment of DPK output
-// planes.  Per plane k of its march: the primitives of plane k + 1 into LDS,
-// the raw fields of plane k in registers (in-plane neighbours' primitives
-// from LDS, those of planes k -+ 1 of the thread's own column from registers
-// and LDS), the filter along i across lanes into LDS, along j from LDS, and
-// along k in
-// registers: out(k) = (0.25 G(k-1) + 0.5 G(k)) + 0.25 G(k+1), carried as the
-// pending sum of the two earlier planes and a quarter of the last.
-template <class QI>
-__global__ void __launch_bounds__(DPX * DPY) k_dyn_plane(Layout L, Phys P, int axis, const double* __restrict__ M,
-                                                         const QI* __restrict__ Q, double* __restrict__ V) {
-  __shared__ double sF[NRAW][DPY][DPX];
-  __shared__ double sP[2][5][PPY][PPX];
-  const long long fe = L.fe;
-  const int tiles_i = (L.ni + 2 + DPTI - 1) / DPTI;
-  const long long tiles = dyn_plane_tiles(L);
-  const long long b = blockIdx.x;
-  const long long tb = b % tiles;
-  const int ka = -1 + (int)(b / tiles) * DPK;                // first output plane
-  const int kb = ka + DPK < L.nk + 1 ? ka + DPK : L.nk + 1;  // one past the last
-  const int tx = threadIdx.x % DPX, ty = threadIdx.x / DPX;
-  const int i0 = -1 + (int)(tb % tiles_i) * DPTI, j0 = -1 + (int)(tb / tiles_i) * DPTJ;
-  const int i = i0 - 1 + tx, j = j0 - 1 + ty;  // this thread's node; the LDS tiles start at (i0 - 2, j0 - 2)
-  const bool in_box = i <= L.ni + 1 && j <= L.nj + 1;
-  // the strain and temperature-gradient products on [-1, n]^3, except on the
-  // polar axis (a node of zero volume, D = 0, whose strain is 0/0: 0 there)
-  const bool grad_ij = i >= -1 && j >= -1 && i <= L.ni && j <= L.nj && !(axis && j == 0);
-  const bool out_node = tx >= 1 && tx < DPX - 1 && ty >= 1 && ty < DPY - 1 && i <= L.ni && j <= L.nj;
-
-  // primitives of plane kp on the LDS tile, into buffer kp & 1
-  auto prims_plane = [&](int kp) {
-    for (int t = threadIdx.x; t < PPX * PPY; t += DPX * DPY) {
-      const int x = t % PPX, y = t / PPX;
-      double pr[5];
-      dyn_prims_at(L, P, Q, i0 - 2 + x, j0 - 2 + y, kp, pr);
-      for (int c = 0; c < 5; ++c) sP[kp & 1][c][y][x] = pr[c];
-    }
-  };
-  double pm[5];  // primitives of plane k - 1 at this node
-  dyn_prims_at(L, P, Q, i, j, ka - 2, pm);
-  prims_plane(ka - 1);
-  double pend[NRAW], quarter[NRAW];
-  for (int q = 0; q < NRAW; ++q) pend[q] = quarter[q] = 0.0;
-  for (int k = ka - 1; k <= kb; ++k) {
-    // (the previous plane's readers of buffer (k + 1) & 1 and of sF passed
-    // the barrier before its filter)
-    prims_plane(k + 1);
-    __syncthreads();
-    const int bc = k & 1, bn = (k + 1) & 1;
-    double pc[5];
-    for (int c = 0; c < 5; ++c) pc[c] = sP[bc][c][ty + 1][tx + 1];
-    double F[NRAW];
-    for (int q = 0; q < NRAW; ++q) F[q] = 0.0;
-    if (in_box) {
-      const double rho = pc[0], u[3] = {pc[1], pc[2], pc[3]}, T = pc[4];
-      F[0] = rho;
-      for (int a = 0; a < 3; ++a) F[1 + a] = rho * u[a];
-      F[4] = rho * T;
-      for (int q = 0; q < 6; ++q) F[5 + q] = rho * u[kPair[q][0]] * u[kPair[q][1]];
-      for (int a = 0; a < 3; ++a) F[11 + a] = rho * u[a] * T;
-      if (grad_ij && k >= -1 && k <= L.nk) {
-        // node gradients of u, v, w, T (central differences, chain rule)
-        double dd[4][3];
-        for (int a = 0; a < 4; ++a) {
-          dd[a][0] = 0.5 * (sP[bc][1 + a][ty + 1][tx + 2] - sP[bc][1 + a][ty + 1][tx]);
-          dd[a][1] = 0.5 * (sP[bc][1 + a][ty + 2][tx + 1] - sP[bc][1 + a][ty][tx + 1]);
-          dd[a][2] = 0.5 * (sP[bn][1 + a][ty + 1][tx + 1] - pm[1 + a]);
-        }
-        const long long n = L.at(i, j, k);
-        double du[3][3], dT[3], Sd[3][3], mag;
-        for (int a = 0; a < 3; ++a) dyn_chain(M, fe, n, dd[a], du[a]);
-        dyn_chain(M, fe, n, dd[3], dT);
-        dyn_strain(du, Sd, mag);
-        const double D = cbrt(1.0 / M[9 * fe + n]);
-        const double w = D * D * rho * mag;
-        for (int q = 0; q < 6; ++q) F[14 + q] = w * Sd[kPair[q][0]][kPair[q][1]];
-        for (int a = 0; a < 3; ++a) F[20 + a] = w * dT[a];
-      }
-    }
-    for (int c = 0; c < 5; ++c) pm[c] = pc[c];
-    // along i: the row's neighbours are the adjacent lanes (a row of the
-    // tile is 32 consecutive lanes of one wave; only interior columns are
-    // used below)
-    for (int q = 0; q < NRAW; ++q) sF[q][ty][tx] = 0.25 * lane_prev(F[q]) + 0.5 * F[q] + 0.25 * lane_next(F[q]);
-    __syncthreads();
-    // along j, then along k
-    if (out_node) {
-      const long long n = L.at(i, j, k - 1);
-      for (int q = 0; q < NRAW; ++q) {
-        const double g = 0.25 * sF[q][ty - 1][tx] + 0.5 * sF[q][ty][tx] + 0.25 * sF[q][ty + 1][tx];
-        if (k - 1 >= ka) V[q * fe + n] = pend[q] + 0.25 * g;
-        pend[q] = quarter[q] + 0.5 * g;
-        quarter[q] = 0.25 * g;
-      }
-    }
-  }
-}
-
-// x[0..3] = L^d:M, M:M, K.N, N.N at interior node (i, j, k) from the
-// filtered fields V (rho^, (rho u)^, (rho T)^ are also read at the six
-// axis neighbours)
-__device__ inline void dyn_contract(const Layout& L, const double* __restrict__ M, const double* __restrict__ V,
-                                    int i, int j, int k, double x[4]) {
-  const long long fe = L.fe, n = L.at(i, j, k);
-  const long long st[3] = {1, L.sj, L.sk};
-  // test-filtered velocity and temperature at the axis neighbours
-  double dd[4][3];
-  for (int e = 0; e < 3; ++e) {
-    const long long p1 = n + st[e], p0 = n - st[e];
-    const double r1 = V[p1], r0 = V[p0];
-    for (int a = 0; a < 3; ++a) dd[a][e] = 0.5 * (V[(1 + a) * fe + p1] / r1 - V[(1 + a) * fe + p0] / r0);
-    dd[3][e] = 0.5 * (V[4 * fe + p1] / r1 - V[4 * fe + p0] / r0);
-  }
-  double du[3][3], dT[3], Sd[3][3], mag;
-  for (int a = 0; a < 3; ++a) dyn_chain(M, fe, n, dd[a], du[a]);
-  dyn_chain(M, fe, n, dd[3], dT);
-  dyn_strain(du, Sd, mag);
-  const double D = cbrt(1.0 / M[9 * fe + n]);
-  const double Dt2 = 4.0 * D * D;  // (2 D)^2
-  double fv[NRAW];
-  for (int q = 0; q < NRAW; ++q) fv[q] = V[q * fe + n];
-  double Lm[3][3], Mm[3][3];
+// strain rate's deviatoric part (by pairs) and |S| = sqrt(2 S:S) from du[a][x]
+__device__ __forceinline__ void dyn_strain(const double du[][3], double Sd[6], double& mag) {
+  double ss = 0.0;
+#pragma unroll
   for (int q = 0; q < 6; ++q) {
-    const int a = kPair[q][0], c = kPair[q][1];
-    Lm[a][c] = Lm[c][a] = fv[5 + q] - fv[1 + a] * fv[1 + c] / fv[0];
-    Mm[a][c] = Mm[c][a] = 2.0 * fv[14 + q] - 2.0 * Dt2 * fv[0] * mag * Sd[a][c];
+    const int a = pair_a(q), b = pair_b(q);
+    Sd[q] = a == b ? du[a][a] : 0.5 * (du[a][b] + du[b][a]);
+    ss += (a == b ? 1.0 : 2.0) * Sd[q] * Sd[q];
   }
-  const double tr = (Lm[0][0] + Lm[1][1] + Lm[2][2]) / 3.0;
-  for (int a = 0; a < 3; ++a) Lm[a][a] -= tr;
-  double lm = 0.0, mm = 0.0, kn = 0.0, nn = 0.0;
-  for (int a = 0; a < 3; ++a)
-    for (int c = 0; c < 3; ++c) {
-      lm += Lm[a][c] * Mm[a][c];
-      mm += Mm[a][c] * Mm[a][c];
-    }
-  for (int a = 0; a < 3; ++a) {
-    const double K = fv[11 + a] - fv[1 + a] * fv[4] / fv[0];
-    const double N = fv[20 + a] - Dt2 * fv[0] * mag * dT[a];
-    kn += K * N;
-    nn += N * N;
-  }
-  x[0] = lm;
-  x[1] = mm;
-  x[2] = kn;
-  x[3] = nn;
+  const double tr = (Sd[0] + Sd[3] + Sd[5]) * (1.0 / 3.0);
+  Sd[0] -= tr;
+  Sd[3] -= tr;
+  Sd[5] -= tr;
+  double r = sqrt_pos(2.0 * ss);
+  pin(r);  // (no branch)
+  mag = ss > 0.0 ? r : 0.0;
 }
 
-// Column segments of the k sums: DNK planes per thread, over the nks
-// distinct planes (nk - 1 along a superposed k direction, whose last plane
-// is its first one's place).
-constexpr int DNK = 16;
-inline int dyn_nseg(int nks) { return (nks + DNK - 1) / DNK; }
+// Patch of 32 x 16 nodes (one thread each) whose inner 28 x 12 nodes are the
+// tile a block contracts.
+constexpr int DBX = 32, DBY = 16, DNT = DBX * DBY;
+constexpr int DTI = DBX - 4, DTJ = DBY - 4;
 
-// Xp[q][seg][j][i] = sum over k of segment seg (ascending) of contraction q
-// at the interior nodes of column (i, j).
-__global__ void __launch_bounds__(256) k_dyn_node(Layout L, int nks, int nseg, int axis, const double* __restrict__ M,
-                                                  const double* __restrict__ V, double* __restrict__ Xp) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+struct DynArgs {
+  Layout L;
+  Phys P;
+  const double* M;
+  double* Xp;
+  int axis, nks, nch, kc, ntx, nblocks, per_xcd, nxcd, nseg;
+};
+
+// One pass: raw fields, test filter and contractions, marching in k.  In
+// step t of a segment a thread
+//   C  forms the base fields of plane t+1 and the other 18 of plane t from
+//      primitives in registers (the xi neighbours' by lane shifts, a patch row
+//      being 32 lanes; the eta neighbours' from LDS), filters them along i
+//      across lanes, and writes the sums to LDS;
+//   E  filters along j from LDS and along k in registers, carried as the
+//      pending sum of two planes and the last plane: the base fields of plane
+//      t and the others of plane t-1 are complete, so the test-filtered
+//      velocity and temperature are known at planes t-2 .. t and plane t-1 is
+//      contracted.
+// The filter's sums are taken with the weights 1, 2, 1, so filtered fields are
+// 64 times and contractions 64^2 times their values (exactly: the rounding is
+// that of the scaled weights), which the ratios of contractions cancel.
+// Q and the metrics are read once per patch node (1.5 times in all), and no
+// field is written: the two passes this replaces wrote 23 filtered fields,
+// read them back and used full divisions and cube roots.  Bound by the VALU
+// issue rate (about 800 instructions a node and step, a quarter of them lane
+// shifts, at two waves a SIMD).  Each sum keeps its two earlier planes in
+// registers (92 of 256), so the order of E keeps few other values at a time.
+// Measured on the 256 x 128 x 128 jet: 297 us, the two passes 490 + 302; on a
+// 60 x 44 x 33 block 30 us, 480.
+template <class QI>
+__global__ void __launch_bounds__(DNT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
+  __shared__ double sF[NRAW][DBY][DBX];
+  __shared__ double sP[4][DBY][DBX];  // u, v, w, T of plane t
+  __shared__ double sU[4][DBY][DBX];  // test-filtered u, v, w, T of plane t-1
+  const int v = (blockIdx.x % a.nxcd) * a.per_xcd + blockIdx.x / a.nxcd;
+  if (v >= a.nblocks) return;
+  const Layout& L = a.L;
+  const long long fe = L.fe;
+  const int tx = threadIdx.x % DBX, ty = threadIdx.x / DBX;
   const long long ncoli = (long long)L.ni * L.nj;
-  if (t >= ncoli * nseg) return;
-  const long long col = t % ncoli;
-  const int seg = (int)(t / ncoli);
-  const int i = (int)(col % L.ni), j = (int)(col / L.ni);
-  // (no contractions on the polar axis: its column takes the ring j = 1's)
-  const int k1 = (axis && j == 0) ? 0 : ((seg + 1) * DNK < nks ? (seg + 1) * DNK : nks);
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = seg * DNK; k < k1; ++k) {
-    double x[4];
-    dyn_contract(L, M, V, i, j, k, x);
-    for (int q = 0; q < 4; ++q) s[q] += x[q];
+  for (int wq = v; wq < a.nseg; wq += a.nblocks) {
+    const int ntiles = a.nseg / a.nch;
+    const int ch = wq / ntiles, tile = wq % ntiles;
+    const int kb = ch * a.kc, ke = min(a.nks, kb + a.kc);
+    const int i = (tile % a.ntx) * DTI - 2 + tx, j = (tile / a.ntx) * DTJ - 2 + ty;
+    const bool out = tx >= 2 && tx < DBX - 2 && ty >= 2 && ty < DBY - 2 && i < L.ni && j < L.nj;
+    // on the polar axis (a node of zero volume) the strain is 0/0: 0 there
+    const bool grad = !(a.axis && j == 0);
+    // (nodes off the padded box repeat its edge; no output depends on them)
+    const unsigned col = (unsigned)L.at(i < L.ni + 1 ? i : L.ni + 1, j < L.nj + 1 ? j : L.nj + 1, 0);
+    auto plane = [&](int k) { return (long long)(k < L.nk + 1 ? (k > -2 ? k : -2) : L.nk + 1) * L.sk; };
+    auto load = [&](int k, QI q[5], double m[10]) {  // Q of plane k + 1, metrics of plane k
+      const long long nq = plane(k + 1), nm = plane(k);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) q[c] = ldo(Q + nq + c * fe, col);
+#pragma unroll
+      for (int c = 0; c < 10; ++c) m[c] = ldo(a.M + nm + c * fe, col);
+    };
+    auto prims = [&](const QI q[5], double p[5]) {
+      p[0] = (double)q[0];
+      const double ir = rcp_nr(p[0]);
+      p[1] = (double)q[1] * ir;
+      p[2] = (double)q[2] * ir;
+      p[3] = (double)q[3] * ir;
+      const double pr = a.P.gm1 * ((double)q[4] - 0.5 * p[0] * (p[1] * p[1] + p[2] * p[2] + p[3] * p[3]));
+      p[4] = pr * ir * a.P.inv_R;
+    };
+    double pend[NRAW], last[NRAW], s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < NRAW; ++q) pend[q] = last[q] = 0.0;
+    double pm[4], pc[5], pn[5];   // primitives of planes t-1, t, t+1
+    double um[4], uc[4], rc = 0;  // test-filtered u, v, w, T of planes t-2, t-1; rho^ of plane t-1
+    double mo[9], do2 = 0.0;      // J m and D^2 of plane t-1
+    QI qn[5];                     // Q of plane t+1 (in flight until C)
+    double mn[10];                // metrics of plane t (in flight until C)
+    load(kb - 3, qn, mn);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) pm[c] = um[c] = uc[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) pc[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) mo[c] = 0.0;
+
+    for (int t = kb - 3; t <= ke; ++t) {
+      const bool full = t >= kb - 1, con = t > kb;  // (both uniform)
+      int tl = threadIdx.x;  // (LDS addresses are formed again in each step)
+      asm volatile("" : "+v"(tl));
+      const int tx = tl % DBX, ty = tl / DBX;
+      const int yp = ty < DBY - 1 ? ty + 1 : ty, ym = ty > 0 ? ty - 1 : ty;
+      // ---- C ----
+      auto put = [&](int q, double f) { sF[q][ty][tx] = fma(2.0, f, lane_prev(f)) + lane_next(f); };
+      prims(qn, pn);
+      put(0, pn[0]);
+#pragma unroll
+      for (int c = 1; c < 5; ++c) put(c, pn[0] * pn[c]);
+      double de[4];  // eta differences of the test-filtered fields, plane t-1
+#pragma unroll
+      for (int c = 0; c < 4; ++c) de[c] = 0.5 * (sU[c][yp][tx] - sU[c][ym][tx]);
+      double m[9], d2;
+      {
+        const double J = mn[9];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) m[c] = J * mn[c];
+        const double D = icbrt(J);
+        d2 = D * D;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (full) {
+        const double rho = pc[0];
+        {
+          const double ru[3] = {rho * pc[1], rho * pc[2], rho * pc[3]};
+#pragma unroll
+          for (int q = 0; q < 6; ++q) put(5 + q, ru[pair_a(q)] * pc[1 + pair_b(q)]);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) put(11 + c, ru[c] * pc[4]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        double du[4][3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const double d0 = 0.5 * (lane_next(pc[1 + c]) - lane_prev(pc[1 + c]));
+          const double d1 = 0.5 * (sP[c][yp][tx] - sP[c][ym][tx]);
+          const double dz = 0.5 * (pn[1 + c] - pm[c]);
+#pragma unroll
+          for (int x = 0; x < 3; ++x) du[c][x] = m[x] * d0 + m[3 + x] * d1 + m[6 + x] * dz;
+        }
+        double Sd[6], mag;
+        dyn_strain(du, Sd, mag);
+        const double w = d2 * rho * mag;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) put(14 + q, grad ? w * Sd[q] : 0.0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) put(20 + c, grad ? w * du[3][c] : 0.0);
+      }
+      lds_barrier();
+
+      // ---- E ----
+      // (the LDS reads run one field ahead of the sums)
+      double r0 = sF[0][ym][tx], r1 = sF[0][ty][tx], r2 = sF[0][yp][tx];
+      auto take = [&](int q, int qnext) {
+        const double g0 = r0, g1 = r1, g2 = r2;
+        r0 = sF[qnext][ym][tx];
+        r1 = sF[qnext][ty][tx];
+        r2 = sF[qnext][yp][tx];
+        __builtin_amdgcn_sched_barrier(0);
+        const double g = fma(2.0, g1, g0) + g2;
+        const double f = pend[q] + g;
+        pend[q] = fma(2.0, g, last[q]);
+        last[q] = g;
+        pin(pend[q]);
+        pin(last[q]);
+        __builtin_amdgcn_sched_barrier(0);
+        return f;
+      };
+      double rn, un[4];
+      rn = take(0, 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) un[c] = take(1 + c, 2 + c);
+      {
+        const double ir = rcp_nr(rn);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) un[c] *= ir;
+      }
+      // plane t-1: (2 D)^2 rho^ |S~|, S~^d and dT~
+      double w = 0.0, Sd[6], dT[3];
+      {
+        double du[4][3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const double dx = 0.5 * (lane_next(uc[c]) - lane_prev(uc[c])), dz = 0.5 * (un[c] - um[c]);
+#pragma unroll
+          for (int x = 0; x < 3; ++x) du[c][x] = mo[x] * dx + mo[3 + x] * de[c] + mo[6 + x] * dz;
+        }
+        double mag;
+        dyn_strain(du, Sd, mag);
+        w = 4.0 * do2 * rc * mag;
+#pragma unroll
+        for (int x = 0; x < 3; ++x) pin(dT[x] = du[3][x]);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) pin(Sd[q]);
+        pin(w);
+      }
+      load(t + 1, qn, mn);
+      __builtin_amdgcn_sched_barrier(0);
+      if (full) {
+        double Lm[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) Lm[q] = take(5 + q, q < 5 ? 6 + q : 14) - rc * (uc[pair_a(q)] * uc[pair_b(q)]);
+        const double tr = (Lm[0] + Lm[3] + Lm[5]) * (1.0 / 3.0);
+        Lm[0] -= tr;
+        Lm[3] -= tr;
+        Lm[5] -= tr;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          const double Mq = 2.0 * take(14 + q, q < 5 ? 15 + q : 11) - 2.0 * w * Sd[q];
+          const double two = pair_a(q) == pair_b(q) ? 1.0 : 2.0;
+          s[0] += two * Lm[q] * Mq;
+          s[1] += two * Mq * Mq;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const double K = take(11 + c, 20 + c) - rc * (uc[c] * uc[3]);
+          const double N = take(20 + c, c < 2 ? 12 + c : 22) - w * dT[c];
+          s[2] += K * N;
+          s[3] += N * N;
+        }
+        if (!con) {  // (plane kb - 1 is not the chunk's)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) s[q] = 0.0;
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        sU[c][ty][tx] = un[c];
+        sP[c][ty][tx] = pn[1 + c];
+        um[c] = uc[c];
+        uc[c] = un[c];
+        pm[c] = pc[1 + c];
+      }
+      rc = rn;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) pc[c] = pn[c];
+#pragma unroll
+      for (int c = 0; c < 9; ++c) mo[c] = m[c];
+      do2 = d2;
+      lds_barrier();
+    }
+    if (out) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        a.Xp[((long long)q * a.nch + ch) * ncoli + (long long)j * L.ni + i] = grad ? s[q] : 0.0;
+    }
   }
-  for (int q = 0; q < 4; ++q) Xp[((long long)q * nseg + seg) * ncoli + col] = s[q];
 }
 
 __device__ inline int dyn_src(int x, int n, int bc) {
@@ -321,31 +336,37 @@ __global__ void __launch_bounds__(256) k_dyn_coef(Layout L, int bc0, int bc1, in
 inline unsigned nblk(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
 template <class QI>
-hipError_t run(hipStream_t s, const Layout& L, const int bc[3], const Phys& P, const double* M, const QI* Q,
-               double* work, double* dyn) {
-  double* V = work;
-  double* X = work + (long long)NRAW * L.fe;
-  const int axis = bc[1] == 3;
-  const int nks = bc[2] == 2 ? L.nk - 1 : L.nk;
-  k_dyn_plane<QI><<<(unsigned)dyn_plane_blocks(L), DPX * DPY, 0, s>>>(L, P, axis, M, Q, V);
-  const int nseg = dyn_nseg(nks);
-  k_dyn_node<<<nblk((long long)L.ni * L.nj * nseg, 256), 256, 0, s>>>(L, nks, nseg, axis, M, V, X);
-  k_dyn_coef<<<nblk(dyn_ncol(L), 256), 256, 0, s>>>(L, bc[0], bc[1], nseg, X, dyn);
+hipError_t run(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
+               const QI* Q, double* X, double* dyn) {
+  DynArgs a{L, P, M, X, bc[1] == 3};
+  a.nks = bc[2] == 2 ? L.nk - 1 : L.nk;
+  a.ntx = (L.ni + DTI - 1) / DTI;
+  const int ntiles = a.ntx * ((L.nj + DTJ - 1) / DTJ);
+  const Schedule sch = segment_schedule(ntiles, a.nks, mach.cus, a.nks);
+  a.kc = sch.kc;
+  a.nch = (a.nks + sch.kc - 1) / sch.kc;
+  a.nseg = ntiles * a.nch;
+  a.nblocks = sch.nblocks;
+  a.nxcd = mach.xcds;
+  a.per_xcd = (sch.nblocks + a.nxcd - 1) / a.nxcd;
+  k_dyn_fused<QI><<<a.per_xcd * a.nxcd, DNT, 0, s>>>(a, Q);
+  k_dyn_coef<<<nblk(dyn_ncol(L), 256), 256, 0, s>>>(L, bc[0], bc[1], a.nch, X, dyn);
   return hipGetLastError();
 }
 
 }  // namespace
 
-long long dynamic_work_elems(const Layout& L) { return (NRAW + 4LL) * L.fe; }
+// (at most one k chunk per plane)
+long long dynamic_work_elems(const Layout& L) { return 4LL * L.ni * L.nj * L.nk; }
 
-hipError_t launch_dynamic(hipStream_t s, const Layout& L, const int bc[3], const Phys& P, const double* M,
+hipError_t launch_dynamic(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
                           const double* Q, double* work, double* dyn) {
-  return run<double>(s, L, bc, P, M, Q, work, dyn);
+  return run<double>(s, L, mach, bc, P, M, Q, work, dyn);
 }
 
-hipError_t launch_dynamic_f32(hipStream_t s, const Layout& L, const int bc[3], const Phys& P, const double* M,
+hipError_t launch_dynamic_f32(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
                               const float* Q, double* work, double* dyn) {
-  return run<float>(s, L, bc, P, M, Q, work, dyn);
+  return run<float>(s, L, mach, bc, P, M, Q, work, dyn);
 }
 
 }  // namespace les

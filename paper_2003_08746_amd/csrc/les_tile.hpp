@@ -93,6 +93,10 @@ __device__ __forceinline__ double lane_next(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// Keeps the computation of x before this point (the compiler would sink it to
+// the use, past a barrier, with all of its inputs alive).
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
+
 // The ten metric values of this thread's node from its wave's copied rows
 // (p = &block[0][row][column], fields 64 doubles apart).  Read by hand, with
 // the wait for the reads in the same block: the compiler would wait for

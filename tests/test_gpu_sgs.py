@@ -131,6 +131,27 @@ def test_dynamic_coefficients_jet_shard(orc, lesmi):
     assert np.array_equal(C[2:-2, :2], C[2:-2, -4:-2]) and np.array_equal(C[:2, 2:-2], np.repeat(C[2:3, 2:-2], 2, 0))
 
 
+@pytest.mark.parametrize("n", [(28, 12, 5), (29, 13, 7), (57, 25, 6)])
+def test_dynamic_coefficients_tile_edges(orc, lesmi, n):
+    """Blocks that just fill one 28 x 12 tile of the closure's kernel, exceed
+    it by one column and row, and exceed two tiles by one; weighted as above,
+    to 1e-10."""
+    case = I.periodic_case(*n, I.wavy_grid(*n, L=(2.0, 1.5, 1.0), amp=0.1), I.smooth_state(*n, seed=23, amp=0.15),
+                           mu_ref=3e-3, sgs=2)
+    print(f"[gpu] dynamic coefficients, tiles {n}", flush=True)
+    s = lesmi.Solver(case)
+    C, D = s.dynamic_coefficients(s.upload(case["Q"]))
+    s.close()
+    m = orc.metrics(case)
+    Co, Do = orc.dynamic_coefficients(case, m, case["Q"])
+    wC, wD, _ = _column_weights(orc, case, m)
+    for lab, x, xo, w in (("C", C, Co, wC), ("D_T", D, Do, wD)):
+        a, ao = x[2:-2, 2:-2] * w, xo[2:-2, 2:-2] * w
+        assert ao.max() > 0.0, lab
+        err = np.abs(a - ao).max() / ao.max()
+        assert err <= 1e-10, (lab, err)
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_sgs_residual_parity(orc, lesmi, name):
     case = CASES[name]
