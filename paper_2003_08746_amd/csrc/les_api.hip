@@ -146,7 +146,7 @@ static hipError_t bc_fill(les_ctx* c, double* Q) {
     hipError_t e = les::launch_axis_avg(c->s, c->L, Q);
     if (e != hipSuccess) return e;
   }
-  return les::launch_ghost_fill(c->s, c->L, c->bc, Q, Q, 5, faces_of(c));
+  return les::launch_ghost_fill(c->s, c->L, c->bc, Q, Q, faces_of(c));
 }
 
 // Dynamic SGS coefficients of the state about to be differenced (its
@@ -548,7 +548,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
     for (int l = 0; l < 5; ++l) {
       double* out = l == 4 ? Q : (stage_ckpt ? stage_ckpt + (size_t)(l + 1) * 5 * fe : ctx->S[l & 1]);
       if (l > 0 && ctx->axis) HIPCHK(ctx, les::launch_axis_avg(ctx->s, L, (double*)in));
-      if (l > 0 || stage_ckpt) HIPCHK(ctx, les::launch_ghost_fill(ctx->s, L, ctx->bc, (double*)in, Q, 5, faces_of(ctx)));
+      if (l > 0 || stage_ckpt) HIPCHK(ctx, les::launch_ghost_fill(ctx->s, L, ctx->bc, (double*)in, Q, faces_of(ctx)));
       // the residual norms of R(Q^n) are reduced on the device (fused into
       // stage 1) whenever with_norms; only their copy to the host is optional
       double* part = (l == 0 && with_norms) ? ctx->part : nullptr;
@@ -762,7 +762,7 @@ int les_debug_dynamic_coefficients(les_ctx* ctx, double* Q, double* out) {
   if (!ctx) return LES_ERR_ARG;
   if (!Q || !out) return fail(ctx, LES_ERR_ARG, "les_debug_dynamic_coefficients: null pointer");
   if (ctx->P.sgs != 2) return fail(ctx, LES_ERR_STATE, "les_debug_dynamic_coefficients: sgs is not 2");
-  HIPCHK(ctx, les::launch_ghost_fill(ctx->s, ctx->L, ctx->bc, Q, Q, 5, faces_of(ctx)));
+  HIPCHK(ctx, les::launch_ghost_fill(ctx->s, ctx->L, ctx->bc, Q, Q, faces_of(ctx)));
   HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
   HIPCHK(ctx, hipMemcpyAsync(out, ctx->dyn, 2 * les::dyn_ncol(ctx->L) * sizeof(double), hipMemcpyDeviceToDevice,
                              ctx->s));

@@ -67,6 +67,7 @@ constexpr int DTI = DBX - 4, DTJ = DBY - 4;
 struct DynArgs {
   Layout L;
   Phys P;
+  Wrap wrap;
   const double* M;
   double* Xp;
   int axis, nks, nch, kc, ntx, nblocks, per_xcd, nxcd, nseg;
@@ -115,14 +116,17 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
     // on the polar axis (a node of zero volume) the strain is 0/0: 0 there
     const bool grad = !(a.axis && j == 0);
     // (nodes off the padded box repeat its edge; no output depends on them)
-    const unsigned col = (unsigned)L.at(i < L.ni + 1 ? i : L.ni + 1, j < L.nj + 1 ? j : L.nj + 1, 0);
-    auto plane = [&](int k) { return (long long)(k < L.nk + 1 ? (k > -2 ? k : -2) : L.nk + 1) * L.sk; };
+    const int ic = min(i, L.ni + 1), jc = min(j, L.nj + 1);
+    const unsigned col = (unsigned)L.at(ic, jc, 0);
+    const unsigned qcol = wrap_column(L, a.wrap, ic, jc);
     auto load = [&](int k, QI q[5], double m[10]) {  // Q of plane k + 1, metrics of plane k
-      const long long nq = plane(k + 1), nm = plane(k);
+      const PlaneRef p = wrap_plane(L, a.wrap, min(max(k + 1, -2), L.nk + 1));
+      const unsigned qo = wrap_offset(qcol, p);
+      const double* const Mk = a.M + (long long)min(max(k, -2), L.nk + 1) * L.sk;
 #pragma unroll
-      for (int c = 0; c < 5; ++c) q[c] = ldo(Q + nq + c * fe, col);
+      for (int c = 0; c < 5; ++c) q[c] = ldo(Q + p.base + c * fe, qo);
 #pragma unroll
-      for (int c = 0; c < 10; ++c) m[c] = ldo(a.M + nm + c * fe, col);
+      for (int c = 0; c < 10; ++c) m[c] = ldo(Mk + c * fe, col);
     };
     auto prims = [&](const QI q[5], double p[5]) {
       p[0] = (double)q[0];
@@ -336,9 +340,9 @@ __global__ void __launch_bounds__(256) k_dyn_coef(Layout L, int bc0, int bc1, in
 inline unsigned nblk(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
 template <class QI>
-hipError_t run(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
-               const QI* Q, double* X, double* dyn) {
-  DynArgs a{L, P, M, X, bc[1] == 3};
+hipError_t run(hipStream_t s, const Layout& L, const Machine& mach, const Wrap& wrap, const int bc[3], const Phys& P,
+               const double* M, const QI* Q, double* X, double* dyn) {
+  DynArgs a{L, P, wrap, M, X, bc[1] == 3};
   a.nks = bc[2] == 2 ? L.nk - 1 : L.nk;
   a.ntx = (L.ni + DTI - 1) / DTI;
   const int ntiles = a.ntx * ((L.nj + DTJ - 1) / DTJ);
@@ -359,14 +363,14 @@ hipError_t run(hipStream_t s, const Layout& L, const Machine& mach, const int bc
 // (at most one k chunk per plane)
 long long dynamic_work_elems(const Layout& L) { return 4LL * L.ni * L.nj * L.nk; }
 
-hipError_t launch_dynamic(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
-                          const double* Q, double* work, double* dyn) {
-  return run<double>(s, L, mach, bc, P, M, Q, work, dyn);
+hipError_t launch_dynamic(hipStream_t s, const Layout& L, const Machine& mach, const Wrap& wrap, const int bc[3], const Phys& P,
+                          const double* M, const double* Q, double* work, double* dyn) {
+  return run<double>(s, L, mach, wrap, bc, P, M, Q, work, dyn);
 }
 
-hipError_t launch_dynamic_f32(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
-                              const float* Q, double* work, double* dyn) {
-  return run<float>(s, L, mach, bc, P, M, Q, work, dyn);
+hipError_t launch_dynamic_f32(hipStream_t s, const Layout& L, const Machine& mach, const Wrap& wrap, const int bc[3], const Phys& P,
+                              const double* M, const float* Q, double* work, double* dyn) {
+  return run<float>(s, L, mach, wrap, bc, P, M, Q, work, dyn);
 }
 
 }  // namespace les

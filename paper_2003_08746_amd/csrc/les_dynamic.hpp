@@ -10,10 +10,11 @@ namespace les {
 long long dynamic_work_elems(const Layout& L);
 
 // dyn[0 .. ncol) = C, dyn[ncol .. 2 ncol) = D_T per padded column (dyn_col)
-// of the state Q (ghosts filled); work: dynamic_work_elems(L) doubles.
-hipError_t launch_dynamic(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
-                          const double* Q, double* work, double* dyn);
-hipError_t launch_dynamic_f32(hipStream_t s, const Layout& L, const Machine& mach, const int bc[3], const Phys& P, const double* M,
-                              const float* Q, double* work, double* dyn);
+// of the state Q (ghosts filled, but for those that wrap reads at
+// their source); work: dynamic_work_elems(L) doubles.
+hipError_t launch_dynamic(hipStream_t s, const Layout& L, const Machine& mach, const Wrap& wrap, const int bc[3], const Phys& P,
+                          const double* M, const double* Q, double* work, double* dyn);
+hipError_t launch_dynamic_f32(hipStream_t s, const Layout& L, const Machine& mach, const Wrap& wrap, const int bc[3], const Phys& P,
+                              const double* M, const float* Q, double* work, double* dyn);
 
 }  // namespace les

@@ -84,8 +84,12 @@ __device__ void face_value(int type, double gamma, double pe, const double nv[3]
   const double ro = qo[0];
   const double uo[3] = {qo[1] / ro, qo[2] / ro, qo[3] / ro};
   const double po = gm1 * (qo[4] - 0.5 * ro * (uo[0] * uo[0] + uo[1] * uo[1] + uo[2] * uo[2]));
-  const T cr = fsqrt(T(gamma) * pr / rr);
-  const double co = sqrt(gamma * po / ro);
+  // (an isentrope p / rho^gamma through (rho_a, c_a) reaches sound speed c at
+  // rho = rho_a (c^2 / c_a^2)^(1 / (gamma - 1)): one power)
+  const T cr2 = T(gamma) * pr / rr;
+  const double co2 = gamma * po / ro;
+  const T cr = fsqrt(cr2);
+  const double co = sqrt(co2);
   const T unr = ur[0] * T(nv[0]) + ur[1] * T(nv[1]) + ur[2] * T(nv[2]);
   const double uno = uo[0] * nv[0] + uo[1] * nv[1] + uo[2] * nv[2];
   if (type == 3) {
@@ -94,8 +98,8 @@ __device__ void face_value(int type, double gamma, double pe, const double nv[3]
     // outside, entropy from outside on inflow and from the node otherwise
     const double rm = uno - 2.0 * co / gm1;
     const T c = T(0.5 * gm1) * (unr - T(rm));
-    const T ent = fval(unr) >= 0.0 ? pr / fpow(rr, gamma) : T(po / pow(ro, gamma));
-    const T rho = fpow(c * c / (T(gamma) * ent), 1.0 / gm1);
+    const bool from_r = fval(unr) >= 0.0;
+    const T rho = (from_r ? rr : T(ro)) * fpow(c * c / (from_r ? cr2 : T(co2)), 1.0 / gm1);
     const T p = rho * c * c / T(gamma);
     T k = T(0.0);
     out[0] = rho;
@@ -120,7 +124,6 @@ __device__ void face_value(int type, double gamma, double pe, const double nv[3]
   const T un = T(0.5) * (rplus + T(rminus));
   const T c = T(0.25 * gm1) * (rplus - T(rminus));
   const bool from_r = fval(un) >= 0.0;
-  const T ent = from_r ? pr / fpow(rr, gamma) : T(po / pow(ro, gamma));
   T us[3], uns;
   if (from_r) {
     for (int a = 0; a < 3; ++a) us[a] = ur[a];
@@ -129,7 +132,7 @@ __device__ void face_value(int type, double gamma, double pe, const double nv[3]
     for (int a = 0; a < 3; ++a) us[a] = T(uo[a]);
     uns = T(uno);
   }
-  const T rho = fpow(c * c / (T(gamma) * ent), 1.0 / gm1);
+  const T rho = (from_r ? rr : T(ro)) * fpow(c * c / (from_r ? cr2 : T(co2)), 1.0 / gm1);
   const T p = rho * c * c / T(gamma);
   T k = T(0.0);
   out[0] = rho;

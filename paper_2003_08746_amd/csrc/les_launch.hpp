@@ -10,7 +10,7 @@ hipError_t launch_metrics(hipStream_t s, const Layout& L, const int bc[3], const
 hipError_t launch_metrics_copy(hipStream_t s, const Layout& L, const double* src, double* M);
 hipError_t launch_metrics_export(hipStream_t s, const Layout& L, const double* M, double* dst);
 long long ghost_count(const Layout& L);
-hipError_t launch_ghost_fill(hipStream_t s, const Layout& L, const int bc[3], double* q, const double* frozen, int nf,
+hipError_t launch_ghost_fill(hipStream_t s, const Layout& L, const int bc[3], double* q, const double* frozen,
                              const Faces& F);
 hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3], float* q, const double* frozen,
                                  const Faces& F);

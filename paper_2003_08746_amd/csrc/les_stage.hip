@@ -112,6 +112,7 @@ struct KArgs {
   int nblocks;          // blocks with work
   int per_xcd;          // blocks per XCD in the remapped order
   int nxcd;             // XCDs of the device
+  Wrap wrap;            // periodic ghosts read at their source
 };
 
 // Two Q planes, written at B of alternate planes: the only LDS values that E
@@ -283,15 +284,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const bool fx_ok = !yh && tx < BX - 1 && i < L.ni && j < L.nj;  // xi face (i, i + 1) of a tile row
     const int hi = i0 - 2 + hx2, hj = j0 - 2 + hy2;
     const bool h_ok = tid < NH2 && hi <= L.ni + 1 && hj <= L.nj + 1;
-    // element offsets of nodes (i, j, kr) and (hi, hj, kr) from the segment
-    // base
+    // element offset of node (i, j, kr) from the segment base
     const unsigned col = (unsigned)((long long)i + (long long)j * L.sj + L.o);
-    const unsigned hcol = (unsigned)((long long)hi + (long long)hj * L.sj + L.o);
-    // own-column loads use the node clamped into the padded box, so that they
-    // and their uses need no branch (threads past the box load, and never
-    // publish, a copy of the box's edge node)
-    const unsigned qcol =
-        (unsigned)((long long)min(i, L.ni + 1) + (long long)min(j, L.nj + 1) * L.sj + L.o);
+    // columns of Q.  Own-column loads use the node clamped into the padded
+    // box, so that they and their uses need no branch (threads past the box
+    // load, and never publish, a copy of the box's edge node)
+    const unsigned qcol = wrap_column(L, a.wrap, min(i, L.ni + 1), min(j, L.nj + 1));
+    const unsigned hcol = wrap_column(L, a.wrap, min(hi, L.ni + 1), min(hj, L.nj + 1));
+    auto load_plane = [&](int k, T q[5]) {
+      const PlaneRef p = wrap_plane(L, a.wrap, k);
+      load_q<T>(Qin + p.base, fe, wrap_offset(qcol, p), q);
+    };
 
     // ---- column queues (own node) ----
     T qw[5], qa[5], qn[5];  // Q at t (written at B), t+1 and t+2 (prefetch)
@@ -324,12 +327,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const long long lane_el = (long long)fsel * fe + L.o + icp + (long long)jcp * L.sj;
     const long long fstep2 = 2 * fe * (long long)sizeof(double);
     dma_rows<10>((const char*)(kp->M + lane_el + (long long)(kb - 1) * L.sk), fstep2, &mbw[wave][0][0][0]);
-    load_q<T>(Qs, fe, qcol, qm1);
-    load_q<T>(Qs, fe, qcol + sk, qw);
-    load_q<T>(Qs, fe, qcol + 2 * sk, qa);
+    load_plane(kb - 2, qm1);
+    load_plane(kb - 1, qw);
+    load_plane(kb, qa);
     prims(kp->P, qm1, um1, pm1);
     prims(kp->P, qw, up1, pp1);  // plane kb-1, written at the first B
-    if (h_ok) load_q<T>(Qs, fe, hcol + sk, hq);
+    if (h_ok) {
+      const PlaneRef p = wrap_plane(L, a.wrap, kb - 1);
+      load_q<T>(Qin + p.base, fe, wrap_offset(hcol, p), hq);
+    }
     wait_vm<0>();  // the first metric rows (later ones are waited for before each stage update)
 
     for (int t = kb - 1; t <= ke; ++t) {
@@ -394,14 +400,26 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // FP64 skips the loads; FP32 issues them all the same (planes ke + 1 at
       // most, inside the padded box), because the branches between its
       // sub-steps cost more (247 against 239 us) than the loads.
-      const unsigned qoff2 = qcol + (unsigned)(min(t + 2, ke + 1) - kr) * sk;
+      // (planes past the block's last are the only wrapped ones here)
+      const QI *Q2 = Qs, *Q1 = Qs;
+      const int k2 = min(t + 2, ke + 1);
+      unsigned qoff2 = (qcol & 0x7fffffffu) + (unsigned)(k2 - kr) * sk;
+      unsigned hoff1 = (hcol & 0x7fffffffu) + (unsigned)(t + 1 - kr) * sk;
+      if (k2 >= kq->L.nk) {
+        const PlaneRef p2 = wrap_plane(kq->L, kq->wrap, k2);
+        Q2 = Qin + p2.base;
+        qoff2 = wrap_offset(qcol, p2);
+        const PlaneRef p1 = wrap_plane(kq->L, kq->wrap, t + 1);
+        Q1 = Qin + p1.base;
+        hoff1 = wrap_offset(hcol, p1);
+      }
       auto load_ahead = [&](int q) {
         if (sizeof(T) == 4 || t < ke) {
           if (q == 0) {
-            if (h_ok) load_q<T>(Qs, fe, hcol + (unsigned)(t + 1 - kr) * sk, hq);
+            if (h_ok) load_q<T>(Q1, fe, hoff1, hq);
           } else {
             copy_to_lds(msrc + (q - 1) * fstep2, mdst + (q - 1) * 128);
-            qn[q - 1] = (T)ldo(Qs + (q - 1) * fe, qoff2);
+            qn[q - 1] = (T)ldo(Q2 + (q - 1) * fe, qoff2);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -612,7 +630,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // copied to LDS two planes ago); consumed after the update
       double cm[9];
       if (CFL) {
-        const unsigned n = (out_ok && t > kb) ? nt - sk : qcol;
+        const unsigned n = (out_ok && t > kb) ? nt - sk : (unsigned)L.o;
 #pragma unroll
         for (int c = 0; c < 9; ++c) cm[c] = ldo(kq->M + sb + c * fe, n);
       }
@@ -754,7 +772,7 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
   if (part && cpart) return hipErrorInvalidValue;  // norms belong to stage 1, the CFL bound to stage 5
   const Config c = config(sa.L, sa.sch, sa.mach.xcds);
   KArgs a{sa.L,  sa.P,  sa.M,      sa.f,   sa.dyn,         sa.axis,   sa.i_f,
-          c.ntx, c.nty, sa.sch.kc, c.nseg, sa.sch.nblocks, c.per_xcd, sa.mach.xcds};
+          c.ntx, c.nty, sa.sch.kc, c.nseg, sa.sch.nblocks, c.per_xcd, sa.mach.xcds, sa.wrap};
   // the optional SGS models (dynamic closure, isotropic SGS stress) and the
   // polar axis run in instantiations of their own, so that each path keeps
   // only the registers it needs

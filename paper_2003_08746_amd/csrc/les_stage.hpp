@@ -15,6 +15,7 @@ struct StageArgs {
   const double* dyn = nullptr;  // dynamic SGS coefficients per column (P.sgs == 2)
   int axis = 0;                 // j = 0 is the polar axis of an O-grid
   Machine mach;
+  Wrap wrap;                    // periodic ghosts of Qin read at their source
 };
 
 // The schedule of the fused kernel for this layout (LES_SEG in the environment
@@ -27,7 +28,7 @@ Schedule stage_schedule(const Layout& L, const Machine& m);
 int stage_kmax(const Layout& L);
 
 // One FP64 stage: Qout = Q0 - alpha dt R(Qin) on the interior (Qin's ghosts
-// already filled).  dtp (device) overrides dt when non-null.  part: norm
+// already filled, but for those of periodic directions with a.wrap).  dtp (device) overrides dt when non-null.  part: norm
 // partials (or null).  cpart (or null): per-block minima of the local CFL
 // bound of the updated state (one double per block; not together with part).
 // Q0 and Qout may alias.

@@ -38,6 +38,41 @@ inline int segment_kmax(const Layout& L) {
   return k < 1 ? 0 : (k > (1 << 30) ? (1 << 30) : (int)k);
 }
 
+// Periodic ghosts read at their source, so that nobody has to copy them: per[d]
+// is the period of direction d (n, or n - 1 with superposed first and last
+// nodes), 0 for a direction whose ghosts are read where they are.  A node
+// outside the block along an in-plane direction with per = 0 keeps its place
+// in all three (an edge ghost of a Dirichlet side holds a value of its own).
+struct Wrap {
+  int per[3] = {0, 0, 0};
+};
+
+// The in-plane element offset of column (i, j), both in [-2, n + 1], with the
+// top bit set when its ghosts keep their place (an offset is below 2^29).
+__device__ __forceinline__ unsigned wrap_column(const Layout& L, const Wrap& w, int i, int j) {
+  const bool gi = i < 0 || i >= L.ni, gj = j < 0 || j >= L.nj;
+  const bool own = (gi && !w.per[0]) || (gj && !w.per[1]);
+  if (gi && !own) i += i < 0 ? w.per[0] : -w.per[0];
+  if (gj && !own) j += j < 0 ? w.per[1] : -w.per[1];
+  return (unsigned)(L.o + i + (long long)j * L.sj) | (own ? 0x80000000u : 0u);
+}
+
+// Plane k in [-2, n + 1] of the columns: element offset of the base plane and
+// what columns that keep their place and columns that wrap add to it (both
+// planes of a wrapped one are reached by 32-bit offsets from the lower).
+struct PlaneRef {
+  long long base;
+  unsigned own, in;
+};
+__device__ __forceinline__ PlaneRef wrap_plane(const Layout& L, const Wrap& w, int k) {
+  const unsigned p = (unsigned)((long long)w.per[2] * L.sk);
+  const bool hi = k >= L.nk;
+  return {(long long)(hi ? k - w.per[2] : k) * L.sk, hi ? p : 0, k < 0 ? p : 0};
+}
+__device__ __forceinline__ unsigned wrap_offset(unsigned col, const PlaneRef& p) {
+  return (col & 0x7fffffffu) + ((int)col < 0 ? p.own : p.in);
+}
+
 // Global accesses use a uniform (scalar) base per field plus a 32-bit
 // per-thread byte offset, so that each access needs one VGPR for its address.
 template <class X>
