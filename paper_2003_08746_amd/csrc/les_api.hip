@@ -146,15 +146,15 @@ static hipError_t bc_fill(les_ctx* c, double* Q) {
     hipError_t e = les::launch_axis_avg(c->s, c->L, Q);
     if (e != hipSuccess) return e;
   }
-  return les::launch_ghost_fill(c->s, c->L, c->bc, Q, Q, faces_of(c));
+  return les::launch_ghost_fill(c->s, c->L, c->bc, les::Wrap{}, Q, Q, faces_of(c));
 }
 
 // Dynamic SGS coefficients of the state about to be differenced (its
 // ghosts filled), when the context uses the dynamic closure.
-static hipError_t dyn_update(les_ctx* c, const double* Q64, const float* Q32) {
+static hipError_t dyn_update(les_ctx* c, const double* Q64, const float* Q32, const les::Wrap& wrap = les::Wrap{}) {
   if (c->P.sgs != 2) return hipSuccess;
-  return Q32 ? les::launch_dynamic_f32(c->s, c->L, c->mach, c->bc, c->P, c->M, Q32, c->dynw, c->dyn)
-             : les::launch_dynamic(c->s, c->L, c->mach, c->bc, c->P, c->M, Q64, c->dynw, c->dyn);
+  return Q32 ? les::launch_dynamic_f32(c->s, c->L, c->mach, wrap, c->bc, c->P, c->M, Q32, c->dynw, c->dyn)
+             : les::launch_dynamic(c->s, c->L, c->mach, wrap, c->bc, c->P, c->M, Q64, c->dynw, c->dyn);
 }
 
 // Resolve recorded event pairs into the running total (synchronises).
@@ -502,6 +502,34 @@ int les_set_forcing(les_ctx* ctx, const double* f, int i_f) {
   return LES_OK;
 }
 
+// The periodic directions whose ghosts a step's kernels read at their source
+// instead of a copy.  All of them, on the fused path, while a wrapped plane
+// lies within a 32-bit byte offset of its ghost (nk + 8 planes below 2^29
+// elements); the reference kernels and larger blocks take filled ghosts, and
+// so do blocks that are not periodic in k, whose frozen k-ghost planes hold
+// i-ghosts of their own.
+// The fills saved cost more than their bytes: a launch each, and i-ghosts are
+// 16-byte pieces of rows.  One 32^3 step 163 to 145 us, four mixed steps on
+// 75 x 61 x 47 599 to 510, four on 256 x 128 x 128 5.70 to 5.53 ms (mixed
+// 5.15 to 4.92), two on the 256 x 128 x 361 O-grid 7.94 to 7.69.
+static les::Wrap step_wrap(const les_ctx* c) {
+  les::Wrap w;
+  const int n[3] = {c->L.ni, c->L.nj, c->L.nk};
+  if (c->use_ref || c->bc[2] == 1 || (c->L.nk + 8) * c->L.sk >= 1LL << 29) return w;
+  for (int d = 0; d < 3; ++d) w.per[d] = c->bc[d] == 0 ? n[d] : (c->bc[d] == 2 ? n[d] - 1 : 0);
+  return w;
+}
+
+// Has the fill of a stage input with `wrap` anything to do?  Periodic ghosts
+// unless wrapped, face rules and the polar axis, and frozen ghosts unless the
+// buffer holds them.
+static bool needs_fill(const les_ctx* c, const les::Wrap& w, bool held) {
+  if (c->axis || faces_of(c).any) return true;
+  for (int d = 0; d < 3; ++d)
+    if (!w.per[d] && (c->bc[d] != 1 || !held)) return true;
+  return false;
+}
+
 // One Runge-Kutta step on the context's stream: ghost fill of Q^n, five
 // stages (time step read from dtp on the device when not null, else dt),
 // norm reduction of R(Q^n).  cpart (or null): the last stage also reduces
@@ -516,20 +544,33 @@ int les_set_forcing(les_ctx* ctx, const double* f, int i_f) {
 // copy of Q^{n+1} (to Sf[par]); shadow_in: stage 1 reads that copy (written
 // by the step before, with the other par) for its stencil instead of
 // converting the FP64 Q^n as it loads it -- the same FP32 values.
+//
+// wrap: periodic ghosts that the stages read at their source (see step_wrap).
+//
+// held: bit b is set once stage buffer b (S or Sf) holds the frozen ghosts of
+// Q; nothing but the ghost fill writes ghosts, so within one call they are
+// copied once a buffer.
 static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, double* stage_ckpt, double* cpart,
-                     bool with_norms = true, int par = 0, bool shadow_in = false, bool shadow_out = false) {
+                     const les::Wrap& wrap, unsigned& held, bool with_norms = true, int par = 0, bool shadow_in = false,
+                     bool shadow_out = false) {
   les::Layout& L = ctx->L;
   const size_t fe = (size_t)L.fe;
   const double* f = ctx->i_f >= 0 ? ctx->f : nullptr;
   const double cnt = (double)L.ni * L.nj * L.nk;
   if (ctx->prec == LES_MIXED) {
-    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
+    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach, wrap};
     for (int l = 0; l < 5; ++l) {
       const float* in32 = (l == 0 && !shadow_in) ? nullptr : ctx->Sf[(l + 1 + par) & 1];
       float* out32 = (l < 4 || shadow_out) ? ctx->Sf[(l + par) & 1] : nullptr;
       if (l > 0 && ctx->axis) HIPCHK(ctx, les::launch_axis_avg_f32(ctx->s, L, (float*)in32));
-      if (in32) HIPCHK(ctx, les::launch_ghost_fill_f32(ctx->s, L, ctx->bc, (float*)in32, Q, faces_of(ctx)));
-      HIPCHK(ctx, dyn_update(ctx, in32 ? nullptr : Q, in32));
+      if (in32) {
+        const unsigned bit = 1u << ((l + 1 + par) & 1);
+        if (needs_fill(ctx, wrap, held & bit))
+          HIPCHK(ctx, les::launch_ghost_fill_f32(ctx->s, L, ctx->bc, wrap, (float*)in32, held & bit ? nullptr : Q,
+                                                 faces_of(ctx)));
+        held |= bit;
+      }
+      HIPCHK(ctx, dyn_update(ctx, in32 ? nullptr : Q, in32, wrap));
       int trc = timing_begin(ctx);
       if (trc != LES_OK) return trc;
       HIPCHK(ctx, les::launch_stage_mixed(ctx->s, a, in32 ? nullptr : Q, in32, Q, l == 4 ? Q : nullptr, out32, dtp,
@@ -548,18 +589,24 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
     for (int l = 0; l < 5; ++l) {
       double* out = l == 4 ? Q : (stage_ckpt ? stage_ckpt + (size_t)(l + 1) * 5 * fe : ctx->S[l & 1]);
       if (l > 0 && ctx->axis) HIPCHK(ctx, les::launch_axis_avg(ctx->s, L, (double*)in));
-      if (l > 0 || stage_ckpt) HIPCHK(ctx, les::launch_ghost_fill(ctx->s, L, ctx->bc, (double*)in, Q, faces_of(ctx)));
+      if (l > 0 || stage_ckpt) {
+        const unsigned bit = l > 0 && !stage_ckpt ? 1u << ((l - 1) & 1) : 0;
+        if (needs_fill(ctx, wrap, held & bit))
+          HIPCHK(ctx, les::launch_ghost_fill(ctx->s, L, ctx->bc, wrap, (double*)in, held & bit ? nullptr : Q,
+                                             faces_of(ctx)));
+        held |= bit;
+      }
       // the residual norms of R(Q^n) are reduced on the device (fused into
       // stage 1) whenever with_norms; only their copy to the host is optional
       double* part = (l == 0 && with_norms) ? ctx->part : nullptr;
-      HIPCHK(ctx, dyn_update(ctx, in, nullptr));
+      HIPCHK(ctx, dyn_update(ctx, in, nullptr, wrap));
       int trc = timing_begin(ctx);
       if (trc != LES_OK) return trc;
       if (ctx->use_ref) {
         HIPCHK(ctx, les::launch_stage_ref(ctx->s, L, ctx->P, ctx->M, in, Q, out, dtp, dt, les::rk_alpha(l), f,
                                           ctx->i_f, part, ctx->dyn, ctx->axis));
       } else {
-        les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
+        les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach, wrap};
         HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, in, Q, out, dtp, dt, les::rk_alpha(l), part,
                                            l == 4 ? cpart : nullptr));
       }
@@ -588,7 +635,9 @@ int les_rk_step(les_ctx* ctx, double* Q, double dt, double* dt_out, double* norm
     HIPCHK(ctx, les::launch_cfl(ctx->s, L, ctx->P, ctx->M, Q, ctx->part, ctx->scal, ctx->flag, nullptr, ctx->axis));
     dtp = ctx->scal;
   }
-  int rc = step_core(ctx, Q, dtp, dt, stage_ckpt, nullptr);
+  unsigned held = 0;
+  // (checkpoints keep filled ghosts: the adjoint reads them)
+  int rc = step_core(ctx, Q, dtp, dt, stage_ckpt, nullptr, stage_ckpt ? les::Wrap{} : step_wrap(ctx), held);
   if (rc != LES_OK) return rc;
   if (!dt_out && !norms) return LES_OK;
   rc = sync_outputs(ctx, dt_out, norms);
@@ -616,13 +665,19 @@ int les_advance(les_ctx* ctx, double* Q, int nsteps, double* dt_out, double* nor
   // frozen values (no face rules, polar axis or dynamic closure, which would
   // then work on FP32 values): the same stencil values, one FP64 read less.
   const bool shadow = ctx->prec == LES_MIXED && !ctx->axis && ctx->P.sgs != 2 && !faces_of(ctx).any;
+  const les::Wrap wrap = step_wrap(ctx);
+  unsigned held = 0;
   for (int n = 0; n < nsteps; ++n) {
     double* dtp = ctx->scal + ((n & 1) ? 12 : 0);
     double* dnext = ctx->scal + ((n & 1) ? 0 : 12);
     const bool more = n + 1 < nsteps;
-    if (n > 0) HIPCHK(ctx, bc_fill(ctx, Q));
-    int rc = step_core(ctx, Q, dtp, 0.0, nullptr, (more && !ctx->use_ref) ? ctx->cpart : nullptr, !more, n & 1,
-                       shadow && n > 0, shadow && more);
+    // (the last step's fill also leaves Q's ghosts filled on return)
+    if (n > 0 && !more)
+      HIPCHK(ctx, bc_fill(ctx, Q));
+    else if (n > 0 && needs_fill(ctx, wrap, true))
+      HIPCHK(ctx, les::launch_ghost_fill(ctx->s, L, ctx->bc, wrap, Q, nullptr, faces_of(ctx)));
+    int rc = step_core(ctx, Q, dtp, 0.0, nullptr, (more && !ctx->use_ref) ? ctx->cpart : nullptr, wrap, held,
+                       !more, n & 1, shadow && n > 0, shadow && more);
     if (rc != LES_OK) return rc;
     if (!more) break;
     double* rec = dt_out ? ctx->dthist + n + 1 : nullptr;
@@ -762,7 +817,7 @@ int les_debug_dynamic_coefficients(les_ctx* ctx, double* Q, double* out) {
   if (!ctx) return LES_ERR_ARG;
   if (!Q || !out) return fail(ctx, LES_ERR_ARG, "les_debug_dynamic_coefficients: null pointer");
   if (ctx->P.sgs != 2) return fail(ctx, LES_ERR_STATE, "les_debug_dynamic_coefficients: sgs is not 2");
-  HIPCHK(ctx, les::launch_ghost_fill(ctx->s, ctx->L, ctx->bc, Q, Q, faces_of(ctx)));
+  HIPCHK(ctx, les::launch_ghost_fill(ctx->s, ctx->L, ctx->bc, les::Wrap{}, Q, Q, faces_of(ctx)));
   HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
   HIPCHK(ctx, hipMemcpyAsync(out, ctx->dyn, 2 * les::dyn_ncol(ctx->L) * sizeof(double), hipMemcpyDeviceToDevice,
                              ctx->s));

@@ -176,8 +176,8 @@ __device__ inline void ghost_source(const int nn[3], const int bc[3], const int 
 // block, with one power a ghost instead of two).
 // ---------------------------------------------------------------------------
 template <class T>
-__global__ void __launch_bounds__(256) k_ghost_fill(Layout L, int bc0, int bc1, int bc2, T* q, const double* frozen,
-                                                    Faces F) {
+__global__ void __launch_bounds__(256) k_ghost_fill(Layout L, int bc0, int bc1, int bc2, bool wrapped, T* q,
+                                                    const double* frozen, Faces F) {
   const unsigned PI = L.ni + 4, PJ = L.nj + 4;
   const unsigned cA = 4 * PJ * PI, cB = (unsigned)L.nk * 4 * PI, cC = (unsigned)L.nk * L.nj * 4;
   unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -216,6 +216,7 @@ __global__ void __launch_bounds__(256) k_ghost_fill(Layout L, int bc0, int bc1, 
 #pragma unroll
     for (int f = 0; f < 5; ++f) v[f] = (T)frozen[f * L.fe + dst];
   } else {
+    if (wrapped && !(bc1 == 3 && j < 0)) return;
     const long long src = L.at(w[0], w[1], w[2]);
 #pragma unroll
     for (int f = 0; f < 5; ++f) v[f] = q[f * L.fe + src];
@@ -734,19 +735,22 @@ hipError_t launch_metrics_export(hipStream_t s, const Layout& L, const double* M
   return hipGetLastError();
 }
 
+// (a step wraps all periodic directions or none)
+static bool wraps(const Wrap& w) { return w.per[0] || w.per[1] || w.per[2]; }
+
 long long ghost_count(const Layout& L) {
   return 4LL * (L.nj + 4) * (L.ni + 4) + (long long)L.nk * 4 * (L.ni + 4) + (long long)L.nk * L.nj * 4;
 }
 
-hipError_t launch_ghost_fill(hipStream_t s, const Layout& L, const int bc[3], double* q, const double* frozen,
-                             const Faces& F) {
-  k_ghost_fill<double><<<nblk(ghost_count(L), 256), 256, 0, s>>>(L, bc[0], bc[1], bc[2], q, frozen, F);
+hipError_t launch_ghost_fill(hipStream_t s, const Layout& L, const int bc[3], const Wrap& wrap, double* q,
+                             const double* frozen, const Faces& F) {
+  k_ghost_fill<double><<<nblk(ghost_count(L), 256), 256, 0, s>>>(L, bc[0], bc[1], bc[2], wraps(wrap), q, frozen, F);
   return hipGetLastError();
 }
 
-hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3], float* q, const double* frozen,
-                                 const Faces& F) {
-  k_ghost_fill<float><<<nblk(ghost_count(L), 256), 256, 0, s>>>(L, bc[0], bc[1], bc[2], q, frozen, F);
+hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3], const Wrap& wrap, float* q,
+                                 const double* frozen, const Faces& F) {
+  k_ghost_fill<float><<<nblk(ghost_count(L), 256), 256, 0, s>>>(L, bc[0], bc[1], bc[2], wraps(wrap), q, frozen, F);
   return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 #pragma once
 #include "les_common.hpp"
 #include "les_faces.hpp"
+#include "les_tile.hpp"
 
 namespace les {
 
@@ -10,10 +11,11 @@ hipError_t launch_metrics(hipStream_t s, const Layout& L, const int bc[3], const
 hipError_t launch_metrics_copy(hipStream_t s, const Layout& L, const double* src, double* M);
 hipError_t launch_metrics_export(hipStream_t s, const Layout& L, const double* M, double* dst);
 long long ghost_count(const Layout& L);
-hipError_t launch_ghost_fill(hipStream_t s, const Layout& L, const int bc[3], double* q, const double* frozen,
-                             const Faces& F);
-hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3], float* q, const double* frozen,
-                                 const Faces& F);
+// (ghosts of a direction with wrap.per are left to the reader)
+hipError_t launch_ghost_fill(hipStream_t s, const Layout& L, const int bc[3], const Wrap& wrap, double* q,
+                             const double* frozen, const Faces& F);
+hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3], const Wrap& wrap, float* q,
+                                 const double* frozen, const Faces& F);
 // acc[12][nj][ni] += sums over k of the primitives and their second moments
 hipError_t launch_stats(hipStream_t s, const Layout& L, const Phys& P, int nks, const double* Q, double* acc);
 hipError_t launch_stats_profiles(hipStream_t s, const Layout& L, const double* acc, double samples, double core_u,
