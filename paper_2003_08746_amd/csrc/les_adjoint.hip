@@ -73,7 +73,7 @@ struct AdjK {
   int per[3];          // period of each axis: n (periodic), n - 1 (superposed), 0 (Dirichlet)
   int lo[3], hi[3];    // output box: ghost layers of periodic axes and of active faces included
   Faces F;             // boundary faces
-  int general;         // a superposed axis, the polar axis or an active face: the fold visits every interior node
+  int nband[3], band[3][4];  // coordinates of the interior nodes that have images along each axis, ascending
   int axis;            // j = 0 is the polar axis (bc1 == 3)
   Machine mach;
 };
@@ -87,7 +87,6 @@ AdjK make_adjk(const AdjArgs& a) {
   A.bc1 = a.bc1;
   A.bc2 = a.bc2;
   A.F = a.F;
-  A.general = 0;
   A.axis = a.axis;
   A.mach = a.mach;
   const int bc[3] = {a.bc0, a.bc1, a.bc2}, nn[3] = {a.L.ni, a.L.nj, a.L.nk};
@@ -101,7 +100,14 @@ AdjK make_adjk(const AdjArgs& a) {
     const bool fhi = (bc[d] == 1 || bc[d] == 3) && a.F.type[2 * d + 1] != 0;
     A.lo[d] = (per_like_lo || flo) ? -2 : 0;
     A.hi[d] = (per_like_hi || fhi) ? nn[d] + 1 : nn[d] - 1;
-    if (bc[d] == 2 || bc[d] == 3 || flo || fhi) A.general = 1;
+    const int p = A.per[d], n = nn[d];
+    A.nband[d] = 0;
+    for (int x = 0; x < n; ++x) {
+      if (x == 4 && n > 8) x = n - 4;  // (images lie within two nodes of a side)
+      const bool in = p ? (x + p >= n && x + p <= n + 1) || (x - p >= -2 && x - p <= -1)
+                        : (x == 0 && flo) || (x == n - 1 && fhi) || (bc[d] == 3 && (x == 1 || x == 2));
+      if (in) A.band[d][A.nband[d]++] = x;
+    }
   }
   return A;
 }
@@ -513,15 +519,6 @@ __device__ __forceinline__ bool has_images(const AdjK& A, int i, int j, int k) {
     }
   }
   return false;
-}
-
-// Last step at an interior node whose adjoint q is complete: in the
-// Runge-Kutta reverse, fbar[c][k][j] += fw q_c on the source plane (fbar
-// non-null, on_f).
-__device__ __forceinline__ void finish_node(const Layout& L, int j, int k, const double q[5], double* __restrict__ fbar,
-                                            bool on_f, double fw, int c0 = 0, int c1 = 5) {
-  if (fbar && on_f)
-    for (int c = c0; c < c1; ++c) fbar[((long long)c * L.nk + k) * L.nj + j] += fw * q[c];
 }
 
 // ---------------------------------------------------------------------------
@@ -1003,235 +1000,158 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 }
 
 // ---------------------------------------------------------------------------
-// Fold: add the periodic ghost images' adjoints to their interior nodes:
-// qout(n) += W_GG over the images of n (at x + n_d for x <= 1 and at x - n_d
-// for x >= n_d - 2 along each periodic axis, all combinations, in a fixed
-// order).  Only nodes in the band {x <= 1 or x >= n_d - 2} of some periodic
-// axis have images; threads enumerate the band as three disjoint slabs
-// (band of k; core of k x band of j; core of k and j x band of i; the core
-// of an axis is [2, n_d - 2), all of [0, n_d) along a non-periodic axis).
+// Face ghosts: the adjoint Gbar of each ghost G = face_value(q_r) of an active
+// face (both layers, and their periodic images) becomes its pull-back to the
+// boundary node, (dG/dq_r)^T Gbar, in place (W_GG).  Ghosts of two Dirichlet
+// directions are frozen and carry nothing.  One thread per ghost, all five
+// columns of the Jacobian from one evaluation of the rule; the fold then adds
+// face ghosts as it adds periodic images.  (One thread per boundary node and
+// column, which evaluated the rule for each image in turn, took 41 us on the
+// 128 x 64 x 121 O-grid with a far-field face; this takes 12.)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int band_coord(unsigned u, int n) { return n <= 4 ? (int)u : (u < 2 ? (int)u : n - 4 + (int)u); }
+// ghosts of face f = 2 d + hi: two layers, and the other two directions with
+// the ghosts of periodic ones
+__host__ __device__ inline int face_extent(const AdjK& A, int e) {
+  return A.per[e] ? (e == 0 ? A.L.ni : (e == 1 ? A.L.nj : A.L.nk)) + 4 : (e == 0 ? A.L.ni : (e == 1 ? A.L.nj : A.L.nk));
+}
+inline long long face_ghosts(const AdjK& A) {
+  long long n = 0;
+  for (int f = 0; f < 6; ++f)
+    if (A.F.type[f] != 0) n += 2LL * face_extent(A, (f / 2 + 1) % 3) * face_extent(A, (f / 2 + 2) % 3);
+  return n;
+}
+
+__global__ void __launch_bounds__(64) k_adj_face(AdjK A, const double* __restrict__ Q, double* __restrict__ G,
+                                                 unsigned total) {
+  const Layout& L = A.L;
+  unsigned x = blockIdx.x * 64 + threadIdx.x;
+  if (x >= total) return;
+  const int nn[3] = {L.ni, L.nj, L.nk};
+  int d = 0, hi = 0;
+  unsigned m1 = 1, m2 = 1;  // extents of the other directions
+  for (int f = 0; f < 6; ++f) {
+    if (A.F.type[f] == 0) continue;
+    d = f / 2;
+    hi = f & 1;
+    m1 = face_extent(A, (d + 1) % 3);
+    m2 = face_extent(A, (d + 2) % 3);
+    if (x < 2 * m1 * m2) break;
+    x -= 2 * m1 * m2;
+  }
+  const unsigned row = x / m1, layer = row / m2;
+  int g[3], r[3];  // the ghost and its boundary node
+  const int u[2] = {(int)(x - row * m1), (int)(row - layer * m2)};
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    if (e == d) {
+      g[e] = hi ? nn[e] + (int)layer : -1 - (int)layer;
+      r[e] = hi ? nn[e] - 1 : 0;
+    } else {
+      const int p = A.per[e], y = u[e == (d + 1) % 3 ? 0 : 1] - (p ? 2 : 0);
+      g[e] = y;
+      r[e] = p && y < 0 ? y + p : (p && y >= nn[e] ? y - p : y);
+    }
+  }
+  const long long fe = L.fe, ng = L.at(g[0], g[1], g[2]), nr = L.at(r[0], r[1], r[2]);
+  double gb[5], qo[5] = {0, 0, 0, 0, 0}, nv[3];
+  Dual5 qr[5], out[5];
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {
+    gb[c] = G[c * fe + ng];
+    qr[c].v = Q[c * fe + nr];
+    qr[c].d[c] = 1.0;
+    if (A.F.outside) qo[c] = A.F.outside[c * fe + ng];
+  }
+  face_normal(L, A.F, d, hi, r[0], r[1], r[2], nv);
+  face_value<Dual5>(A.F.type[2 * d + hi], A.F.gamma, A.F.p_exit[2 * d + hi], nv, qr, qo, out);
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {  // column c of the Jacobian
+    double dot = 0.0;
+#pragma unroll
+    for (int m = 0; m < 5; ++m) dot += out[m].d[c] * gb[m];
+    G[c * fe + ng] = dot;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Fold: every interior node with ghost images adds their adjoints (W_GG), in a
+// fixed order: periodic images (x +- period along each periodic axis, all
+// combinations), the face ghosts pulled back to it, and the images across
+// the polar axis.  Only nodes with a coordinate in the band of some axis have
+// images; threads enumerate them as three disjoint slabs (band of k; core of
+// k x band of j; core of k and j x band of i): 12 us on that O-grid, where a
+// pass over every interior node took 21.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ int core_coord(const AdjK& A, int d, int u) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q)  // (bands are ascending)
+    if (q < A.nband[d] && u >= A.band[d][q]) ++u;
+  return u;
+}
 
 __global__ void __launch_bounds__(256) k_adj_fold(AdjK A, const double* __restrict__ Wk, double* __restrict__ qout,
                                                   double* __restrict__ fbar, int i_f, double fw) {
   const Layout& L = A.L;
   const int nn[3] = {L.ni, L.nj, L.nk};
-  const int bc[3] = {A.bc0, A.bc1, A.bc2};
-  unsigned bs[3], cs[3];  // band and core sizes
-  int c0[3];              // first core coordinate
-  for (int d = 0; d < 3; ++d) {
-    if (bc[d] == 0) {
-      bs[d] = nn[d] < 4 ? nn[d] : 4;
-      cs[d] = nn[d] > 4 ? nn[d] - 4 : 0;
-      c0[d] = 2;
-    } else {
-      bs[d] = 0;
-      cs[d] = nn[d];
-      c0[d] = 0;
-    }
-  }
   const unsigned ni = nn[0], nj = nn[1];
-  const unsigned S2 = bs[2] * nj * ni, S1 = cs[2] * bs[1] * ni, S0 = cs[2] * cs[1] * bs[0];
+  const unsigned b0 = A.nband[0], b1 = A.nband[1], c1 = nj - b1, c2 = nn[2] - A.nband[2];
+  const unsigned S2 = A.nband[2] * nj * ni, S1 = c2 * b1 * ni, S0 = c2 * c1 * b0;
   unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= S2 + S1 + S0) return;
   int i, j, k;
   if (t < S2) {
-    i = (int)(t % ni);
-    j = (int)((t / ni) % nj);
-    k = band_coord(t / (ni * nj), nn[2]);
+    const unsigned row = t / ni, kk = row / nj;
+    i = (int)(t - row * ni);
+    j = (int)(row - kk * nj);
+    k = A.band[2][kk];
   } else if (t < S2 + S1) {
     t -= S2;
-    i = (int)(t % ni);
-    j = band_coord((t / ni) % bs[1], nn[1]);
-    k = c0[2] + (int)(t / (ni * bs[1]));
+    const unsigned row = t / ni, kk = row / b1;
+    i = (int)(t - row * ni);
+    j = A.band[1][row - kk * b1];
+    k = core_coord(A, 2, (int)kk);
   } else {
     t -= S2 + S1;
-    i = band_coord(t % bs[0], nn[0]);
-    j = c0[1] + (int)((t / bs[0]) % cs[1]);
-    k = c0[2] + (int)(t / (bs[0] * cs[1]));
+    const unsigned row = t / b0, kk = row / c1;
+    i = A.band[0][t - row * b0];
+    j = core_coord(A, 1, (int)(row - kk * c1));
+    k = core_coord(A, 2, (int)kk);
   }
-  const int id[3] = {i, j, k};
+  const int id[3] = {i, j, k}, bc[3] = {A.bc0, A.bc1, A.bc2};
   int cand[3][3], nc[3];
-  for (int d = 0; d < 3; ++d) {
-    nc[d] = 0;
-    cand[d][nc[d]++] = id[d];
-    if (bc[d] == 0) {
-      if (id[d] + nn[d] <= nn[d] + 1) cand[d][nc[d]++] = id[d] + nn[d];
-      if (id[d] - nn[d] >= -2) cand[d][nc[d]++] = id[d] - nn[d];
-    }
-  }
-  const long long n0 = L.at(i, j, k);
-  const double* G = Wk + (long long)W_GG * L.fe;
-  double q[5];
-  for (int c = 0; c < 5; ++c) {
-    double s = qout[c * L.fe + n0];
-    for (int a = 0; a < nc[0]; ++a)
-      for (int b = 0; b < nc[1]; ++b)
-        for (int e = 0; e < nc[2]; ++e)
-          if (a | b | e) s += G[c * L.fe + L.at(cand[0][a], cand[1][b], cand[2][e])];
-    qout[c * L.fe + n0] = s;
-    q[c] = s;
-  }
-  finish_node(L, j, k, q, fbar, i == i_f, fw);
-}
-
-// Fold when an axis is superposed or a boundary face is active: every
-// interior node with images adds, in a fixed order, the gathers of its
-// periodic images (period p along each periodic axis) and pulls back those
-// of its face ghosts through the face rule: qbar(r) += (dG/dq_r)^T Gbar for
-// each face ghost G = face_value(q_r) (both layers, and their periodic
-// images), the Jacobian column by column from forward-mode dual numbers.
-// Ghosts of two Dirichlet directions are frozen and carry nothing.
-// Is interior node (i, j, k) the boundary node of an active face (so that
-// its face ghosts depend on it through the face rule)?
-__device__ __forceinline__ bool at_active_face(const AdjK& A, int i, int j, int k) {
-  const int id[3] = {i, j, k}, nn[3] = {A.L.ni, A.L.nj, A.L.nk}, bc[3] = {A.bc0, A.bc1, A.bc2};
-  for (int d = 0; d < 3; ++d) {
-    if (bc[d] == 1 && id[d] == 0 && A.F.type[2 * d] != 0) return true;
-    if ((bc[d] == 1 || bc[d] == 3) && id[d] == nn[d] - 1 && A.F.type[2 * d + 1] != 0) return true;
-  }
-  return false;
-}
-
-// Boundary nodes of the active faces, listed face by face (face f = 2 d +
-// hi, the plane id[d] = 0 or n_d - 1 with the other two indices in row
-// order); a node on several active faces is listed under the first.
-__host__ __device__ inline long long face_plane(const int nn[3], int f) {
-  const int d = f / 2;
-  return (long long)nn[(d + 1) % 3] * nn[(d + 2) % 3];
-}
-inline long long face_node_slots(const AdjK& A) {
-  const int nn[3] = {A.L.ni, A.L.nj, A.L.nk};
-  long long n = 0;
-  for (int f = 0; f < 6; ++f)
-    if (A.F.type[f] != 0) n += face_plane(nn, f);
-  return n;
-}
-// node of slot x of that list, or false when the slot is a repeat
-__device__ inline bool face_node(const AdjK& A, long long x, int id[3]) {
-  const int nn[3] = {A.L.ni, A.L.nj, A.L.nk};
-  for (int f = 0; f < 6; ++f) {
-    if (A.F.type[f] == 0) continue;
-    const long long np = face_plane(nn, f);
-    if (x >= np) {
-      x -= np;
-      continue;
-    }
-    const int d = f / 2, e1 = (d + 1) % 3, e2 = (d + 2) % 3;
-    id[d] = (f & 1) ? nn[d] - 1 : 0;
-    id[e1] = (int)(x % nn[e1]);
-    id[e2] = (int)(x / nn[e1]);
-    for (int g = 0; g < f; ++g) {  // listed under an earlier face?
-      if (A.F.type[g] == 0) continue;
-      const int dg = g / 2;
-      if (id[dg] == ((g & 1) ? nn[dg] - 1 : 0)) return false;
-    }
-    return true;
-  }
-  return false;
-}
-
-// FACES = false: the nodes with images that are not at an active face (no
-// face-rule Jacobian, so the kernel stays light), one thread per node;
-// FACES = true: the boundary nodes of the active faces, one thread per
-// (component, listed node), each taking one column of the face rule's
-// Jacobian.  Together they visit each node with images once; each
-// component's sum is formed in the same order either way.
-template <bool FACES>
-__global__ void __launch_bounds__(256) k_adj_fold_general(AdjK A, const double* __restrict__ Q,
-                                                          const double* __restrict__ Wk, double* __restrict__ qout,
-                                                          double* __restrict__ fbar, int i_f, double fw,
-                                                          long long slots) {
-  const Layout& L = A.L;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  int c0 = 0, c1 = 5, i, j, k;
-  if (FACES) {
-    if (t >= 5 * slots) return;
-    c0 = (int)(t / slots);
-    c1 = c0 + 1;
-    int id3[3];
-    if (!face_node(A, t % slots, id3)) return;
-    i = id3[0];
-    j = id3[1];
-    k = id3[2];
-  } else {
-    const unsigned ni = L.ni, nij = (unsigned)L.ni * L.nj;
-    if (t >= (long long)nij * L.nk) return;
-    i = (int)(t % ni);
-    j = (int)((t % nij) / ni);
-    k = (int)(t / nij);
-    if (!has_images(A, i, j, k) || at_active_face(A, i, j, k)) return;
-  }
-  const int id[3] = {i, j, k}, nn[3] = {L.ni, L.nj, L.nk}, bc[3] = {A.bc0, A.bc1, A.bc2};
-  int cand[3][3], kind[3][3], nc[3];  // kind: 0 own / periodic image, 1 lo-face ghost, 2 hi-face ghost
+  bool face[3];  // the images along d are face ghosts
   for (int d = 0; d < 3; ++d) {
     nc[d] = 1;
     cand[d][0] = id[d];
-    kind[d][0] = 0;
+    face[d] = false;
     const int p = A.per[d];
     if (p) {
-      if (id[d] + p >= nn[d] && id[d] + p <= nn[d] + 1) {
-        cand[d][nc[d]] = id[d] + p;
-        kind[d][nc[d]++] = 0;
-      }
-      if (id[d] - p <= -1 && id[d] - p >= -2) {
-        cand[d][nc[d]] = id[d] - p;
-        kind[d][nc[d]++] = 0;
-      }
-    } else if (bc[d] == 1 || bc[d] == 3) {
-      if (id[d] == 0 && bc[d] == 1 && A.F.type[2 * d] != 0) {
-        cand[d][nc[d]] = -1;
-        kind[d][nc[d]++] = 1;
-        cand[d][nc[d]] = -2;
-        kind[d][nc[d]++] = 1;
-      } else if (id[d] == nn[d] - 1 && A.F.type[2 * d + 1] != 0) {
-        cand[d][nc[d]] = nn[d];
-        kind[d][nc[d]++] = 2;
-        cand[d][nc[d]] = nn[d] + 1;
-        kind[d][nc[d]++] = 2;
-      }
+      if (id[d] + p >= nn[d] && id[d] + p <= nn[d] + 1) cand[d][nc[d]++] = id[d] + p;
+      if (id[d] - p <= -1 && id[d] - p >= -2) cand[d][nc[d]++] = id[d] - p;
+    } else if (id[d] == 0 && bc[d] == 1 && A.F.type[2 * d] != 0) {
+      cand[d][1] = -1;
+      cand[d][2] = -2;
+      nc[d] = 3;
+      face[d] = true;
+    } else if (id[d] == nn[d] - 1 && (bc[d] == 1 || bc[d] == 3) && A.F.type[2 * d + 1] != 0) {
+      cand[d][1] = nn[d];
+      cand[d][2] = nn[d] + 1;
+      nc[d] = 3;
+      face[d] = true;
     }
   }
   const long long fe = L.fe, n0 = L.at(i, j, k);
   const double* G = Wk + (long long)W_GG * fe;
-  double s[5], qr[5];
-  for (int c = c0; c < c1; ++c) s[c] = qout[c * fe + n0];
-  if (FACES)
-    for (int c = 0; c < 5; ++c) qr[c] = Q[c * fe + n0];
+  double s[5];
+  for (int c = 0; c < 5; ++c) s[c] = qout[c * fe + n0];
   for (int a = 0; a < nc[0]; ++a)
     for (int b = 0; b < nc[1]; ++b)
       for (int e = 0; e < nc[2]; ++e) {
         if (!(a | b | e)) continue;
-        const int kd[3] = {kind[0][a], kind[1][b], kind[2][e]};
-        const int nface = (kd[0] != 0) + (kd[1] != 0) + (kd[2] != 0);
+        const int nface = (a && face[0]) + (b && face[1]) + (e && face[2]);
         if (nface > 1) continue;  // edge ghost: frozen
         const long long g = L.at(cand[0][a], cand[1][b], cand[2][e]);
-        if (nface == 0) {
-          for (int c = c0; c < c1; ++c) s[c] += G[c * fe + g];
-          continue;
-        }
-        if (!FACES) continue;  // (not reached: face ghosts exist at active faces only)
-        double gb[5];
-        for (int c = 0; c < 5; ++c) gb[c] = G[c * fe + g];
-        const int d = kd[0] ? 0 : (kd[1] ? 1 : 2), hi = kd[d] == 2;
-        const int type = A.F.type[2 * d + hi];
-        double nv[3], qo[5] = {0, 0, 0, 0, 0};
-        {
-          int r[3] = {i, j, k};
-          r[d] = hi ? nn[d] - 1 : 0;
-          face_normal(L, A.F, d, hi, r[0], r[1], r[2], nv);
-        }
-        if (A.F.outside)
-          for (int c = 0; c < 5; ++c) qo[c] = A.F.outside[c * fe + g];
-        for (int c = c0; c < c1; ++c) {  // column c of the face rule's Jacobian
-          DualD qd[5], od[5];
-          for (int m = 0; m < 5; ++m) qd[m] = DualD(qr[m], m == c ? 1.0 : 0.0);
-          face_value<DualD>(type, A.F.gamma, A.F.p_exit[2 * d + hi], nv, qd, qo, od);
-          double dot = 0.0;
-          for (int m = 0; m < 5; ++m) dot += od[m].d * gb[m];
-          s[c] += dot;
-        }
+        for (int c = 0; c < 5; ++c) s[c] += G[c * fe + g];
       }
   if (A.axis && (j == 1 || j == 2)) {
     // ghosts (i', -j, k') across the polar axis copy node (w(i'), j,
@@ -1245,39 +1165,50 @@ __global__ void __launch_bounds__(256) k_adj_fold_general(AdjK A, const double* 
     const int t0 = ((k - half) % p + p) % p;
     const int kks[6] = {-2, -1, t0, t0 + p, L.nk, L.nk + 1};
     for (int a = 0; a < nc[0]; ++a) {
-      if (kind[0][a] != 0) continue;
+      if (a && face[0]) continue;
       for (int q = 0; q < 6; ++q) {
         const int kk = kks[q];
         if (q == 3 && kk >= L.nk) continue;  // t0 + p lies in [0, nk) only for t0 = 0
         const int w2 = (kk >= 0 && kk < L.nk) ? kk : (kk + p) % p;
         if ((w2 + half) % p != k) continue;
         const long long g = L.at(cand[0][a], -j, kk);
-        for (int c = c0; c < c1; ++c) s[c] += G[c * fe + g];
+        for (int c = 0; c < 5; ++c) s[c] += G[c * fe + g];
       }
     }
   }
-  for (int c = c0; c < c1; ++c) qout[c * fe + n0] = s[c];
-  finish_node(L, j, k, s, fbar, i == i_f, fw, c0, c1);
+  for (int c = 0; c < 5; ++c) qout[c * fe + n0] = s[c];
+  if (fbar && i == i_f)
+    for (int c = 0; c < 5; ++c) fbar[((long long)c * L.nk + k) * L.nj + j] += fw * s[c];
 }
 
-// Reverse of the centerline condition, one wave per (i, variable): the
-// forward writes the mean of the ring (i, 1, k'), k' = 0 .. nk - 2, to every
-// axis node (i, 0, k), k = 0 .. nk - 1; so every ring node receives the sum
-// of the axis adjoints over k divided by nk - 1, and the axis adjoints are
-// consumed (set to 0).  Lane l sums k = l, l + 64, ... ascending, and the
-// partial sums are added by a fixed shuffle tree.
-__global__ void __launch_bounds__(64) k_axis_avg_adj(Layout L, double* __restrict__ q) {
-  const int f = blockIdx.x / L.ni, i = blockIdx.x % L.ni;
+// Reverse of the centerline condition: the forward writes the mean of the ring
+// (i, 1, k'), k' = 0 .. nk - 2, to every axis node (i, 0, k), k = 0 .. nk - 1;
+// so every ring node receives the sum of the axis adjoints over k divided by
+// nk - 1, and the axis adjoints are consumed (set to 0).  Per (i, variable)
+// lane l sums k = l, l + 64, ... ascending, and the partial sums are added by
+// a fixed shuffle tree; blocks of 16 i x 64 lanes read and write row segments
+// of 16 nodes (128 x 64 x 121: 5.8 us, one i a block 7.5).
+__global__ void __launch_bounds__(1024) k_axis_avg_adj(Layout L, double* __restrict__ q) {
+  __shared__ double part[64][17], mean[16];
+  const int ni16 = (L.ni + 15) / 16;
+  const int f = blockIdx.x / ni16, ii = threadIdx.x % 16, l = threadIdx.x / 16;
+  const int i = blockIdx.x % ni16 * 16 + ii;
   double* a = q + f * L.fe;
   double sum = 0.0;
-  for (int k = threadIdx.x; k < L.nk; k += 64) {
-    const long long n = L.at(i, 0, k);
-    sum += a[n];
-    a[n] = 0.0;
-  }
-  sum = __shfl(wave_sum(sum), 0, 64);
-  const double share = sum / (double)(L.nk - 1);
-  for (int k = threadIdx.x; k < L.nk - 1; k += 64) a[L.at(i, 1, k)] += share;
+  if (i < L.ni)
+    for (int k = l; k < L.nk; k += 64) {
+      const long long n = L.at(i, 0, k);
+      sum += a[n];
+      a[n] = 0.0;
+    }
+  part[l][ii] = sum;
+  __syncthreads();
+  sum = wave_sum(part[threadIdx.x % 64][threadIdx.x / 64]);
+  if (threadIdx.x % 64 == 0) mean[threadIdx.x / 64] = sum / (double)(L.nk - 1);
+  __syncthreads();
+  const double share = mean[ii];
+  if (i < L.ni)
+    for (int k = l; k < L.nk - 1; k += 64) a[L.at(i, 1, k)] += share;
 }
 
 // fbar[c][k][j] += w q_c on the source plane i_f (interior nodes).
@@ -1314,22 +1245,14 @@ __global__ void __launch_bounds__(256) k_adj_sum(Layout L, Terms z) {
 
 inline unsigned nb(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// qout = (dR/dQ|Q)^T (coef * qb) on the interior; fbar: see finish_node.
+// qout = (dR/dQ|Q)^T (coef * qb) on the interior; in the Runge-Kutta
+// reverse, fbar[c][k][j] += fw qout_c on the source plane i_f (fbar non-null).
 hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const double* qb, double coef, double* Wk,
                         double* qout, double* fbar = nullptr, int i_f = -1, double fw = 0.0) {
   const Layout& L = A.L;
-  const long long nIn = (long long)L.ni * L.nj * L.nk;
-  long long nBand = 0;
-  {
-    const long long nn[3] = {L.ni, L.nj, L.nk};
-    const int bc[3] = {A.bc0, A.bc1, A.bc2};
-    long long bs[3], cs[3];
-    for (int d = 0; d < 3; ++d) {
-      bs[d] = bc[d] == 0 ? (nn[d] < 4 ? nn[d] : 4) : 0;
-      cs[d] = bc[d] == 0 ? (nn[d] > 4 ? nn[d] - 4 : 0) : nn[d];
-    }
-    nBand = bs[2] * nn[1] * nn[0] + cs[2] * bs[1] * nn[0] + cs[2] * cs[1] * bs[0];
-  }
+  // nodes with ghost images (see k_adj_fold)
+  const long long c1 = L.nj - A.nband[1], c2 = L.nk - A.nband[2];
+  const long long nBand = ((long long)A.nband[2] * L.nj + c2 * A.nband[1]) * L.ni + c2 * c1 * A.nband[0];
   // blocks over tiles of tx x ty output nodes, whose first column lies `lead`
   // before the output box
   auto tiles = [&](int tx, int ty, int lead) {
@@ -1351,13 +1274,9 @@ hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const dou
     k_adj_diss<true><<<td.t.per_xcd * td.t.nxcd, NT, 0, s>>>(td);
   else
     k_adj_diss<false><<<td.t.per_xcd * td.t.nxcd, NT, 0, s>>>(td);
-  if (A.general) {
-    k_adj_fold_general<false><<<nb(nIn, 256), 256, 0, s>>>(A, Q, Wk, qout, fbar, i_f, fw, 0);
-    const long long slots = face_node_slots(A);
-    if (slots > 0)
-      k_adj_fold_general<true><<<nb(5 * slots, 256), 256, 0, s>>>(A, Q, Wk, qout, fbar, i_f, fw, slots);
-  } else if (nBand > 0)
-    k_adj_fold<<<nb(nBand, 256), 256, 0, s>>>(A, Wk, qout, fbar, i_f, fw);
+  const long long ng = face_ghosts(A);
+  if (ng > 0) k_adj_face<<<nb(ng, 64), 64, 0, s>>>(A, Q, Wk + (long long)W_GG * L.fe, (unsigned)ng);
+  if (nBand > 0) k_adj_fold<<<nb(nBand, 256), 256, 0, s>>>(A, Wk, qout, fbar, i_f, fw);
   return hipGetLastError();
 }
 
@@ -1366,7 +1285,7 @@ hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const dou
 size_t adjoint_work_elems(const Layout& L) { return (size_t)W_NF * (size_t)L.fe; }
 
 hipError_t launch_axis_avg_adjoint(hipStream_t s, const Layout& L, double* qbar) {
-  k_axis_avg_adj<<<(unsigned)(5LL * L.ni), 64, 0, s>>>(L, qbar);
+  k_axis_avg_adj<<<5 * nb(L.ni, 16), 1024, 0, s>>>(L, qbar);
   return hipGetLastError();
 }
 

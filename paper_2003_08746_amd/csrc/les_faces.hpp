@@ -19,30 +19,55 @@ struct Faces {
   int axis;               // j = 0 is the polar axis (face normals there, see face_normal)
 };
 
-// A value with one derivative (forward mode), enough for the face rule.
-struct DualD {
-  double v, d;
-  __host__ __device__ DualD() : v(0.0), d(0.0) {}
-  __host__ __device__ DualD(double a) : v(a), d(0.0) {}
-  __host__ __device__ DualD(double a, double b) : v(a), d(b) {}
+// A value with its five derivatives with respect to the boundary node's state
+// (forward mode), enough for the face rule.
+struct Dual5 {
+  double v, d[5];
+  __device__ Dual5() : Dual5(0.0) {}
+  __device__ Dual5(double a) : v(a), d{0.0, 0.0, 0.0, 0.0, 0.0} {}
 };
-__host__ __device__ inline DualD operator+(DualD a, DualD b) { return DualD(a.v + b.v, a.d + b.d); }
-__host__ __device__ inline DualD operator-(DualD a, DualD b) { return DualD(a.v - b.v, a.d - b.d); }
-__host__ __device__ inline DualD operator*(DualD a, DualD b) { return DualD(a.v * b.v, a.d * b.v + a.v * b.d); }
-__host__ __device__ inline DualD operator/(DualD a, DualD b) {
-  return DualD(a.v / b.v, (a.d * b.v - a.v * b.d) / (b.v * b.v));
+__device__ __forceinline__ Dual5 operator+(const Dual5& a, const Dual5& b) {
+  Dual5 r(a.v + b.v);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) r.d[m] = a.d[m] + b.d[m];
+  return r;
+}
+__device__ __forceinline__ Dual5 operator-(const Dual5& a, const Dual5& b) {
+  Dual5 r(a.v - b.v);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) r.d[m] = a.d[m] - b.d[m];
+  return r;
+}
+__device__ __forceinline__ Dual5 operator*(const Dual5& a, const Dual5& b) {
+  Dual5 r(a.v * b.v);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) r.d[m] = a.d[m] * b.v + a.v * b.d[m];
+  return r;
+}
+__device__ __forceinline__ Dual5 operator/(const Dual5& a, const Dual5& b) {
+  Dual5 r(a.v / b.v);
+  const double ib = 1.0 / b.v;
+#pragma unroll
+  for (int m = 0; m < 5; ++m) r.d[m] = (a.d[m] - r.v * b.d[m]) * ib;
+  return r;
 }
 __host__ __device__ inline double fval(double a) { return a; }
-__host__ __device__ inline double fval(DualD a) { return a.v; }
+__device__ __forceinline__ double fval(const Dual5& a) { return a.v; }
 __device__ inline double fsqrt(double a) { return sqrt(a); }
-__device__ inline DualD fsqrt(DualD a) {
-  const double s = sqrt(a.v);
-  return DualD(s, a.d / (2.0 * s));
+__device__ __forceinline__ Dual5 fsqrt(const Dual5& a) {
+  Dual5 r(sqrt(a.v));
+  const double h = 0.5 / r.v;
+#pragma unroll
+  for (int m = 0; m < 5; ++m) r.d[m] = h * a.d[m];
+  return r;
 }
 __device__ inline double fpow(double a, double e) { return pow(a, e); }
-__device__ inline DualD fpow(DualD a, double e) {
-  const double p = pow(a.v, e);
-  return DualD(p, e * p / a.v * a.d);
+__device__ __forceinline__ Dual5 fpow(const Dual5& a, double e) {
+  Dual5 r(pow(a.v, e));
+  const double h = e * r.v / a.v;
+#pragma unroll
+  for (int m = 0; m < 5; ++m) r.d[m] = h * a.d[m];
+  return r;
 }
 
 // Ghost state of a boundary face from the boundary node's conserved state
@@ -64,8 +89,8 @@ __device__ inline DualD fpow(DualD a, double e) {
 //     incoming one u.n - 2c/(gamma-1) from outside, and the entropy
 //     p / rho^gamma and the tangential velocity from the boundary node
 //     (outflow, u.n >= 0) or from outside.
-// T = double (the ghost fill) or DualD (its derivative along a direction of
-// qr; branches follow the values).
+// T = double (the ghost fill) or Dual5 (with its Jacobian; branches follow the
+// values).
 template <class T>
 __device__ void face_value(int type, double gamma, double pe, const double nv[3], const T qr[5],
                            const double qo[5], T out[5]) {
