@@ -754,6 +754,23 @@ hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3]
   return hipGetLastError();
 }
 
+// (bound by its launch, 4 us; see sync_outputs)
+__global__ void __launch_bounds__(256) k_publish(const double* __restrict__ scal, int* __restrict__ flag,
+                                                 const double* __restrict__ dts, int nd, double* __restrict__ host) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t < 16) host[t] = scal[t];
+  if (t == 16) {
+    host[PUBLISH_FLAG] = (double)*flag;
+    *flag = 0;
+  }
+  if (t < nd) host[PUBLISH_DTS + t] = dts[t];
+}
+
+hipError_t launch_publish(hipStream_t s, const double* scal, int* flag, const double* dts, int nd, double* host) {
+  k_publish<<<nblk(nd > 256 ? nd : 256, 256), 256, 0, s>>>(scal, flag, dts, nd, host);
+  return hipGetLastError();
+}
+
 // p[0 .. n) = 0 (a kernel, not a memset, so that a captured call records
 // only kernel nodes).
 __global__ void __launch_bounds__(256) k_zero(double* __restrict__ p, long long n) {

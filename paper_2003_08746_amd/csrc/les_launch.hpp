@@ -21,6 +21,9 @@ hipError_t launch_stats(hipStream_t s, const Layout& L, const Phys& P, int nks, 
 hipError_t launch_stats_profiles(hipStream_t s, const Layout& L, const double* acc, double samples, double core_u,
                                  double* prof, unsigned char* core);
 // p[0 .. n) = 0 on stream s.
+// host (pinned) = scal[16], the flag (cleared), and dts[0 .. nd)
+constexpr int PUBLISH_FLAG = 16, PUBLISH_DTS = 17;
+hipError_t launch_publish(hipStream_t s, const double* scal, int* flag, const double* dts, int nd, double* host);
 hipError_t launch_zero(hipStream_t s, double* p, long long n);
 // Plain copy of n16 16-byte words (instrumentation: achievable stream rate).
 hipError_t launch_stream_copy(hipStream_t s, const void* src, void* dst, long long n16);
