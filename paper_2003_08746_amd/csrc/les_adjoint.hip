@@ -151,7 +151,9 @@ struct TileArgs {
   double coef;
   double Rg, inv_gm1;  // gas constant, 1 / (gamma - 1)
   double* Wk;
-  int ntx, nty, kc, nseg, nblocks, per_xcd, nxcd;
+  int ntx, nty;
+  Schedule sch;
+  int per_xcd, nxcd;
 };
 
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
@@ -167,7 +169,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const long long fe = L.fe;
   const int hb = blockIdx.x;
   const int v = (hb % a.nxcd) * a.per_xcd + hb / a.nxcd;
-  if (v >= a.nblocks) return;
+  if (v >= a.sch.nblocks) return;
   const int tid = threadIdx.x;
   const int tx = tid % BX, ty = tid / BX, ex = tx + 1, ey = ty + 1;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -182,10 +184,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     else if (h < 2 * TY + TX) { hy2 = 0; hx2 = 2 + h - 2 * TY; }
     else { hy2 = EY - 1; hx2 = 2 + h - 2 * TY - TX; }
   }
-  for (int wq = v; wq < a.nseg; wq += a.nblocks) {
-    const int ntiles = a.ntx * a.nty;
-    const int ch = wq / ntiles, tile = wq % ntiles;
-    const int kb = a.A.lo[2] + ch * a.kc, ke = min(a.A.hi[2] + 1, kb + a.kc);  // output planes
+  for (int wq = v; wq < a.sch.nseg; wq += a.sch.nblocks) {
+    const Segment seg = segment_at(a.sch, a.ntx * a.nty, a.A.hi[2] - a.A.lo[2] + 1, wq);
+    const int tile = seg.tile;
+    const int kb = a.A.lo[2] + seg.k0, ke = a.A.lo[2] + seg.k1;  // output planes
     const int i = a.A.lo[0] - 1 + (tile % a.ntx) * TX + tx, j = a.A.lo[1] - 1 + (tile / a.ntx) * TY + ty;
     const bool in_ij = i >= 0 && i < L.ni && j >= (a.A.axis ? 1 : 0) && j < L.nj;  // W may be nonzero
     // nodes with weights: [-1, n]^3 (not on or below the polar axis, where
@@ -612,7 +614,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const long long fe = L.fe;
   const int hb = blockIdx.x;
   const int v = (hb % ta.nxcd) * ta.per_xcd + hb / ta.nxcd;
-  if (v >= ta.nblocks) return;
+  if (v >= ta.sch.nblocks) return;
   const int tid = threadIdx.x;
   const int tx = tid % BX, ty = tid / BX, ex = tx + 1, ey = ty + 1, cx = tx - 2;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -628,10 +630,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     else if (h < 2 * DTY + DTX) { hy2 = 0; hx2 = 3 + h - 2 * DTY; }
     else if (h < DNH) { hy2 = EY - 1; hx2 = 3 + h - 2 * DTY - DTX; }
   }
-  for (int wq = v; wq < ta.nseg; wq += ta.nblocks) {
-    const int ntiles = ta.ntx * ta.nty;
-    const int ch = wq / ntiles, tile = wq % ntiles;
-    const int kb = ta.A.lo[2] + ch * ta.kc, ke = min(ta.A.hi[2] + 1, kb + ta.kc);  // output planes
+  for (int wq = v; wq < ta.sch.nseg; wq += ta.sch.nblocks) {
+    const Segment seg = segment_at(ta.sch, ta.ntx * ta.nty, ta.A.hi[2] - ta.A.lo[2] + 1, wq);
+    const int tile = seg.tile;
+    const int kb = ta.A.lo[2] + seg.k0, ke = ta.A.lo[2] + seg.k1;  // output planes
     // (tiles start one node before the output box in i, so that row copies are
     // 16-byte aligned)
     const int i = ta.A.lo[0] - 3 + (tile % ta.ntx) * DTX + tx, j = ta.A.lo[1] - 2 + (tile / ta.ntx) * DTY + ty;
@@ -1256,15 +1258,12 @@ hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const dou
   // blocks over tiles of tx x ty output nodes, whose first column lies `lead`
   // before the output box
   auto tiles = [&](int tx, int ty, int lead) {
-    TileArgs ta{A, Q, qb, coef, A.P.gamma_R / A.P.gamma, 1.0 / A.P.gm1, Wk, 0, 0, 0, 0, 0, 0, A.mach.xcds};
+    TileArgs ta{A, Q, qb, coef, A.P.gamma_R / A.P.gamma, 1.0 / A.P.gm1, Wk, 0, 0, {}, 0, A.mach.xcds};
     ta.ntx = (A.hi[0] - A.lo[0] + lead + tx) / tx;
     ta.nty = (A.hi[1] - A.lo[1] + ty) / ty;
     const int nkt = A.hi[2] - A.lo[2] + 1;
-    const Schedule sch = segment_schedule((long long)ta.ntx * ta.nty, nkt, A.mach.cus, segment_kmax(L));
-    ta.kc = sch.kc;
-    ta.nblocks = sch.nblocks;
-    ta.nseg = ta.ntx * ta.nty * ((nkt + sch.kc - 1) / sch.kc);
-    ta.per_xcd = (sch.nblocks + ta.nxcd - 1) / ta.nxcd;
+    ta.sch = segment_schedule((long long)ta.ntx * ta.nty, nkt, A.mach.cus, segment_kmax(L));
+    ta.per_xcd = (ta.sch.nblocks + ta.nxcd - 1) / ta.nxcd;
     return ta;
   };
   const TileArgs tf = tiles(TX, TY, 0);

@@ -98,21 +98,20 @@ constexpr int BPC = 512 / NT;                  // resident blocks per CU (two wa
 static_assert(BX == 16 || BX == 32, "a wave covers whole patch rows");
 static_assert(BY % RPW == 0 && NT % 64 == 0 && NH2 <= NT && BPC >= 1, "tile shape");
 
+// (what a segment's start needs first, so that it comes with few cache lines)
 struct KArgs {
   Layout L;
-  Phys P;
+  Schedule sch;         // (chunk, tile) segments
+  int ntx, nty;         // tiles in i, j
+  int per_xcd;          // blocks per XCD in the remapped order
+  int nxcd;             // XCDs of the device
+  Wrap wrap;            // periodic ghosts read at their source
   const double* M;
+  Phys P;
   const double* f;
   const double* dyn;    // per-column dynamic SGS coefficients (P.sgs == 2)
   int axis;             // j = 0 is the polar axis
   int i_f;
-  int ntx, nty;         // tiles in i, j
-  int kc;               // planes per k chunk
-  int nseg;             // (chunk, tile) segments
-  int nblocks;          // blocks with work
-  int per_xcd;          // blocks per XCD in the remapped order
-  int nxcd;             // XCDs of the device
-  Wrap wrap;            // periodic ghosts read at their source
 };
 
 // Two Q planes, written at B of alternate planes: the only LDS values that E
@@ -220,7 +219,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // XCD-aware order: consecutive virtual blocks land on one XCD.
   const int hb = blockIdx.x;
   const int v = (hb % a.nxcd) * a.per_xcd + hb / a.nxcd;
-  if (v >= a.nblocks) return;
+  if (v >= a.sch.nblocks) return;
   const int tid = threadIdx.x;
   const int tx = tid % BX, ty = tid / BX;
   const int ex = tx + 1, ey = ty + 1;
@@ -255,16 +254,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // updated state Q^(l) = Q^{n+1} over the block's nodes
   double cmin = INFINITY;
   int qbuf = 0;  // LDS Q plane written at the next B (alternates every plane)
-  for (int wq = v; wq < a.nseg; wq += a.nblocks) {
+  for (int wq = v; wq < a.sch.nseg; wq += a.sch.nblocks) {
     // ---- one segment: planes [kb, ke) of one tile ----
     // segments are ordered k chunk by k chunk (kc planes; the last chunk may
     // be shorter) and tile by tile within a chunk, and the blocks take them
     // round robin: the blocks that run at the same time on one XCD work on
     // neighbouring tiles at the same planes, so the halo lines they share are
     // read while they are still in that XCD's L2
-    const int ntiles = a.ntx * a.nty;
-    const int ch = wq / ntiles, tile = wq % ntiles;
-    const int kb = ch * a.kc, ke = min(L.nk, kb + a.kc);
+    const Segment g = segment_at(a.sch, a.ntx * a.nty, L.nk, wq);
+    const int tile = g.tile, kb = g.k0, ke = g.k1;
     // segment base: plane kb - 2, the first the segment reads.  Per-thread
     // element offsets are taken from there, so they stay below 2^29 for any
     // block whose planes are small enough that kc + 6 of them are (the
@@ -752,14 +750,13 @@ namespace {
 
 // Stage kernel configuration for a layout and a schedule.
 struct Config {
-  int ntx, nty, nseg, grid, per_xcd;
+  int ntx, nty, grid, per_xcd;
 };
 
 Config config(const Layout& L, const Schedule& sch, int nxcd) {
   Config c;
   c.ntx = (L.ni + TX - 1) / TX;
   c.nty = (L.nj + TY - 1) / TY;
-  c.nseg = c.ntx * c.nty * ((L.nk + sch.kc - 1) / sch.kc);
   // hardware block b runs on XCD b mod nxcd: virtual block (b mod nxcd)
   // per_xcd + b / nxcd, so consecutive virtual blocks share an XCD
   c.per_xcd = (sch.nblocks + nxcd - 1) / nxcd;
@@ -784,8 +781,7 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
                   const double* dtp, double dt, double alpha, double* part, double* cpart) {
   if (part && cpart) return hipErrorInvalidValue;  // norms belong to stage 1, the CFL bound to stage 5
   const Config c = config(sa.L, sa.sch, sa.mach.xcds);
-  KArgs a{sa.L,  sa.P,  sa.M,      sa.f,   sa.dyn,         sa.axis,   sa.i_f,
-          c.ntx, c.nty, sa.sch.kc, c.nseg, sa.sch.nblocks, c.per_xcd, sa.mach.xcds, sa.wrap};
+  KArgs a{sa.L, sa.sch, c.ntx, c.nty, c.per_xcd, sa.mach.xcds, sa.wrap, sa.M, sa.P, sa.f, sa.dyn, sa.axis, sa.i_f};
   // the optional SGS models (dynamic closure, isotropic SGS stress) and the
   // polar axis run in instantiations of their own, so that each path keeps
   // only the registers it needs
@@ -805,7 +801,7 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
 
 }  // namespace
 
-Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax) {
+Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, bool two_sizes) {
   Schedule best;
   long long cost = -1;
   for (int n = (nk + kmax - 1) / kmax; n <= nk; ++n) {
@@ -819,8 +815,32 @@ Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax) {
       cost = c;
       best.kc = kc;
       best.nblocks = (int)nb;
+      best.nseg = (int)nseg;
     }
     if (rounds * 3 > cost) break;  // more chunks only add starts
+  }
+  // Chunks of two sizes: r full rounds are r slots segments, n a tile and one
+  // more for the rest.  Long segments come first, so the slowest block has
+  // its share of them, rounded up.  Tiles next to each other with different
+  // chunks share fewer halo lines in the L2, so this has to shorten the slowest
+  // block by 1/20 to pay: 256 x 128 x 128 (57 to 54 planes) gains 1.5 % (mixed
+  // 2 %), 256 x 128 x 361 (144 to 140) loses 1.7 %, 800 x 500 x 500 7 %.
+  const long long equal = cost;
+  for (long long r = (ntiles + slots - 1) / slots; two_sizes && r * 3 < cost; ++r) {
+    const long long n = r * slots / ntiles, more = r * slots - n * ntiles, fewer = ntiles - more;
+    if (n >= nk) break;
+    const int kl = (int)((nk + n - 1) / n), kc = (int)((nk + n) / (n + 1));
+    if (more == 0 || kl == kc || kl > kmax || (nk + kl - 1) / kl != n || (nk + kc - 1) / kc != n + 1) continue;
+    const long long lg = (fewer * n + slots - 1) / slots;  // long segments of the slowest block
+    const long long c = lg * kl + (r - lg) * kc + r * 3;
+    if (c >= cost || 20 * c > 19 * equal) continue;
+    cost = c;
+    best.kc = kc;
+    best.kl = kl;
+    best.nl = (int)fewer;
+    best.nlong = (int)(fewer * n);
+    best.nblocks = slots;
+    best.nseg = (int)(r * slots);
   }
   return best;
 }
@@ -841,6 +861,7 @@ Schedule stage_schedule(const Layout& L, const Machine& m) {
       if (s.kc > stage_kmax(L)) s.kc = stage_kmax(L);
       const long long nseg = ntiles * ((L.nk + s.kc - 1) / s.kc), nb = (ntiles * L.nk + seg - 1) / seg;
       s.nblocks = (int)(nseg < nb ? nseg : nb);
+      s.nseg = (int)nseg;
       return s;
     }
   }

@@ -15,11 +15,15 @@ struct Machine {
   int xcds = 8;
 };
 
-// Work of the persistent blocks: (k chunk, tile) segments of kc planes, taken
-// round robin by nblocks blocks.
+// Work of the persistent blocks: (k chunk, tile) segments, taken round robin
+// by nblocks blocks.  The first nl tiles have chunks of kl planes, the others
+// of kc; the nlong segments of the former come first, each kind chunk by
+// chunk and tile by tile within a chunk.
 struct Schedule {
   int kc = 0;
   int nblocks = 0;
+  int nl = 0, kl = 0, nlong = 0;
+  int nseg = 0;
 };
 
 // The schedule of nk planes of ntiles tiles on `slots` resident blocks, at
@@ -27,8 +31,24 @@ struct Schedule {
 // (the planes below and above it) and about one more for its start, so the
 // time of a launch is that of its slowest block, block 0: the sum of n + 3
 // over its segments.  The number of chunks with the smallest sum is taken,
-// the fewest on ties.
-Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax);
+// the fewest on ties.  With two_sizes, some tiles may take one chunk fewer than
+// the others, where no number of equal chunks fills the blocks' last round.
+Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, bool two_sizes = true);
+
+// The tile and planes [k0, k1) of segment x.
+struct Segment {
+  int tile, ch, k0, k1;
+};
+__device__ __forceinline__ Segment segment_at(const Schedule& s, int ntiles, int nk, int x) {
+  const bool lg = x < s.nlong;
+  const int y = lg ? x : x - s.nlong, n = lg ? s.nl : ntiles - s.nl, len = lg ? s.kl : s.kc;
+  Segment g;
+  g.ch = __builtin_amdgcn_readfirstlane(y / n);
+  g.tile = __builtin_amdgcn_readfirstlane((lg ? 0 : s.nl) + y - g.ch * n);
+  g.k0 = g.ch * len;
+  g.k1 = min(nk, g.k0 + len);
+  return g;
+}
 
 // The most planes one segment may march: its per-thread element offsets,
 // taken from two planes below it, reach kc + 6 planes and must stay below

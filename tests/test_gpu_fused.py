@@ -29,11 +29,13 @@ def _rel(a, b):
 
 
 @pytest.mark.parametrize("shape,prec", [((5, 5, 5), 0), ((30, 14, 8), 0), ((31, 15, 33), 0), ((60, 28, 300), 0),
-                                        ((200, 100, 21), 0), ((31, 15, 33), 1)])
+                                        ((200, 100, 21), 0), ((31, 15, 33), 1), ((331, 155, 12), 0),
+                                        ((331, 155, 12), 1)])
 def test_automatic_schedule_bitwise(lesmi, shape, prec, monkeypatch):
     """The automatic number of k chunks over its range: one plane per segment,
     one tile, a second tile of one row and column, many chunks of one tile,
-    several rounds of blocks.  The arithmetic of a point does not depend on
+    several rounds of blocks, and chunks of two sizes (3 and 4 planes of 144
+    tiles).  The arithmetic of a point does not depend on
     the schedule, so the result equals that of chunks of 7 planes bit for
     bit."""
     ni, nj, nk = shape
