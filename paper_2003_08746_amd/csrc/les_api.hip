@@ -438,13 +438,14 @@ int les_residual(les_ctx* ctx, double* Q, double* R, double* norms) {
   double* part = norms ? ctx->part : nullptr;
   long long nb;
   if (!ctx->use_ref && !(((uintptr_t)R) & 15)) {
-    // the fused stage kernel with Q^(0) = R = 0 and alpha dt = -1 writes
-    // 0 + R(Q) at every interior node (and reduces the norms of R)
+    // the fused stage kernel with Q^(0) = 0 and alpha dt = -1 writes 0 + R(Q)
+    // at every interior node (and reduces the norms of R); the ghosts and
+    // row padding of R are cleared
     const les::Layout& L = ctx->L;
-    HIPCHK(ctx, les::launch_zero(ctx->s, R, 5 * L.fe));
+    HIPCHK(ctx, les::launch_zero_shell(ctx->s, L, R));
     HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
     const les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
-    HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, Q, R, R, nullptr, 1.0, -1.0, part, nullptr));
+    HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, Q, nullptr, R, nullptr, 1.0, -1.0, part, nullptr));
     nb = ctx->sch.nblocks;
   } else {
     HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
@@ -470,12 +471,12 @@ int les_residual_noalloc(les_ctx* ctx, double* Q, double* R, double* norms_dev) 
     return fail(ctx, LES_ERR_ARG, "les_residual_noalloc: %lld kernel blocks exceed the scratch's %d", nb,
                 LES_NOALLOC_BLOCKS);
   HIPCHK(ctx, bc_fill(ctx, Q));
-  HIPCHK(ctx, les::launch_zero(ctx->s, R, 5 * L.fe));
+  HIPCHK(ctx, les::launch_zero_shell(ctx->s, L, R));
   const double* f = ctx->i_f >= 0 ? ctx->f : nullptr;
   HIPCHK(ctx, dyn_update(ctx, Q, nullptr));
   const les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach};
   double* part = norms_dev ? ctx->scratch : nullptr;
-  HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, Q, R, R, nullptr, 1.0, -1.0, part, nullptr));
+  HIPCHK(ctx, les::launch_stage_fp64(ctx->s, a, Q, nullptr, R, nullptr, 1.0, -1.0, part, nullptr));
   if (norms_dev) {
     // the flag word after the partials is written but never read: a
     // non-finite residual shows as NaN in the norms

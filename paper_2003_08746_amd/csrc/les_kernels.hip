@@ -771,15 +771,26 @@ hipError_t launch_publish(hipStream_t s, const double* scal, int* flag, const do
   return hipGetLastError();
 }
 
-// p[0 .. n) = 0 (a kernel, not a memset, so that a captured call records
-// only kernel nodes).
-__global__ void __launch_bounds__(256) k_zero(double* __restrict__ p, long long n) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.0;
+// The five fields of p, all elements but the interior nodes, = 0 (a kernel, not
+// a memset, so that a captured call records only kernel nodes).  16 lanes per
+// row: whole rows of ghosts, the two ends of the others, and the field's tail
+// (with the interior too: 12 us on a 150 x 110 x 90 block, this 5).
+__global__ void __launch_bounds__(256) k_zero_shell(Layout L, double* __restrict__ p) {
+  const unsigned t = blockIdx.x * 256 + threadIdx.x, row = t / 16, l = t % 16;
+  const unsigned PJ = L.nj + 4, rows = PJ * (L.nk + 4);
+  if (row >= rows) return;
+  const int k = (int)(row / PJ) - 2, j = (int)(row % PJ) - 2;
+  double* const q = p + blockIdx.y * L.fe + (long long)row * L.sj;
+  const bool inner = k >= 0 && k < L.nk && j >= 0 && j < L.nj;
+  const int n = (int)L.sj - (inner ? L.ni : 0);
+  for (int x = l; x < n; x += 16) q[inner && x >= LEAD ? x + L.ni : x] = 0.0;
+  if (row == rows - 1)
+    for (long long x = L.sj + l; x < L.fe - (long long)row * L.sj; x += 16) q[x] = 0.0;
 }
 
-hipError_t launch_zero(hipStream_t s, double* p, long long n) {
-  k_zero<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n);
+hipError_t launch_zero_shell(hipStream_t s, const Layout& L, double* p) {
+  const long long n = 16LL * (L.nj + 4) * (L.nk + 4);
+  k_zero_shell<<<dim3(nblk(n, 256), 5), 256, 0, s>>>(L, p);
   return hipGetLastError();
 }
 

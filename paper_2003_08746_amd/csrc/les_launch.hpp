@@ -24,7 +24,8 @@ hipError_t launch_stats_profiles(hipStream_t s, const Layout& L, const double* a
 // host (pinned) = scal[16], the flag (cleared), and dts[0 .. nd)
 constexpr int PUBLISH_FLAG = 16, PUBLISH_DTS = 17;
 hipError_t launch_publish(hipStream_t s, const double* scal, int* flag, const double* dts, int nd, double* host);
-hipError_t launch_zero(hipStream_t s, double* p, long long n);
+// all of the five fields of p but their interior nodes = 0
+hipError_t launch_zero_shell(hipStream_t s, const Layout& L, double* p);
 // Plain copy of n16 16-byte words (instrumentation: achievable stream rate).
 hipError_t launch_stream_copy(hipStream_t s, const void* src, void* dst, long long n16);
 long long ref_blocks(const Layout& L);

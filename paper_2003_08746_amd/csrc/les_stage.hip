@@ -575,7 +575,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
       }
       double q0v[5] = {0, 0, 0, 0, 0};
-      if (t > kb && out_ok) {
+      if (t > kb && out_ok && Q0) {
 #pragma unroll
         for (int c = 0; c < 5; ++c) q0v[c] = ldo(Q0 + sb + c * fe, nt - sk);
       }

@@ -31,7 +31,7 @@ int stage_kmax(const Layout& L);
 // already filled, but for those of periodic directions with a.wrap).  dtp (device) overrides dt when non-null.  part: norm
 // partials (or null).  cpart (or null): per-block minima of the local CFL
 // bound of the updated state (one double per block; not together with part).
-// Q0 and Qout may alias.
+// Q0 and Qout may alias; Q0 null is a zero state.
 hipError_t launch_stage_fp64(hipStream_t s, const StageArgs& a, const double* Qin, const double* Q0, double* Qout,
                              const double* dtp, double dt, double alpha, double* part, double* cpart);
 
