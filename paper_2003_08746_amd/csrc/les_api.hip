@@ -53,6 +53,7 @@ struct les_ctx {
   hipStream_t s;
   int device;
   double* M = nullptr;               // metrics [10][fe]
+  float* M32 = nullptr;              // mixed: the nine metric terms in FP32 [9][fe]
   double* S[2] = {nullptr, nullptr}; // FP64 stage buffers [5][fe]
   float* Sf[2] = {nullptr, nullptr}; // FP32 stage buffers [5][fe] (mixed precision)
   double* f = nullptr;               // source [5][nk][nj]
@@ -124,6 +125,7 @@ static void free_all(les_ctx* c) {
   for (int e = 0; e < c->nev; ++e) (void)hipEventDestroy(c->ev[e]);
   c->nev = 0;
   (void)hipFree(c->M);
+  (void)hipFree(c->M32);
   (void)hipFree(c->S[0]);
   (void)hipFree(c->S[1]);
   (void)hipFree(c->Sf[0]);
@@ -346,7 +348,8 @@ int les_create(les_ctx** out, const les_grid* grid, const les_metrics* metrics, 
             hipMalloc(&c->scal, 16 * sizeof(double)) == hipSuccess && hipMalloc(&c->flag, sizeof(int)) == hipSuccess;
   if (ok && c->prec == LES_MIXED)
     ok = hipMalloc(&c->Sf[0], 5 * fe * sizeof(float)) == hipSuccess &&
-         hipMalloc(&c->Sf[1], 5 * fe * sizeof(float)) == hipSuccess;
+         hipMalloc(&c->Sf[1], 5 * fe * sizeof(float)) == hipSuccess &&
+         hipMalloc(&c->M32, 9 * fe * sizeof(float)) == hipSuccess;
   if (ok && prm->sgs == 2)
     ok = hipMalloc(&c->dyn, 2 * les::dyn_ncol(c->L) * sizeof(double)) == hipSuccess &&
          hipMalloc(&c->dynw, les::dynamic_work_elems(c->L) * sizeof(double)) == hipSuccess;
@@ -378,6 +381,7 @@ int les_create(les_ctx** out, const les_grid* grid, const les_metrics* metrics, 
     }
     e = metrics_dense ? les::launch_metrics_copy(c->s, c->L, metrics_dense, c->M)
                       : les::launch_metrics(c->s, c->L, c->bc, grid->xyz, c->M);
+    if (e == hipSuccess && c->M32) e = les::launch_metrics_f32(c->s, c->L, c->M, c->M32);
     if (e == hipSuccess) e = hipStreamSynchronize(c->s);
     if (e != hipSuccess) {
       rc = fail(nullptr, LES_ERR_HIP, "les_create: metrics: %s", hipGetErrorString(e));
@@ -565,7 +569,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
   const double* f = ctx->i_f >= 0 ? ctx->f : nullptr;
   const double cnt = (double)L.ni * L.nj * L.nk;
   if (ctx->prec == LES_MIXED) {
-    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach, wrap};
+    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach, wrap, ctx->M32};
     for (int l = 0; l < 5; ++l) {
       const float* in32 = (l == 0 && !shadow_in) ? nullptr : ctx->Sf[(l + 1 + par) & 1];
       float* out32 = (l < 4 || shadow_out) ? ctx->Sf[(l + par) & 1] : nullptr;

@@ -729,6 +729,17 @@ hipError_t launch_metrics_copy(hipStream_t s, const Layout& L, const double* src
   return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(256) k_metrics_f32(long long n, const double* __restrict__ M,
+                                                     float* __restrict__ M32) {
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t < n) M32[t] = (float)M[t];
+}
+
+hipError_t launch_metrics_f32(hipStream_t s, const Layout& L, const double* M, float* M32) {
+  k_metrics_f32<<<nblk(9 * L.fe, 256), 256, 0, s>>>(9 * L.fe, M, M32);
+  return hipGetLastError();
+}
+
 hipError_t launch_metrics_export(hipStream_t s, const Layout& L, const double* M, double* dst) {
   Dense D{L.ni, L.nj, L.nk};
   k_metrics_export<<<nblk(D.n(), 256), 256, 0, s>>>(L, D, M, dst);

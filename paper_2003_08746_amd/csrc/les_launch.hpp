@@ -9,6 +9,8 @@ namespace les {
 
 hipError_t launch_metrics(hipStream_t s, const Layout& L, const int bc[3], const double* xyz, double* M);
 hipError_t launch_metrics_copy(hipStream_t s, const Layout& L, const double* src, double* M);
+// M32[9][fe] = the nine metric terms in FP32
+hipError_t launch_metrics_f32(hipStream_t s, const Layout& L, const double* M, float* M32);
 hipError_t launch_metrics_export(hipStream_t s, const Layout& L, const double* M, double* dst);
 long long ghost_count(const Layout& L);
 // (ghosts of a direction with wrap.per are left to the reader)
