@@ -94,7 +94,8 @@ struct DynArgs {
 // shifts, at two waves a SIMD).  Each sum keeps its two earlier planes in
 // registers (92 of 256), so the order of E keeps few other values at a time.
 // Measured on the 256 x 128 x 128 jet: 297 us, the two passes 490 + 302; on a
-// 60 x 44 x 33 block 30 us, 480.
+// 60 x 44 x 33 block 30 us, 480.  (Priorities: see wave_priority; 1 % of a step
+// on either block.)
 template <class QI>
 __global__ void __launch_bounds__(DNT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
@@ -160,6 +161,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
       const int tx = tl % DBX, ty = tl / DBX;
       const int yp = ty < DBY - 1 ? ty + 1 : ty, ym = ty > 0 ? ty - 1 : ty;
       // ---- C ----
+      wave_priority<3>();
       auto put = [&](int q, double f) { sF[q][ty][tx] = fma(2.0, f, lane_prev(f)) + lane_next(f); };
       prims(qn, pn);
       put(0, pn[0]);
@@ -176,6 +178,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
         const double D = icbrt(J);
         d2 = D * D;
       }
+      wave_priority<2>();
       __builtin_amdgcn_sched_barrier(0);
       if (full) {
         const double rho = pc[0];
@@ -186,6 +189,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) put(11 + c, ru[c] * pc[4]);
         }
+        wave_priority<1>();
         __builtin_amdgcn_sched_barrier(0);
         double du[4][3];
 #pragma unroll
@@ -207,6 +211,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
       lds_barrier();
 
       // ---- E ----
+      wave_priority<3>();
       // (the LDS reads run one field ahead of the sums)
       double r0 = sF[0][ym][tx], r1 = sF[0][ty][tx], r2 = sF[0][yp][tx];
       auto take = [&](int q, int qnext) {
@@ -253,6 +258,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
         pin(w);
       }
       load(t + 1, qn, mn);
+      wave_priority<2>();
       __builtin_amdgcn_sched_barrier(0);
       if (full) {
         double Lm[6];
@@ -262,6 +268,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
         Lm[0] -= tr;
         Lm[3] -= tr;
         Lm[5] -= tr;
+        wave_priority<1>();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
@@ -270,6 +277,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
           s[0] += two * Lm[q] * Mq;
           s[1] += two * Mq * Mq;
         }
+        wave_priority<0>();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {

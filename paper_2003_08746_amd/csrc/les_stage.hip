@@ -454,6 +454,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
             qn[q - 1] = (T)ldo(Q2 + (q - 1) * fe, qoff2);
           }
         }
+        // (FP64 only: its phases are bound by the issue rate, and gain 2 to 3 %
+        // - 256 x 128 x 128 5.43 to 5.33 ms a call, 191 x 97 x 75 1985 to 1924
+        // us; the mixed path, bound by memory, loses 0.4 %)
+        if (sizeof(T) == 8) {
+          if (q == 0) wave_priority<3>();
+          if (q == 2) wave_priority<2>();
+          if (q == 3) wave_priority<1>();
+          if (q == 5) wave_priority<0>();
+        }
         __builtin_amdgcn_sched_barrier(0);
       };
       load_ahead(0);
@@ -613,6 +622,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       lds_barrier();
 
       // ---- E: residual (tile nodes) ----
+      if (sizeof(T) == 8) wave_priority<3>();
       if (kTwice && inner && fy_ok) {
         // FP64: the eta face above this row, subtracted from this row's
         // residual and left in LDS for the row above, which adds it in phase C
@@ -675,6 +685,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
         for (int c = 0; c < 9; ++c) cm[c] = ldo(kq->M + sb + c * fe, n);
       }
+      if (sizeof(T) == 8) wave_priority<2>();
       // zeta face t - 1/2 between plane t-1 and plane t; it completes the
       // residual of plane t-1 (rs) and opens that of plane t (racc)
       T rs[5] = {0, 0, 0, 0, 0};
@@ -693,6 +704,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
         for (int c = 0; c < 5; ++c) racc[c] = r[c];
       }
+      if (sizeof(T) == 8) wave_priority<1>();
       const double J_fin = J_prev;
 #pragma unroll
       for (int c = 0; c < 5; ++c) hz_prev[c] = hz[c];

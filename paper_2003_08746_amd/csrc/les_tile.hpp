@@ -129,6 +129,18 @@ __device__ __forceinline__ void lds_barrier() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// Priority (3 high .. 0) of this wave for its SIMD's issue slots.  Two waves
+// share a SIMD; at equal priority the older one runs ahead and the younger
+// finishes each phase alone, with nothing to hide its latencies behind, while
+// the older waits at the barrier.  A wave that lowers its priority as it
+// gets through a phase lets the one behind catch up.  (Stage kernel and
+// dynamic closure; the adjoint's dissipation pass, whose phases wait more for
+// LDS, lost 6 % by it.)
+template <int N>
+__device__ __forceinline__ void wave_priority() {
+  __builtin_amdgcn_s_setprio(N);
+}
+
 // The value of the lane before / after this one (DPP wave shifts by one lane;
 // the end lanes read 0).
 __device__ __forceinline__ float lane_prev(float v) {
