@@ -40,8 +40,9 @@
 // Memory.  Wave w owns patch rows 2w and 2w+1 (rows 4w .. 4w+3 with the
 // 16-wide patch the shape constants also allow).  The ten metric fields of
 // those rows are wave-private, so they travel as asynchronous global->LDS
-// copies (16 bytes per lane) into per-wave LDS blocks with no barrier.  The
-// copies of the next plane's metrics and the loads of the own column two
+// copies (16 bytes per lane) into per-wave LDS blocks with no barrier (FP32:
+// nine terms from an FP32 copy, and J, straight into registers).  The copies
+// of the next plane's metrics and the loads of the own column two
 // planes ahead are issued one at a time between the sub-steps of C, the
 // helper ring of the next plane at its start, Q^(0) of the plane being
 // finished at its end.  The block barriers order LDS data only: a full
@@ -59,11 +60,13 @@
 // the FP64 work of earlier ones and the live ranges exceed the 256 registers
 // of a two-wave-per-SIMD launch.
 //
-// What bounds it, 256 x 128 x 128 FP64 (268 us a stage, 346 before): two waves
-// per SIMD (LDS and registers allow no more) spend 6,500 cycles of a plane's
-// 10,800 issuing vector instructions, most of the rest at the two barriers,
-// where the older wave of each SIMD waits for the younger; the core runs at
-// 2.0 GHz under this load (2.36 GHz on a block of 32^3).  At 800 x 500 x 500 the
+// What bounds it, 256 x 128 x 128 FP64 (258 us a stage, 346 before): 6.3e7
+// vector instructions a launch need 123 us of issue at the 2.0 GHz the core
+// runs at under this load (2.36 GHz on a block of 32^3), and 1.06 GB between
+// L2 and memory 190 us at the rate of a large copy; two waves per SIMD (LDS
+// and registers allow no more) overlap the two only in part and wait for a
+// third of their cycles, at the two barriers most of all.  Falling priorities
+// (wave_priority) keep the two waves of a SIMD together.  At 800 x 500 x 500 the
 // traffic between L2 and memory is as near.
 //
 // Work per thread is independent of the floating-point type T (double for
