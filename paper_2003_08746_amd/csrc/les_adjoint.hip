@@ -553,9 +553,9 @@ __device__ __forceinline__ bool has_images(const AdjK& A, int i, int j, int k) {
 // the loads of the next plane are issued after the zeta face, because the 512
 // threads' 256 registers do not hold them beside it (with all of it in
 // registers: 183 spills and 300 us on the 128 x 64 x 64 jet).  Bound by the
-// FP64 issue rate, a patch having 1.5 times its tile's nodes: 97 us on that
-// jet and 138 us on the 128 x 64 x 121 O-grid, where the passes replaced took
-// 199 and 404 us (with the flux pass: 269 to 147 and 536 to 219 us).
+// FP64 issue rate, a patch having 1.5 times its tile's nodes: 94 us on that
+// jet and 134 us on the 128 x 64 x 121 O-grid, where the passes replaced took
+// 199 and 404 us (with the flux pass: 269 to 143 and 536 to 215 us).
 // ---------------------------------------------------------------------------
 constexpr int DTX = BX - 4, DTY = BY - 4;  // output tile of the dissipation pass
 constexpr int DNH = 2 * DTX + 2 * DTY;     // ring nodes
@@ -606,6 +606,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   __shared__ double ly[BY][DTX], ny[BY][DTX], cy[BY][DTX];  // eta radius, signed sensor, 1 / Sigma; columns 2..DTX+1
   __shared__ double fF[5][BY - 1][DTX], fG[5][BY - 1][DTX], fL[BY - 1][DTX], fA[BY - 1][DTX], fB[BY - 1][DTX];
   __shared__ double sV[5][BY][DTX];  // V_1 of the plane
+  __shared__ unsigned sh[DNH];       // columns of the ring nodes
   __shared__ double mbw[NW][10][2][BX];
   const TileArgs& ta = a.t;
   const Layout& L = ta.A.L;
@@ -622,14 +623,19 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const unsigned sk = (unsigned)L.sk;
   const double coef = ta.coef;
   const int axis = ta.A.axis;
-  int hx2 = 0, hy2 = 0;  // ring slot of helper thread tid < DNH
-  {
-    const int h = tid;
-    if (h < DTY) { hx2 = 0; hy2 = 3 + h; }
-    else if (h < 2 * DTY) { hx2 = EX - 1; hy2 = 3 + h - DTY; }
-    else if (h < 2 * DTY + DTX) { hy2 = 0; hx2 = 3 + h - 2 * DTY; }
-    else if (h < DNH) { hy2 = EY - 1; hx2 = 3 + h - 2 * DTY - DTX; }
-  }
+  // ring slot of helper thread h < DNH; formed again in each plane, and its
+  // column kept in LDS: as spilled registers, their reloads would wait for the
+  // stores before them (the counter of outstanding operations is in order)
+  auto ring = [&](int h, int& hx2, int& hy2) {
+    if (h < 2 * DTY) {
+      hx2 = h < DTY ? 0 : EX - 1;
+      hy2 = 3 + (h < DTY ? h : h - DTY);
+    } else {
+      const int g = h - 2 * DTY;
+      hy2 = g < DTX ? 0 : EY - 1;
+      hx2 = 3 + (g < DTX ? g : g - DTX);
+    }
+  };
   for (int wq = v; wq < ta.sch.nseg; wq += ta.sch.nblocks) {
     const Segment seg = segment_at(ta.sch, ta.ntx * ta.nty, ta.A.hi[2] - ta.A.lo[2] + 1, wq);
     const int tile = seg.tile;
@@ -643,7 +649,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const bool fx_ij = jj && i >= -1 && i < L.ni && tx < BX - 1;     // xi face (i, i + 1)
     const bool fy_ij = ii && j >= -1 && j < L.nj && ty < BY - 1 && cx_ok;
     const bool out_ok = cx_ok && ry_ok && i >= ta.A.lo[0] && i <= ta.A.hi[0] && j <= ta.A.hi[1];
-    const int hi = i - tx + hx2 - 1, hj = j - ty + hy2 - 1;
+    int hx = 0, hy = 0;
+    ring(tid < DNH ? tid : 0, hx, hy);
+    const int hi = i - tx + hx - 1, hj = j - ty + hy - 1;
     const int kr = kb - 4;
     const long long sb = (long long)kr * L.sk;
     const unsigned col = (unsigned)((long long)clampi(i, -2, L.ni + 1) + (long long)clampi(j, -2, L.nj + 1) * L.sj + L.o);
@@ -688,7 +696,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       load5(kp->t.Q, off(col, kb - 3), qm1);
       load5(kp->t.Q, off(col, kb - 2), qw);
       load5(kp->t.Q, off(col, kb - 1), qa);
-      if (tid < DNH) load5(kp->t.Q, off(hcol, kb - 2), hq);
+      if (tid < DNH) {
+        sh[tid] = hcol;
+        load5(kp->t.Q, off(hcol, kb - 2), hq);
+      }
       load5(kp->t.qb, off(col, kb - 2), bn);
       Jn = ldo(kp->t.A.M + sb + 9 * fe, off(col, kb - 2));
       pm1 = pres(kp->t.A.P, qm1);
@@ -720,7 +731,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       sp[ey][ex] = pc;
 #pragma unroll
       for (int c = 0; c < 5; ++c) sW[c][ty][tx] = Wc[c];
-      if (tid < DNH) {
+      if (tl < DNH) {
+        int hx2, hy2;
+        ring(tl, hx2, hy2);
 #pragma unroll
         for (int c = 0; c < 5; ++c) sq[c][hy2][hx2] = hq[c];
         sp[hy2][hx2] = pres(P, hq);
@@ -732,7 +745,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       double m[9], J;
       read_metric_rows(&mbw[wave][0][ty & 1][tx], m, J);
       const char* const msrc = (const char*)(kq->t.A.M + lane_el + (long long)clampi(t + 1, -2, L.nk + 1) * L.sk);
-      const unsigned on = off(col, t + 2), ob = off(col, t + 1), oh = off(hcol, t + 1);
+      const unsigned on = off(col, t + 2), ob = off(col, t + 1);
       auto load_ahead = [&](int q) {
         if (t <= ke) {
           copy_to_lds(msrc + q * fstep2, mdst + q * 128);
@@ -873,6 +886,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
       load_ahead(3);
       load_ahead(4);
+      // (the own column's loads before that arithmetic, the others after it: 16
+      // together wait to issue)
+      load5(kq->t.Q, on, qn);
+      __builtin_amdgcn_sched_barrier(0);
       // plane t-2 is complete: the pressure adjoint to conserved variables
       double o[5];
       {
@@ -895,8 +912,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       pin(pb1);
       pin(pbc);
       pin(nbz);
-      if (tid < DNH) load5(kq->t.Q, oh, hq);
-      load5(kq->t.Q, on, qn);
+      if (tl < DNH) load5(kq->t.Q, off(sh[tl], t + 1), hq);
       load5(kq->t.qb, ob, bn);
       Jn = ldo(kq->t.A.M + sb + 9 * fe, ob);
       __builtin_amdgcn_sched_barrier(0);
