@@ -553,9 +553,9 @@ __device__ __forceinline__ bool has_images(const AdjK& A, int i, int j, int k) {
 // the loads of the next plane are issued after the zeta face, because the 512
 // threads' 256 registers do not hold them beside it (with all of it in
 // registers: 183 spills and 300 us on the 128 x 64 x 64 jet).  Bound by the
-// FP64 issue rate, a patch having 1.5 times its tile's nodes: 94 us on that
-// jet and 134 us on the 128 x 64 x 121 O-grid, where the passes replaced took
-// 199 and 404 us (with the flux pass: 269 to 143 and 536 to 215 us).
+// FP64 issue rate, a patch having 1.5 times its tile's nodes: 92 us on that
+// jet and 131 us on the 128 x 64 x 121 O-grid, where the passes replaced took
+// 199 and 404 us (with the flux pass: 269 to 141 and 536 to 212 us).
 // ---------------------------------------------------------------------------
 constexpr int DTX = BX - 4, DTY = BY - 4;  // output tile of the dissipation pass
 constexpr int DNH = 2 * DTX + 2 * DTY;     // ring nodes
