@@ -93,9 +93,9 @@ struct DynArgs {
 // issue rate (about 800 instructions a node and step, a quarter of them lane
 // shifts, at two waves a SIMD).  Each sum keeps its two earlier planes in
 // registers (92 of 256), so the order of E keeps few other values at a time.
-// Measured on the 256 x 128 x 128 jet: 297 us, the two passes 490 + 302; on a
-// 60 x 44 x 33 block 30 us, 480.  (Priorities: see wave_priority; 1 % of a step
-// on either block.)
+// Measured on the 256 x 128 x 128 jet: 274 us, the two passes 490 + 302; on a
+// 60 x 44 x 33 block about 27 us, 480.  (Priorities: see wave_priority; 1 % of
+// a step on either block.)
 template <class QI>
 __global__ void __launch_bounds__(DNT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
@@ -120,14 +120,16 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
     const int ic = min(i, L.ni + 1), jc = min(j, L.nj + 1);
     const unsigned col = (unsigned)L.at(ic, jc, 0);
     const unsigned qcol = wrap_column(L, a.wrap, ic, jc);
-    auto load = [&](int k, QI q[5], double m[10]) {  // Q of plane k + 1, metrics of plane k
-      const PlaneRef p = wrap_plane(L, a.wrap, min(max(k + 1, -2), L.nk + 1));
+    auto load_state = [&](int k, QI q[5]) {
+      const PlaneRef p = wrap_plane(L, a.wrap, min(max(k, -2), L.nk + 1));
       const unsigned qo = wrap_offset(qcol, p);
-      const double* const Mk = a.M + (long long)min(max(k, -2), L.nk + 1) * L.sk;
 #pragma unroll
       for (int c = 0; c < 5; ++c) q[c] = ldo(Q + p.base + c * fe, qo);
+    };
+    auto load_metrics = [&](int k, int c0, double m[10]) {  // five of the ten fields
+      const double* const Mk = a.M + (long long)min(max(k, -2), L.nk + 1) * L.sk;
 #pragma unroll
-      for (int c = 0; c < 10; ++c) m[c] = ldo(Mk + c * fe, col);
+      for (int c = 0; c < 5; ++c) m[c0 + c] = ldo(Mk + (c0 + c) * fe, col);
     };
     auto prims = [&](const QI q[5], double p[5]) {
       p[0] = (double)q[0];
@@ -146,7 +148,9 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
     double mo[9], do2 = 0.0;      // J m and D^2 of plane t-1
     QI qn[5];                     // Q of plane t+1 (in flight until C)
     double mn[10];                // metrics of plane t (in flight until C)
-    load(kb - 3, qn, mn);
+    load_state(kb - 2, qn);
+    load_metrics(kb - 3, 0, mn);
+    load_metrics(kb - 3, 5, mn);
 #pragma unroll
     for (int c = 0; c < 4; ++c) pm[c] = um[c] = uc[c] = 0.0;
 #pragma unroll
@@ -208,10 +212,14 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) put(20 + c, grad ? w * du[3][c] : 0.0);
       }
+      // (the next plane's 15 loads in three groups: issued together in E they
+      // wait in the memory pipeline's queue, 5680 against 5510 us for two steps)
+      load_state(t + 2, qn);
       lds_barrier();
 
       // ---- E ----
       wave_priority<3>();
+      load_metrics(t + 1, 0, mn);
       // (the LDS reads run one field ahead of the sums)
       double r0 = sF[0][ym][tx], r1 = sF[0][ty][tx], r2 = sF[0][yp][tx];
       auto take = [&](int q, int qnext) {
@@ -257,7 +265,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
         for (int q = 0; q < 6; ++q) pin(Sd[q]);
         pin(w);
       }
-      load(t + 1, qn, mn);
+      load_metrics(t + 1, 5, mn);
       wave_priority<2>();
       __builtin_amdgcn_sched_barrier(0);
       if (full) {
