@@ -98,6 +98,25 @@ def test_wrapped_ghosts_bitwise(lesmi, name):
     s.close()
 
 
+@pytest.mark.parametrize("shape", [(5, 5, 5), (23, 7, 6), (37, 15, 9)])
+def test_residual_clears_shell(lesmi, shape):
+    """les_residual writes every element of R: the residual at the interior
+    nodes, and 0 in the ghosts, the row padding and the field's tail (rows of
+    one and of several 16-element groups)."""
+    import torch
+    case = I.jet_case(*shape, seed=3)
+    print(f"[gpu] residual shell {shape}", flush=True)
+    s = lesmi.Solver(case)
+    Q = s.upload(case["Q"])
+    R = torch.full((5 * s.fe,), float("nan"), dtype=torch.float64, device="cuda")
+    lesmi.les_residual(s.ctx, Q.data_ptr(), R.data_ptr())
+    torch.cuda.synchronize()
+    assert torch.isfinite(R).all()
+    inner = s.download(R)[(slice(None), slice(2, -2), slice(2, -2), slice(2, -2))]
+    assert np.count_nonzero(R.cpu().numpy()) == np.count_nonzero(inner) > 0
+    s.close()
+
+
 @pytest.mark.parametrize("shape,seg", [((61, 29, 23), "5"), ((31, 15, 9), "4"), ((93, 43, 17), ""),
                                        ((40, 20, 12), "7"), ((61, 29, 23), "40"), ((93, 43, 37), "200")])
 def test_fused_matches_reference_kernel(lesmi, shape, seg, monkeypatch):
