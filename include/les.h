@@ -288,7 +288,8 @@ int les_advance(les_ctx *ctx, double *Q, int nsteps, double *dt_out, double *nor
  * fbar: device, dense [5][nk][nj], accumulated, or NULL.
  * The first adjoint call allocates the work arrays (35 fields of field_elems
  * doubles; LES_ERR_NOMEM if they do not fit).  LES_ERR_STATE for the
- * dynamic closure, and for a block of 2^30 padded nodes or more.  With
+ * dynamic closure, for a block of 2^30 padded nodes or more, and for a padded
+ * k plane so large that ten of them exceed 2^29 elements.  With
  * LES_BC_AXIS the centerline condition on every stage input and on the
  * result is part of the step (the axis entries of Qbar come out 0), and a
  * forcing plane's axis row (i_f, 0, k) receives no fbar: the centerline
@@ -305,7 +306,7 @@ int les_adjoint_step(les_ctx *ctx, const double *stage_ckpt, double dt, double *
  * Rbar: device, library layout; only interior values are read.
  * Qbar: device, library layout; interior written (must not alias Q or Rbar).
  * Allocates the adjoint work arrays on first use (35 fields of field_elems
- * doubles, kept by the context). */
+ * doubles, kept by the context); the limits of les_adjoint_step hold. */
 int les_residual_adjoint(les_ctx *ctx, double *Q, const double *Rbar, double *Qbar);
 
 /* Probe objective on the plane i = i_p (interior of Q):

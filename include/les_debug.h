@@ -36,6 +36,16 @@ int les_debug_stage_time(les_ctx *ctx, double *total_ms, long long *launches);
  * when the launch fails.  Needs no context. */
 int les_debug_stream_copy(const void *src, void *dst, long long nbytes, void *hip_stream);
 
+/* How a marching kernel cuts a block of grid->ni x nj x nk nodes with
+ * boundaries grid->bc (faces frozen) into segments of k planes on a device of
+ * cus compute units (host only: no GPU, no context, xyz not read).  kernel: 0
+ * the stage kernel, 1 the adjoint's flux pass, 2 its dissipation pass.
+ * out = {most planes of a segment (0: the block is refused), first and last
+ * plane marched, planes before a segment's first where its 32-bit offsets
+ * start, planes after its last where they end}.  LES_ERR_ARG for bad
+ * arguments. */
+int les_debug_segments(const les_grid *grid, int kernel, int cus, int out[5]);
+
 /* Dynamic SGS closure (sgs = 2): evaluates the per-column coefficients of Q
  * (its ghost layers filled in place) and copies them to out (device,
  * 2 (nj+4)(ni+4) doubles: C, then D_T, per padded column (j+2)(ni+4)+(i+2)).

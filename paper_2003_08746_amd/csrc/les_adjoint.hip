@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const bool h_use = tid < NH2;
     const bool h_in = hi >= 0 && hi < L.ni && hj >= (a.A.axis ? 1 : 0) && hj < L.nj;
     // per-thread offsets from plane kb - 2 (nodes clamped into the padded box)
-    const int kr = kb - 2;
+    const int kr = kb - kStageSpan.below;
     const long long sb = (long long)kr * L.sk;
     const unsigned col = (unsigned)((long long)clampi(i, -2, L.ni + 1) + (long long)clampi(j, -2, L.nj + 1) * L.sj + L.o);
     const unsigned hcol =
@@ -559,6 +559,9 @@ __device__ __forceinline__ bool has_images(const AdjK& A, int i, int j, int k) {
 // ---------------------------------------------------------------------------
 constexpr int DTX = BX - 4, DTY = BY - 4;  // output tile of the dissipation pass
 constexpr int DNH = 2 * DTX + 2 * DTY;     // ring nodes
+// (the march starts two planes before the segment, with Q of the plane before
+// that, and ends two planes after it, loading Q two planes ahead)
+constexpr Span kDissSpan{3, 4};
 
 struct DissArgs {
   TileArgs t;
@@ -652,7 +655,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     int hx = 0, hy = 0;
     ring(tid < DNH ? tid : 0, hx, hy);
     const int hi = i - tx + hx - 1, hj = j - ty + hy - 1;
-    const int kr = kb - 4;
+    const int kr = kb - kDissSpan.below;
     const long long sb = (long long)kr * L.sk;
     const unsigned col = (unsigned)((long long)clampi(i, -2, L.ni + 1) + (long long)clampi(j, -2, L.nj + 1) * L.sj + L.o);
     const unsigned hcol =
@@ -951,7 +954,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       const int k = t - 2;
       const bool st = out_ok && k >= kb;  // (k < ke always)
       const bool own = ii && jj && k >= 0 && k < L.nk;
-      const unsigned ot = st ? col + (unsigned)(k - kr) * sk : col + 4 * sk;
+      const unsigned ot = st ? col + (unsigned)(k - kr) * sk : col + kDissSpan.below * sk;
       double fl[5];
 #pragma unroll
       for (int c = 0; c < 5; ++c) fl[c] = ldo(kq->t.Wk + (W_FL + c) * fe + sb, ot);
@@ -1263,6 +1266,20 @@ __global__ void __launch_bounds__(256) k_adj_sum(Layout L, Terms z) {
 
 inline unsigned nb(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
+// A tiled pass: blocks over tiles of tx x ty output nodes, whose first column
+// lies `lead` before the output box.
+struct Pass {
+  int tx, ty, lead;
+  Span span;
+};
+constexpr Pass kFluxPass{TX, TY, 0, kStageSpan}, kDissPass{DTX, DTY, 1, kDissSpan};
+
+Schedule pass_schedule(const AdjK& A, const Pass& p, int& ntx, int& nty) {
+  ntx = (A.hi[0] - A.lo[0] + p.lead + p.tx) / p.tx;
+  nty = (A.hi[1] - A.lo[1] + p.ty) / p.ty;
+  return segment_schedule((long long)ntx * nty, A.hi[2] - A.lo[2] + 1, A.mach.cus, segment_kmax(A.L, p.span));
+}
+
 // qout = (dR/dQ|Q)^T (coef * qb) on the interior; in the Runge-Kutta
 // reverse, fbar[c][k][j] += fw qout_c on the source plane i_f (fbar non-null).
 hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const double* qb, double coef, double* Wk,
@@ -1271,20 +1288,15 @@ hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const dou
   // nodes with ghost images (see k_adj_fold)
   const long long c1 = L.nj - A.nband[1], c2 = L.nk - A.nband[2];
   const long long nBand = ((long long)A.nband[2] * L.nj + c2 * A.nband[1]) * L.ni + c2 * c1 * A.nband[0];
-  // blocks over tiles of tx x ty output nodes, whose first column lies `lead`
-  // before the output box
-  auto tiles = [&](int tx, int ty, int lead) {
+  auto tiles = [&](const Pass& p) {
     TileArgs ta{A, Q, qb, coef, A.P.gamma_R / A.P.gamma, 1.0 / A.P.gm1, Wk, 0, 0, {}, 0, A.mach.xcds};
-    ta.ntx = (A.hi[0] - A.lo[0] + lead + tx) / tx;
-    ta.nty = (A.hi[1] - A.lo[1] + ty) / ty;
-    const int nkt = A.hi[2] - A.lo[2] + 1;
-    ta.sch = segment_schedule((long long)ta.ntx * ta.nty, nkt, A.mach.cus, segment_kmax(L));
+    ta.sch = pass_schedule(A, p, ta.ntx, ta.nty);
     ta.per_xcd = (ta.sch.nblocks + ta.nxcd - 1) / ta.nxcd;
     return ta;
   };
-  const TileArgs tf = tiles(TX, TY, 0);
+  const TileArgs tf = tiles(kFluxPass);
   k_adj_flux<<<tf.per_xcd * tf.nxcd, NT, 0, s>>>(tf);
-  const DissArgs td{tiles(DTX, DTY, 1), qout, fbar, fw, i_f};
+  const DissArgs td{tiles(kDissPass), qout, fbar, fw, i_f};
   if (A.P.alpha_half)
     k_adj_diss<true><<<td.t.per_xcd * td.t.nxcd, NT, 0, s>>>(td);
   else
@@ -1296,6 +1308,21 @@ hipError_t residual_vjp(hipStream_t s, const AdjK& A, const double* Q, const dou
 }
 
 }  // namespace
+
+bool adjoint_fits(const Layout& L) {
+  const long long box = (long long)(L.ni + 4) * (L.nj + 4) * (L.nk + 4);
+  return box < (1LL << 30) && segment_kmax(L, kDissSpan) >= 1;
+}
+
+void adjoint_segments(const AdjArgs& a, bool diss, SegmentBounds& b) {
+  const AdjK A = make_adjk(a);
+  const Pass& p = diss ? kDissPass : kFluxPass;
+  int ntx, nty;
+  b = {0, A.lo[2], A.hi[2], p.span.below, p.span.ahead};
+  if (segment_kmax(a.L, p.span) < 1) return;
+  const Schedule s = pass_schedule(A, p, ntx, nty);
+  b.planes = s.kl > s.kc ? s.kl : s.kc;
+}
 
 size_t adjoint_work_elems(const Layout& L) { return (size_t)W_NF * (size_t)L.fe; }
 

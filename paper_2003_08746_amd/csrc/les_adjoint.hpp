@@ -17,6 +17,13 @@ struct AdjArgs {
   Machine mach;
 };
 
+// Can the passes index this block?  Their flat thread indices are 32-bit (box
+// nodes below 2^30), and one plane per segment of the dissipation pass must fit
+// its 32-bit offsets (segment_kmax).
+bool adjoint_fits(const Layout& L);
+// The segments of the flux or the dissipation pass (host only).
+void adjoint_segments(const AdjArgs& a, bool diss, SegmentBounds& b);
+
 // Device work elements (doubles) needed by run_adjoint_step.
 size_t adjoint_work_elems(const Layout& L);
 

@@ -198,11 +198,10 @@ static int timing_end(les_ctx* c) {
 
 // Adjoint work arrays are allocated on first use and kept by the context.
 static int ensure_adj_work(les_ctx* c) {
-  // the adjoint passes index nodes and faces (about three per node) with
-  // 32-bit integers (their work arrays limit the block far below that anyway)
-  const long long box = (long long)(c->L.ni + 4) * (c->L.nj + 4) * (c->L.nk + 4);
-  if (box >= (1LL << 30))
-    return fail(c, LES_ERR_STATE, "adjoint: block too large (%lld padded nodes, limit 2^30)", box);
+  if (!les::adjoint_fits(c->L))
+    return fail(c, LES_ERR_STATE,
+                "adjoint: block too large (%d x %d x %d: 2^30 padded nodes or more, or ten padded k planes above 2^29 "
+                "elements)", c->L.ni, c->L.nj, c->L.nk);
   const size_t need = les::adjoint_work_elems(c->L);
   if ((long long)need <= c->adj_n) return LES_OK;
   (void)hipFree(c->adj);
@@ -821,6 +820,37 @@ int les_debug_stage_time(les_ctx* ctx, double* total_ms, long long* launches) {
   ctx->t_ms = 0.0;
   ctx->t_cnt = 0;
   return rc;
+}
+
+int les_debug_segments(const les_grid* grid, int kernel, int cus, int out[5]) {
+  if (!grid || !out || kernel < 0 || kernel > 2 || cus < 1 || grid->ni < 5 || grid->nj < 5 || grid->nk < 5)
+    return LES_ERR_ARG;
+  les::SegmentBounds b;
+  les::Machine mach;
+  mach.cus = cus;
+  const les::Layout L = les::make_layout(grid->ni, grid->nj, grid->nk);
+  if (kernel == 0) {
+    b = {0, 0, L.nk - 1, les::kStageSpan.below, les::kStageSpan.ahead};
+    if (les::stage_kmax(L) >= 1) {
+      const les::Schedule s = les::stage_schedule(L, mach);
+      b.planes = s.kl > s.kc ? s.kl : s.kc;
+    }
+  } else {
+    les::AdjArgs a{};
+    a.L = L;
+    a.bc0 = grid->bc[0];
+    a.bc1 = grid->bc[1];
+    a.bc2 = grid->bc[2];
+    a.axis = grid->bc[1] == LES_BC_AXIS;
+    a.mach = mach;
+    les::adjoint_segments(a, kernel == 2, b);
+  }
+  out[0] = b.planes;
+  out[1] = b.first;
+  out[2] = b.last;
+  out[3] = b.below;
+  out[4] = b.ahead;
+  return LES_OK;
 }
 
 int les_debug_dynamic_coefficients(les_ctx* ctx, double* Q, double* out) {

@@ -274,9 +274,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int tile = g.tile, kb = g.k0, ke = g.k1;
     // segment base: plane kb - 2, the first the segment reads.  Per-thread
     // element offsets are taken from there, so they stay below 2^29 for any
-    // block whose planes are small enough that kc + 6 of them are (the
-    // schedule bounds kc accordingly); field and segment bases are 64-bit.
-    const int kr = kb - 2;
+    // segment that segment_kmax allows; field and segment bases are 64-bit.
+    const int kr = kb - kStageSpan.below;
     const long long sb = (long long)kr * L.sk;
     const QI* const Qs = Qin + sb;
     const int tix = tile % a.ntx, tiy = tile / a.ntx;
@@ -789,7 +788,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 }  // namespace
 
-int stage_kmax(const Layout& L) { return segment_kmax(L); }
+int stage_kmax(const Layout& L) { return segment_kmax(L, kStageSpan); }
 
 namespace {
 

@@ -51,13 +51,28 @@ __device__ __forceinline__ Segment segment_at(const Schedule& s, int ntiles, int
   return g;
 }
 
-// The most planes one segment may march: its per-thread element offsets,
-// taken from two planes below it, reach kc + 6 planes and must stay below
-// 2^29 (32-bit byte offsets of doubles).  0 when even one plane is too large.
-inline int segment_kmax(const Layout& L) {
-  const long long k = (1LL << 29) / L.sk - 6;
+// The planes around its segment that a kernel's per-thread element offsets
+// span: from `below` planes before the segment's first, where they start, to
+// `ahead` planes after its last.
+struct Span {
+  int below, ahead;
+};
+constexpr Span kStageSpan{2, 2};  // the stage kernel and the adjoint's flux pass
+
+// The most planes one segment may march: its offsets reach kc - 1 + below +
+// ahead planes and, within a plane, less than three more (the two ghost planes
+// before the interior, and the node), and must stay below 2^29 (32-bit byte
+// offsets of doubles).  0 when even one plane is too large.
+inline int segment_kmax(const Layout& L, Span s) {
+  const long long k = (1LL << 29) / L.sk - (s.below + s.ahead + 2);
   return k < 1 ? 0 : (k > (1 << 30) ? (1 << 30) : (int)k);
 }
+
+// What bounds a kernel's offsets on a block (see segment_kmax): the most
+// planes of its segments, the first and last plane it marches, and its span.
+struct SegmentBounds {
+  int planes, first, last, below, ahead;
+};
 
 // Periodic ghosts read at their source, so that nobody has to copy them: per[d]
 // is the period of direction d (n, or n - 1 with superposed first and last

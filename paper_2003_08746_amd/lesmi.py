@@ -125,6 +125,9 @@ def lib():
     L.les_debug_stage_time.argtypes = [_vp, _dp, ctypes.POINTER(ctypes.c_longlong)]
     L.les_debug_dynamic_coefficients.restype = ctypes.c_int
     L.les_debug_dynamic_coefficients.argtypes = [_vp, _vp, _vp]
+    L.les_debug_segments.restype = ctypes.c_int
+    L.les_debug_segments.argtypes = [ctypes.POINTER(LesGrid), ctypes.c_int, ctypes.c_int,
+                                     ctypes.POINTER(ctypes.c_int)]
     L.les_debug_stream_copy.restype = ctypes.c_int
     L.les_debug_stream_copy.argtypes = [_vp, _vp, ctypes.c_longlong, _vp]
     _lib = L
@@ -280,6 +283,14 @@ def les_debug_stage_time(ctx):
     n = ctypes.c_longlong()
     _check(lib().les_debug_stage_time(ctx, ctypes.byref(ms), ctypes.byref(n)), ctx, "les_debug_stage_time")
     return ms.value, n.value
+
+
+def les_debug_segments(grid: LesGrid, kernel, cus=256):
+    """(planes, first, last, below, ahead) of a marching kernel's segments
+    (host only)"""
+    out = (ctypes.c_int * 5)()
+    _check(lib().les_debug_segments(ctypes.byref(grid), int(kernel), int(cus), out), None, "les_debug_segments")
+    return tuple(out)
 
 
 def les_debug_stream_copy(src_ptr, dst_ptr, nbytes, stream_ptr=None):

@@ -127,3 +127,47 @@ def test_create_size_limit():
     assert 7 * lesmi.les_layout_for(8200, 8200, 5)[0][2] < (1 << 29)
     assert lesmi.les_layout_for(800, 800, 815)[2] >= (1 << 29)
     assert ctx.value is None
+
+
+_MARCHES = {"stage": 0, "adjoint flux": 1, "adjoint dissipation": 2}
+
+
+def _largest_offset(n, bc, march, cus):
+    """Largest element offset of a march's segments (those of the longest chunk
+    length, at every plane they may start at): from the plane `below` planes
+    before the first to the far corner (n + 1, n + 1) of the plane `ahead`
+    planes after the last, no further than ghost plane nk + 1.  None when the
+    block is refused."""
+    g = lesmi.LesGrid()
+    g.ni, g.nj, g.nk = n
+    for d in range(3):
+        g.bc[d] = bc[d]
+    planes, first, last, below, ahead = lesmi.les_debug_segments(g, march, cus)
+    if planes < 1:
+        return None
+    st, o, _, _ = lesmi.les_layout_for(*n)
+    far = 0
+    for kb in range(first, last + 1):
+        end = min(min(kb + planes - 1, last) + ahead, n[2] + 1)
+        far = max(far, end - (kb - below))
+    return far * st[2] + o + (n[0] + 1) + (n[1] + 1) * st[1]
+
+
+@pytest.mark.parametrize("march", list(_MARCHES))
+@pytest.mark.parametrize("n,bc", [((6500, 5900, 5), (0, 1, 0)), ((1400, 4100, 84), (0, 1, 1)),
+                                  ((6500, 5900, 5), (0, 0, 0)), ((5000, 7000, 8), (0, 1, 1)),
+                                  ((7000, 6900, 5), (0, 0, 0)), ((8200, 8200, 5), (0, 1, 0)),
+                                  ((20000, 1200, 14), (0, 1, 2)), ((900, 900, 640), (0, 1, 0)),
+                                  ((1700, 1700, 361), (0, 1, 0)), ((800, 500, 500), (0, 1, 0)),
+                                  ((256, 128, 361), (0, 3, 2)), ((5, 5, 200000), (0, 0, 0)), ((5, 5, 5), (1, 1, 1))])
+def test_march_offsets_in_range(n, bc, march):
+    """The marching kernels take 32-bit byte offsets of doubles from a base per
+    segment: on blocks of few huge planes, on large blocks and on small ones
+    every offset stays below 2^29 elements, or the block is refused."""
+    sk = lesmi.les_layout_for(*n)[0][2]
+    for cus in (1, 64, 256, 304):
+        off = _largest_offset(n, bc, _MARCHES[march], cus)
+        # refused only where one plane and the planes around it do not fit
+        need = {"stage": 7, "adjoint flux": 7, "adjoint dissipation": 10}[march]
+        assert (off is None) == (need * sk > 1 << 29), (off, sk)
+        assert off is None or off < 1 << 29, (off, cus)
