@@ -729,14 +729,16 @@ hipError_t launch_metrics_copy(hipStream_t s, const Layout& L, const double* src
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) k_metrics_f32(long long n, const double* __restrict__ M,
+// (blockIdx.y is the field: a grid dimension holds at most 2^32 - 1 threads,
+// which nine fields in one would pass from 4.8e8 padded nodes on)
+__global__ void __launch_bounds__(256) k_metrics_f32(long long fe, const double* __restrict__ M,
                                                      float* __restrict__ M32) {
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (t < n) M32[t] = (float)M[t];
+  if (t < fe) M32[blockIdx.y * fe + t] = (float)M[blockIdx.y * fe + t];
 }
 
 hipError_t launch_metrics_f32(hipStream_t s, const Layout& L, const double* M, float* M32) {
-  k_metrics_f32<<<nblk(9 * L.fe, 256), 256, 0, s>>>(9 * L.fe, M, M32);
+  k_metrics_f32<<<dim3(nblk(L.fe, 256), 9), 256, 0, s>>>(L.fe, M, M32);
   return hipGetLastError();
 }
 

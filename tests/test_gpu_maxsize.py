@@ -74,3 +74,39 @@ def test_mesh_i_fp64_windows(orc, lesmi):
     s.close()
     del Q, Qv
     torch.cuda.empty_cache()
+
+
+def test_large_mixed_block(orc, lesmi):
+    """A mixed block of 4.8e8 padded nodes, above 2^32 / 9 (its nine FP32
+    metric fields together have more elements than one grid dimension has
+    threads): one step against the oracle on a window on the jet's centre line
+    in the last planes, whose metrics end the copy, to the mixed path's bound."""
+    import torch
+    n = (800, 800, 726)
+    ni, nj, nk = n
+    assert 9 * lesmi.les_layout_for(*n)[2] > 1 << 32
+    print(f"[gpu] generating jet block {n} on the device", flush=True)
+    case = I.jet_case_device(*n, seed=1)
+    win, idx, core = window(case, (ni - W, nj // 2 + 20, nk - W), W)
+    sc = case["Q"][:, 2:-2, 2:-2, 2:-2].abs().amax(dim=(1, 2, 3)).cpu().numpy()
+    sc[1:4] = sc[1:4].max()  # (the bound's scale: the momenta share one)
+    torch.cuda.empty_cache()
+    print("[gpu] large mixed block: create", flush=True)
+    s = lesmi.Solver(case, prec=lesmi.LES_MIXED)
+    case["xyz"] = None
+    Q = s.upload(case["Q"])
+    del case
+    print("[gpu] large mixed block: one step", flush=True)
+    s.rk_step(Q, DT)
+    torch.cuda.synchronize()
+    m = orc.metrics(win)
+    Qo, _, _, _ = orc.rk_step(win, m, win["Q"], dt=DT)
+    a = _gather(s.view(Q), *idx)[core]
+    err = np.abs(a - Qo[core]).reshape(5, -1).max(1) / sc
+    moved = np.abs(Qo[core] - win["Q"][core]).max()
+    print(f"[gpu] large mixed block: rel {err.max():.2e}, step {moved:.2e}", flush=True)
+    assert moved > 10 * 2e-6  # (the window is in motion)
+    assert (err <= 2e-6).all(), err
+    s.close()
+    del Q
+    torch.cuda.empty_cache()
