@@ -142,8 +142,9 @@ typedef struct {
  * cfl: time step used when les_rk_step gets dt <= 0:
  *   dt = cfl * min_interior 1 / (sum_d (|U_d| + c |grad d|)
  *                               + 2 max(4/3, gamma/Pr) (mu/rho) sum_d |grad d|^2).
- * prec: LES_FP64, or LES_MIXED (stage states, fluxes and dissipation in FP32;
- *   Q^n, the RK accumulation, metrics and all reductions in FP64). */
+ * prec: LES_FP64, or LES_MIXED (stage states, fluxes and dissipation in FP32,
+ *   the fluxes with the metric terms rounded to FP32; Q^n, the RK accumulation,
+ *   J, the time step's metrics and all reductions in FP64). */
 typedef struct {
   double gamma, Pr, Pr_sgs;
   double mu_ref, T_ref, S_suth;
@@ -171,7 +172,10 @@ typedef struct {
  * without a superposed k of odd nk), gamma <= 1,
  * R_gas <= 0, Pr <= 0, negative k2/k4/mu_ref/CI, sgs outside 0..2, unknown
  * prec; LES_ERR_NOMEM when the block's arrays (20 FP64 fields of
- * field_elems doubles, 10 more FP32 ones when mixed) do not fit.  sgs = 2
+ * field_elems doubles, 10 more FP32 ones when mixed) do not fit.  A mixed
+ * context also keeps an FP32 copy of the nine metric terms (9 FP32 fields) when
+ * at least 10 FP64 fields stay free besides; without it the results are the
+ * same and a step takes about 6 % longer.  sgs = 2
  * allocates the dynamic closure's work array (4 fields) here too. */
 int les_create(les_ctx **out, const les_grid *grid, const les_metrics *metrics,
                const les_flow_params *params, void *hip_stream);

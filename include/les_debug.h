@@ -19,6 +19,12 @@ extern "C" {
  * LES_ERR_ARG for a null context. */
 int les_debug_use_reference(les_ctx *ctx, int on);
 
+/* use != 0: mixed stages take their metric terms from the context's FP32 copy
+ * where it has one (default); use == 0: from the FP64 fields.  Returns 1 when
+ * the context holds the copy, 0 when not (an FP64 context, or no memory for
+ * it); LES_ERR_ARG for a null context. */
+int les_debug_metric_copy(les_ctx *ctx, int use);
+
 /* on != 0: record a HIP event pair around every stage-kernel launch on the
  * context's stream (and reset the totals); on == 0: stop recording. */
 int les_debug_stage_timing(les_ctx *ctx, int on);

@@ -53,7 +53,7 @@ struct les_ctx {
   hipStream_t s;
   int device;
   double* M = nullptr;               // metrics [10][fe]
-  float* M32 = nullptr;              // mixed: the nine metric terms in FP32 [9][fe]
+  float* M32 = nullptr;              // mixed: the nine metric terms in FP32 [9][fe], where memory allows
   double* S[2] = {nullptr, nullptr}; // FP64 stage buffers [5][fe]
   float* Sf[2] = {nullptr, nullptr}; // FP32 stage buffers [5][fe] (mixed precision)
   double* f = nullptr;               // source [5][nk][nj]
@@ -73,6 +73,7 @@ struct les_ctx {
   double p_exit[6] = {0, 0, 0, 0, 0, 0};
   double* outside = nullptr;         // [5][fe] outside state of characteristic faces
   int axis = 0;                      // j = 0 is the polar axis of an O-grid (bc[1] == LES_BC_AXIS)
+  int use_m32 = 1;                   // 0: mixed stages take the FP64 metrics all the same
   int use_ref = 0;                   // 1: stage through the reference kernel
   les::Schedule sch;                 // segments of the fused kernel
   les::Machine mach;                 // CU and XCD counts of the device
@@ -347,8 +348,7 @@ int les_create(les_ctx** out, const les_grid* grid, const les_metrics* metrics, 
             hipMalloc(&c->scal, 16 * sizeof(double)) == hipSuccess && hipMalloc(&c->flag, sizeof(int)) == hipSuccess;
   if (ok && c->prec == LES_MIXED)
     ok = hipMalloc(&c->Sf[0], 5 * fe * sizeof(float)) == hipSuccess &&
-         hipMalloc(&c->Sf[1], 5 * fe * sizeof(float)) == hipSuccess &&
-         hipMalloc(&c->M32, 9 * fe * sizeof(float)) == hipSuccess;
+         hipMalloc(&c->Sf[1], 5 * fe * sizeof(float)) == hipSuccess;
   if (ok && prm->sgs == 2)
     ok = hipMalloc(&c->dyn, 2 * les::dyn_ncol(c->L) * sizeof(double)) == hipSuccess &&
          hipMalloc(&c->dynw, les::dynamic_work_elems(c->L) * sizeof(double)) == hipSuccess;
@@ -357,6 +357,19 @@ int les_create(les_ctx** out, const les_grid* grid, const les_metrics* metrics, 
     delete c;
     return fail(nullptr, LES_ERR_NOMEM, "les_create: device allocation failed (%zu bytes per field)",
                 fe * sizeof(double));
+  }
+  // The FP32 metric copy only saves traffic (see les_stage.hip): it is left out
+  // where it would take memory that a run still needs, the caller's state and
+  // the outside state of boundary faces (on 288 GB, from about 0.9e9 padded
+  // nodes on; the largest mixed block has 1.2e9).
+  if (c->prec == LES_MIXED) {
+    const size_t bytes = 9 * fe * sizeof(float);
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess || avail < bytes + 10 * fe * sizeof(double) ||
+        hipMalloc(&c->M32, bytes) != hipSuccess) {
+      c->M32 = nullptr;
+      (void)hipGetLastError();
+    }
   }
   int rc = LES_OK;
   do {
@@ -568,7 +581,8 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
   const double* f = ctx->i_f >= 0 ? ctx->f : nullptr;
   const double cnt = (double)L.ni * L.nj * L.nk;
   if (ctx->prec == LES_MIXED) {
-    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach, wrap, ctx->M32};
+    les::StageArgs a{L, ctx->P, ctx->M, f, ctx->i_f, ctx->sch, ctx->dyn, ctx->axis, ctx->mach, wrap,
+                    ctx->use_m32 ? ctx->M32 : nullptr};
     for (int l = 0; l < 5; ++l) {
       const float* in32 = (l == 0 && !shadow_in) ? nullptr : ctx->Sf[(l + 1 + par) & 1];
       float* out32 = (l < 4 || shadow_out) ? ctx->Sf[(l + par) & 1] : nullptr;
@@ -796,6 +810,13 @@ int les_debug_use_reference(les_ctx* ctx, int on) {
   if (!ctx) return LES_ERR_ARG;
   ctx->use_ref = on ? 1 : 0;
   return LES_OK;
+}
+
+// Use the FP32 metric copy or not; returns whether there is one (les_debug.h).
+int les_debug_metric_copy(les_ctx* ctx, int use) {
+  if (!ctx) return LES_ERR_ARG;
+  ctx->use_m32 = use ? 1 : 0;
+  return ctx->M32 ? 1 : 0;
 }
 
 // Stage-kernel timing (les_debug.h; used by the benchmark):

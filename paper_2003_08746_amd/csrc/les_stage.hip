@@ -70,8 +70,9 @@
 // traffic between L2 and memory is as near.
 //
 // Work per thread is independent of the floating-point type T (double for
-// the FP64 path, float for the mixed path); metrics, Q^(0), the stage
-// update, J and all reductions stay in FP64.  The FP32 path keeps the order of
+// the FP64 path, float for the mixed path, which rounds the metric terms of
+// its fluxes to float); Q^(0), the stage update, J, the CFL bound's metrics
+// and all reductions stay in FP64.  The FP32 path keeps the order of
 // operations that its results were first defined by (its rounding is visible
 // at 1e-8), the FP64 path works with twice the residual and joins the
 // pressure to the normal stresses.
@@ -198,6 +199,9 @@ constexpr int kExtAxis = 2;  // the O-grid's polar axis at j = 0
 // 84 spilled scalar registers per plane (345 -> 334 us per FP64 stage at 256 x
 // 128 x 128 without them)
 constexpr int kExtPow = 4;
+// mixed path, a context without the FP32 copy of the metric terms: they are
+// taken from the FP64 fields and converted (the same values)
+constexpr int kExtM64 = 8;
 
 template <class T, class QI, bool NORM, bool CFL, int EXT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) k_stage(KArgs a, const QI* __restrict__ Qin, const double* Q0, double* Qout,
@@ -211,8 +215,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // FP32 without the CFL bound takes its metric terms from an FP32 copy (the
   // values it would convert to; J stays FP64), straight into registers: 48
   // bytes a node and stage less, of about 230 with halos.  Stage on 256 x 128
-  // x 128 227 to 210 us, 400 x 250 x 250 1160 to 1083.
-  constexpr bool kM32 = sizeof(T) == 4 && !CFL;
+  // x 128 227 to 210 us, 400 x 250 x 250 1160 to 1083.  (A context holds the
+  // copy where memory allows; kExtM64 without it.)
+  constexpr bool kM32 = sizeof(T) == 4 && !CFL && !(EXT & kExtM64);
   __shared__ double mbw[kM32 ? 1 : NW][10][RPW][BX];  // per-wave metrics rows of the current plane
   __shared__ double red_s[NW][10];         // block reductions
   static_assert(sizeof(Smem<T>) + sizeof(mbw) + sizeof(red_s) <= 163840 / BPC, "LDS of BPC blocks per CU");
@@ -811,12 +816,17 @@ Config config(const Layout& L, const Schedule& sch, int nxcd) {
 template <class T, class QI, int EXT>
 hipError_t launch_x(hipStream_t st, const Config& c, const KArgs& a, const QI* Qin, const double* Q0, double* Qout,
                     float* Qsh, const double* dtp, double dt, double alpha, double* part, double* cpart) {
-  if (part)
-    k_stage<T, QI, true, false, EXT><<<c.grid, NT, 0, st>>>(a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
-  else if (cpart)
+  constexpr int M64 = sizeof(T) == 4 ? EXT | kExtM64 : EXT;
+  if (cpart)
     k_stage<T, QI, false, true, EXT><<<c.grid, NT, 0, st>>>(a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
-  else
+  else if (part && a.M32)
+    k_stage<T, QI, true, false, EXT><<<c.grid, NT, 0, st>>>(a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
+  else if (part)
+    k_stage<T, QI, true, false, M64><<<c.grid, NT, 0, st>>>(a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
+  else if (a.M32)
     k_stage<T, QI, false, false, EXT><<<c.grid, NT, 0, st>>>(a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
+  else
+    k_stage<T, QI, false, false, M64><<<c.grid, NT, 0, st>>>(a, Qin, Q0, Qout, Qsh, dtp, dt, alpha, part, cpart);
   return hipGetLastError();
 }
 

@@ -16,7 +16,7 @@ struct StageArgs {
   int axis = 0;                 // j = 0 is the polar axis of an O-grid
   Machine mach;
   Wrap wrap;                    // periodic ghosts of Qin read at their source
-  const float* M32 = nullptr;   // mixed: the nine metric terms in FP32 [9][fe]
+  const float* M32 = nullptr;   // mixed: the nine metric terms in FP32 [9][fe], or null
 };
 
 // The schedule of the fused kernel for this layout (LES_SEG in the environment

@@ -98,6 +98,41 @@ def test_wrapped_ghosts_bitwise(lesmi, name):
     s.close()
 
 
+def _metric_copy_cases():
+    n = (31, 15, 9)
+    wavy = I.wavy_grid(*n, L=(2.0, 1.5, 1.0), amp=0.2)
+    return {"jet61x29x23": I.jet_case(61, 29, 23, seed=3), "jet61x29x23_dyn": I.jet_case(61, 29, 23, seed=3, sgs=2),
+            "wavy_ci": I.periodic_case(*n, wavy, I.smooth_state(*n, seed=7, amp=0.1), mu_ref=3e-3, sgs=1, CI=0.05),
+            "wavy_alpha07": I.periodic_case(*n, wavy, I.smooth_state(*n, seed=7, amp=0.1), mu_ref=3e-3, alpha=0.7),
+            "ogrid24x16x21": I.ogrid_case(24, 16, 21, seed=2),
+            "ogrid24x16x21_dyn": I.ogrid_case(24, 16, 21, seed=2, sgs=2)}
+
+
+METRIC_COPY_CASES = _metric_copy_cases()
+
+
+@pytest.mark.parametrize("name", list(METRIC_COPY_CASES))
+def test_mixed_without_metric_copy_bitwise(lesmi, name):
+    """Mixed steps that take their metric terms from the FP64 fields (a context
+    without memory for the FP32 copy) against steps that take them from the
+    copy, in every instantiation of the stage kernel: the same FP32 values, so
+    the same results bit for bit."""
+    case = METRIC_COPY_CASES[name]
+    print(f"[gpu] mixed without the metric copy {name}", flush=True)
+    s = lesmi.Solver(case, prec=1)
+    got = []
+    for use in (True, False):
+        assert lesmi.les_debug_metric_copy(s.ctx, use)
+        Q = s.upload(case["Q"])
+        step = s.rk_step(Q, 0.0, want_dt=True, want_norms=True)
+        adv = s.advance(Q, 3, want_dt=True, want_norms=True)
+        got.append((s.download(Q), step[0], step[1], adv[0], adv[1]))
+    assert np.isfinite(I.interior(got[0][0])).all()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+    s.close()
+
+
 @pytest.mark.parametrize("shape", [(5, 5, 5), (23, 7, 6), (37, 15, 9)])
 def test_residual_clears_shell(lesmi, shape):
     """les_residual writes every element of R: the residual at the interior

@@ -110,3 +110,35 @@ def test_large_mixed_block(orc, lesmi):
     s.close()
     del Q
     torch.cuda.empty_cache()
+
+
+def test_mixed_block_without_room_for_the_metric_copy(lesmi):
+    """A mixed block that fits the device, but not together with the FP32 copy
+    of its metrics: the context is created without the copy, and two steps
+    (with norms and time steps) equal those of a context with it, bit for
+    bit.  The device is filled up to the block's arrays (10 FP64 fields and
+    what 20 FP64 and 10 FP32 fields take) and half of the copy."""
+    import torch
+    n = (800, 500, 500)
+    fe = lesmi.les_layout_for(*n)[2]
+    print(f"[gpu] mixed block {n} with the metric copy", flush=True)
+    case = I.jet_case_device(*n, seed=2)
+    torch.cuda.empty_cache()
+    s = lesmi.Solver(case, prec=lesmi.LES_MIXED)
+    assert lesmi.les_debug_metric_copy(s.ctx)
+    Q0 = s.upload(case["Q"])
+    case["Q"] = None
+    Q = Q0.clone()
+    out = s.advance(Q, 2, want_dt=True, want_norms=True)
+    s.close()
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    ballast = torch.empty(free - (20 * 8 + 10 * 4 + 9 * 2) * fe, dtype=torch.uint8, device="cuda")
+    print(f"[gpu] mixed block {n} without room for it ({free / 1e9:.0f} GB free before)", flush=True)
+    s = lesmi.Solver(case, prec=lesmi.LES_MIXED)
+    assert not lesmi.les_debug_metric_copy(s.ctx)
+    out2 = s.advance(Q0, 2, want_dt=True, want_norms=True)
+    assert torch.equal(Q, Q0) and all(np.array_equal(a, b) for a, b in zip(out, out2))
+    s.close()
+    del ballast, Q, Q0
+    torch.cuda.empty_cache()
