@@ -402,12 +402,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         rb += musb * cd2 * Smag + pb * cid2 * ss;
         double sb2 = 2.0 * pb * rho * cid2;
         if (Smag > 0.0) sb2 += 2.0 * musb * rho * cd2 * rcp_nr(Smag);
-        Sb11 += S11 * sb2;
-        Sb22 += S22 * sb2;
-        Sb33 += S33 * sb2;
-        Sb12 += 2.0 * S12 * sb2;
-        Sb13 += 2.0 * S13 * sb2;
-        Sb23 += 2.0 * S23 * sb2;
+        // (a node whose flux no residual uses has no adjoint, and may have a
+        // strain of ghosts that nothing reads: its weights stay 0)
+        if (sb2 != 0.0) {
+          Sb11 += S11 * sb2;
+          Sb22 += S22 * sb2;
+          Sb33 += S33 * sb2;
+          Sb12 += 2.0 * S12 * sb2;
+          Sb13 += 2.0 * S13 * sb2;
+          Sb23 += 2.0 * S23 * sb2;
+        }
       }
       // Sutherland: dmu/dT = mu (3/(2 th) - 1/(th + S)) / T_ref
       double Tb = mub * mu * (1.5 * rcp_nr(th) - ithS) * P.inv_Tref;
@@ -651,15 +655,25 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const bool b1_ij = i >= -1 && i <= L.ni && j >= -1 && j <= L.nj;  // radii and sensors exist
     const bool fx_ij = jj && i >= -1 && i < L.ni && tx < BX - 1;     // xi face (i, i + 1)
     const bool fy_ij = ii && j >= -1 && j < L.nj && ty < BY - 1 && cx_ok;
-    const bool out_ok = cx_ok && ry_ok && i >= ta.A.lo[0] && i <= ta.A.hi[0] && j <= ta.A.hi[1];
     int hx = 0, hy = 0;
     ring(tid < DNH ? tid : 0, hx, hy);
     const int hi = i - tx + hx - 1, hj = j - ty + hy - 1;
+    // Edge ghosts of the two directions when neither is periodic: frozen, in
+    // no face's stencil (the residual reads only the first of them, for
+    // gradients) and not read by the fold.  They may hold anything, so they
+    // load a column next to the interior and are not stored.
+    auto edge = [&](int x, int y) {
+      return (x < 0 || x >= L.ni) && (y < 0 || y >= L.nj) && ta.A.per[0] == 0 && ta.A.per[1] == 0;
+    };
+    auto column = [&](int x, int y) {
+      const int yc = edge(x, y) ? clampi(y, 0, L.nj - 1) : clampi(y, -2, L.nj + 1);
+      return (unsigned)((long long)clampi(x, -2, L.ni + 1) + (long long)yc * L.sj + L.o);
+    };
+    const bool out_ok = cx_ok && ry_ok && i >= ta.A.lo[0] && i <= ta.A.hi[0] && j <= ta.A.hi[1] &&
+                        !edge(i, j);
     const int kr = kb - kDissSpan.below;
     const long long sb = (long long)kr * L.sk;
-    const unsigned col = (unsigned)((long long)clampi(i, -2, L.ni + 1) + (long long)clampi(j, -2, L.nj + 1) * L.sj + L.o);
-    const unsigned hcol =
-        (unsigned)((long long)clampi(hi, -2, L.ni + 1) + (long long)clampi(hj, -2, L.nj + 1) * L.sj + L.o);
+    const unsigned col = column(i, j), hcol = column(hi, hj);
     auto off = [&](unsigned c, int k) { return c + (unsigned)(clampi(k, -2, L.nk + 1) - kr) * sk; };
     const int fsel = lane >> 5, rsel = (lane / 16) % 2, pr = lane % 16;
     int icp = i - tx + 2 * pr;
@@ -857,8 +871,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       load_ahead(2);
       // ---- zeta face (t-1, t) ----
       {
-        const double iS = b1 ? rcp_nr(pp1 + 2.0 * pc + pm1) : 0.0;
-        const double ns = b1 ? (pp1 - 2.0 * pc + pm1) * iS : 0.0;
+        // (only columns of interior nodes have zeta faces; in the others the
+        // second k-ghost may be one that nothing reads)
+        const bool zs = in_ij && t >= -1 && t <= L.nk;
+        const double iS = zs ? rcp_nr(pp1 + 2.0 * pc + pm1) : 0.0;
+        const double ns = zs ? (pp1 - 2.0 * pc + pm1) * iS : 0.0;
         double F[5], G[5], LH, NA, NB;
         {
           double qc[5], Db[5];

@@ -228,3 +228,40 @@ def test_face_rk_step_adjoint_dot_product(orc, lesmi):
     scale = float(np.abs(I.interior(w) * I.interior(dQ1)).sum())
     assert abs(lhs - rhs) <= 1e-12 * scale, (lhs, rhs, scale)
     s.close()
+
+
+@pytest.mark.parametrize("sgs", [0, 1])
+@pytest.mark.parametrize("bck", [0, 1])
+def test_unread_edge_ghosts(lesmi, sgs, bck):
+    """The residual reads a ghost of two directions only where both are at
+    their first layer (the gradient at a ghost next to the interior).  NaN in
+    every other ghost of two or three Dirichlet directions, which keep the
+    caller's values, changes neither the residual nor its adjoint through the
+    face rules, bit for bit."""
+    case, Q0 = _case(ni=40, nj=20, nk=12)
+    case["bc"] = (1, 1, bck)
+    case["params"]["sgs"] = sgs
+    n = (12, 20, 40)  # k, j, i
+    out = [np.maximum(np.maximum(-x, x - (m - 1)), 0) for m, x in ((m, np.arange(-2, m + 2)) for m in n)]
+    if bck == 0:
+        out[0] = np.zeros_like(out[0])  # (its ghosts are copies of interior planes)
+    layer = np.stack(np.meshgrid(*out, indexing="ij"))
+    ndir = (layer > 0).sum(0)
+    unread = (ndir >= 2) & ((layer.max(0) == 2) | (ndir == 3))
+    P = case["Q"].copy()
+    P[:, unread] = np.nan
+    w = _interior_rand(case, 2, scale_by_field=False)
+    print(f"[gpu] faces: unread edge ghosts sgs={sgs} k bc={bck}", flush=True)
+    s = _solver(lesmi, case, Q0)
+    if bck == 1:
+        s.set_face(4, lesmi.LES_FACE_FARFIELD)
+        s.set_face(5, lesmi.LES_FACE_EXIT, p_exit=case["faces"]["p_exit"][1])
+    R, A = [], []
+    for q in (case["Q"], P):
+        Q = s.upload(q)
+        R.append(I.interior(s.download(s.residual(Q))))
+        A.append(I.interior(s.download(s.residual_adjoint(Q, s.upload(w)))))
+    assert np.isfinite(R[0]).all() and np.isfinite(A[0]).all()
+    assert np.array_equal(R[0], R[1])
+    assert np.array_equal(A[0], A[1]), f"{np.isnan(A[1]).sum()} NaN"
+    s.close()
