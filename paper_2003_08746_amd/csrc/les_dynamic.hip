@@ -179,7 +179,7 @@ k_dyn_fused(DynArgs a, const QI* __restrict__ Q) {
         const double J = mn[9];
 #pragma unroll
         for (int c = 0; c < 9; ++c) m[c] = J * mn[c];
-        const double D = icbrt(J);
+        const double D = icbrt(fabs(J));  // (D^2 has no sign: left-handed grids, J < 0)
         d2 = D * D;
       }
       wave_priority<2>();

@@ -231,3 +231,35 @@ def test_sgs_adjoint_refused(lesmi):
         s.residual_adjoint(Q, s.upload(case["Q"]))
     assert e.value.code == lesmi.LES_ERR_STATE
     s.close()
+
+
+def test_dynamic_closure_left_handed_grid(orc, lesmi):
+    """Indices that run against the coordinates (J < 0): the coefficients
+    against the oracle, weighted as above, to 1e-10, and the residual that the
+    reference kernel takes from them (an R off 16-byte alignment) to 1e-12."""
+    import torch
+    n = (23, 14, 9)
+    xyz = I.wavy_grid(*n, L=(2.0, 1.5, 1.0), amp=0.1)
+    xyz[0] = -xyz[0]
+    case = I.periodic_case(*n, xyz, I.smooth_state(*n, seed=29, amp=0.15), mu_ref=3e-3, sgs=2)
+    m = orc.metrics(case)
+    assert (m[9, 2:-2, 2:-2, 2:-2] < 0.0).all()
+    print("[gpu] dynamic closure, left-handed grid", flush=True)
+    s = lesmi.Solver(case)
+    C, D = s.dynamic_coefficients(s.upload(case["Q"]))
+    Co, Do = orc.dynamic_coefficients(case, m, case["Q"])
+    wC, wD, _ = _column_weights(orc, case, m)
+    for lab, x, xo, w in (("C", C, Co, np.abs(wC)), ("D_T", D, Do, np.abs(wD))):
+        a, ao = x[2:-2, 2:-2] * w, xo[2:-2, 2:-2] * w
+        assert ao.max() > 0.0, lab
+        err = np.abs(a - ao).max() / ao.max()
+        assert err <= 1e-10, (lab, err)
+    buf = torch.zeros(5 * s.fe + 2, dtype=torch.float64, device="cuda")
+    R = buf[1:1 + 5 * s.fe]
+    assert R.data_ptr() % 16 == 8
+    lesmi.les_residual(s.ctx, s.upload(case["Q"]).data_ptr(), R.data_ptr())
+    torch.cuda.synchronize()
+    Rg, Ro = I.interior(s.download(R)), I.interior(orc.residual(case, m, case["Q"]))
+    err = np.abs(Rg - Ro).reshape(5, -1).max(1) / np.abs(Ro).reshape(5, -1).max(1)
+    assert (err <= 1e-12).all(), err
+    s.close()
