@@ -1288,13 +1288,15 @@ inline unsigned nb(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 struct Pass {
   int tx, ty, lead;
   Span span;
+  int halo;  // planes marched around a segment
 };
-constexpr Pass kFluxPass{TX, TY, 0, kStageSpan}, kDissPass{DTX, DTY, 1, kDissSpan};
+constexpr Pass kFluxPass{TX, TY, 0, kStageSpan, 2}, kDissPass{DTX, DTY, 1, kDissSpan, 4};
 
 Schedule pass_schedule(const AdjK& A, const Pass& p, int& ntx, int& nty) {
   ntx = (A.hi[0] - A.lo[0] + p.lead + p.tx) / p.tx;
   nty = (A.hi[1] - A.lo[1] + p.ty) / p.ty;
-  return segment_schedule((long long)ntx * nty, A.hi[2] - A.lo[2] + 1, A.mach.cus, segment_kmax(A.L, p.span));
+  return segment_schedule((long long)ntx * nty, A.hi[2] - A.lo[2] + 1, A.mach.cus, segment_kmax(A.L, p.span),
+                          p.halo);
 }
 
 // qout = (dR/dQ|Q)^T (coef * qb) on the interior; in the Runge-Kutta

@@ -363,7 +363,7 @@ hipError_t run(hipStream_t s, const Layout& L, const Machine& mach, const Wrap& 
   a.ntx = (L.ni + DTI - 1) / DTI;
   const int ntiles = a.ntx * ((L.nj + DTJ - 1) / DTJ);
   // (equal chunks: the second size's arguments alone cost the kernel 85 register spills)
-  const Schedule sch = segment_schedule(ntiles, a.nks, mach.cus, a.nks, false);
+  const Schedule sch = segment_schedule(ntiles, a.nks, mach.cus, a.nks, 4, false);
   a.kc = sch.kc;
   a.nch = (a.nks + sch.kc - 1) / sch.kc;
   a.nseg = ntiles * a.nch;

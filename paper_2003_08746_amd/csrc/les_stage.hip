@@ -855,7 +855,8 @@ hipError_t launch(hipStream_t st, const StageArgs& sa, const QI* Qin, const doub
 
 }  // namespace
 
-Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, bool two_sizes) {
+Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, int halo, bool two_sizes) {
+  const int start = halo + 1;
   Schedule best;
   long long cost = -1;
   for (int n = (nk + kmax - 1) / kmax; n <= nk; ++n) {
@@ -864,14 +865,14 @@ Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, bool tw
     const int last = nk - (n - 1) * kc;
     const long long nseg = ntiles * n, nb = nseg < slots ? nseg : slots;
     const long long rounds = (nseg + nb - 1) / nb, full = (ntiles * (n - 1) + nb - 1) / nb;
-    const long long c = full * kc + (rounds - full) * last + rounds * 3;
+    const long long c = full * kc + (rounds - full) * last + rounds * start;
     if (cost < 0 || c < cost) {
       cost = c;
       best.kc = kc;
       best.nblocks = (int)nb;
       best.nseg = (int)nseg;
     }
-    if (rounds * 3 > cost) break;  // more chunks only add starts
+    if (rounds * start > cost) break;  // more chunks only add starts
   }
   // Chunks of two sizes: r full rounds are r slots segments, n a tile and one
   // more for the rest.  Long segments come first, so the slowest block has
@@ -883,13 +884,13 @@ Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, bool tw
   // where they would shorten the slowest block by less, 9 blocks, 3 % less to
   // 3 % more, 0.7 % more in the mean (mixed 1 to 4 % less).
   const long long equal = cost;
-  for (long long r = (ntiles + slots - 1) / slots; two_sizes && r * 3 < cost; ++r) {
+  for (long long r = (ntiles + slots - 1) / slots; two_sizes && r * start < cost; ++r) {
     const long long n = r * slots / ntiles, more = r * slots - n * ntiles, fewer = ntiles - more;
     if (n >= nk) break;
     const int kl = (int)((nk + n - 1) / n), kc = (int)((nk + n) / (n + 1));
     if (more == 0 || kl == kc || kl > kmax || (nk + kl - 1) / kl != n || (nk + kc - 1) / kc != n + 1) continue;
     const long long lg = (fewer * n + slots - 1) / slots;  // long segments of the slowest block
-    const long long c = lg * kl + (r - lg) * kc + r * 3;
+    const long long c = lg * kl + (r - lg) * kc + r * start;
     if (c >= cost || 20 * c > 19 * equal) continue;
     cost = c;
     best.kc = kc;
@@ -922,7 +923,7 @@ Schedule stage_schedule(const Layout& L, const Machine& m) {
       return s;
     }
   }
-  return segment_schedule(ntiles, L.nk, m.cus * BPC, stage_kmax(L));
+  return segment_schedule(ntiles, L.nk, m.cus * BPC, stage_kmax(L), 2);
 }
 
 hipError_t launch_stage_fp64(hipStream_t s, const StageArgs& a, const double* Qin, const double* Q0, double* Qout,

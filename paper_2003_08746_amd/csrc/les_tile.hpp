@@ -28,13 +28,14 @@ struct Schedule {
 };
 
 // The schedule of nk planes of ntiles tiles on `slots` resident blocks, at
-// most kmax planes per segment.  A segment of n planes runs n + 2 iterations
-// (the planes below and above it) and about one more for its start, so the
-// time of a launch is that of its slowest block, block 0: the sum of n + 3
-// over its segments.  The number of chunks with the smallest sum is taken,
-// the fewest on ties.  With two_sizes, some tiles may take one chunk fewer than
-// the others, where no number of equal chunks fills the blocks' last round.
-Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, bool two_sizes = true);
+// most kmax planes per segment.  A segment of n planes runs n + halo iterations
+// (the planes before and after it that its kernel marches too) and about one
+// more for its start, so the time of a launch is that of its slowest block,
+// block 0: the sum of n + halo + 1 over its segments.  The number of chunks
+// with the smallest sum is taken, the fewest on ties.  With two_sizes, some
+// tiles may take one chunk fewer than the others, where no number of equal
+// chunks fills the blocks' last round.
+Schedule segment_schedule(long long ntiles, int nk, int slots, int kmax, int halo, bool two_sizes = true);
 
 // The tile and planes [k0, k1) of segment x.
 struct Segment {

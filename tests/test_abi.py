@@ -171,3 +171,28 @@ def test_march_offsets_in_range(n, bc, march):
         need = {"stage": 7, "adjoint flux": 7, "adjoint dissipation": 10}[march]
         assert (off is None) == (need * sk > 1 << 29), (off, sk)
         assert off is None or off < 1 << 29, (off, cus)
+
+
+@pytest.mark.parametrize("n,tiles,halo,march", [((411, 49, 298), 15 * 5, 4, "adjoint dissipation"),
+                                                ((391, 62, 29), 15 * 6, 4, "adjoint dissipation"),
+                                                ((411, 49, 298), 14 * 4, 2, "adjoint flux"),
+                                                ((128, 64, 64), 5 * 5, 2, "stage")])
+def test_schedule_minimises_the_slowest_block(n, tiles, halo, march):
+    """On periodic-i, Dirichlet-j, periodic-k blocks that take equal chunks, the
+    chunk length is the one whose slowest of 256 blocks marches the fewest
+    iterations: the planes of its segments, the planes around each that the
+    kernel marches too (halo) and one for each start; the longest on ties."""
+    g = lesmi.LesGrid()
+    g.ni, g.nj, g.nk = n
+    for d, b in enumerate((0, 1, 0)):
+        g.bc[d] = b
+    planes, first, last, _, _ = lesmi.les_debug_segments(g, _MARCHES[march], 256)
+    nk = last - first + 1
+
+    def slowest(kc):
+        chunks = [min(kc, nk - k) for k in range(0, nk, kc)]
+        segs = [c for c in chunks for _ in range(tiles)]
+        return sum(segs[s] + halo + 1 for s in range(0, len(segs), min(256, len(segs))))
+    # (the fewest planes that give a number of chunks)
+    lengths = sorted({-(-nk // m) for m in range(1, nk + 1)}, reverse=True)
+    assert planes == min(lengths, key=slowest)
