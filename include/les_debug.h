@@ -19,6 +19,12 @@ extern "C" {
  * LES_ERR_ARG for a null context. */
 int les_debug_use_reference(les_ctx *ctx, int on);
 
+/* on != 0: every ghost of every stage input is filled before the stage; on ==
+ * 0 (default): periodic ghosts are read at their source where the stage kernel
+ * can, and a stage buffer keeps its frozen ghosts within a call.  LES_ERR_ARG
+ * for a null context. */
+int les_debug_fill_ghosts(les_ctx *ctx, int on);
+
 /* use != 0: mixed stages take their metric terms from the context's FP32 copy
  * where it has one (default); use == 0: from the FP64 fields.  Returns 1 when
  * the context holds the copy, 0 when not (an FP64 context, or no memory for

@@ -74,6 +74,7 @@ struct les_ctx {
   double* outside = nullptr;         // [5][fe] outside state of characteristic faces
   int axis = 0;                      // j = 0 is the polar axis of an O-grid (bc[1] == LES_BC_AXIS)
   int use_m32 = 1;                   // 0: mixed stages take the FP64 metrics all the same
+  int fill_all = 0;                  // 1: every ghost filled before every stage
   int use_ref = 0;                   // 1: stage through the reference kernel
   les::Schedule sch;                 // segments of the fused kernel
   les::Machine mach;                 // CU and XCD counts of the device
@@ -538,7 +539,7 @@ int les_set_forcing(les_ctx* ctx, const double* f, int i_f) {
 static les::Wrap step_wrap(const les_ctx* c) {
   les::Wrap w;
   const int n[3] = {c->L.ni, c->L.nj, c->L.nk};
-  if (c->use_ref || c->bc[2] == 1 || (c->L.nk + 8) * c->L.sk >= 1LL << 29) return w;
+  if (c->use_ref || c->fill_all || c->bc[2] == 1 || (c->L.nk + 8) * c->L.sk >= 1LL << 29) return w;
   for (int d = 0; d < 3; ++d) w.per[d] = c->bc[d] == 0 ? n[d] : (c->bc[d] == 2 ? n[d] - 1 : 0);
   return w;
 }
@@ -588,7 +589,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
       float* out32 = (l < 4 || shadow_out) ? ctx->Sf[(l + par) & 1] : nullptr;
       if (l > 0 && ctx->axis) HIPCHK(ctx, les::launch_axis_avg_f32(ctx->s, L, (float*)in32));
       if (in32) {
-        const unsigned bit = 1u << ((l + 1 + par) & 1);
+        const unsigned bit = ctx->fill_all ? 0 : 1u << ((l + 1 + par) & 1);
         if (needs_fill(ctx, wrap, held & bit))
           HIPCHK(ctx, les::launch_ghost_fill_f32(ctx->s, L, ctx->bc, wrap, (float*)in32, held & bit ? nullptr : Q,
                                                  faces_of(ctx)));
@@ -614,7 +615,7 @@ static int step_core(les_ctx* ctx, double* Q, const double* dtp, double dt, doub
       double* out = l == 4 ? Q : (stage_ckpt ? stage_ckpt + (size_t)(l + 1) * 5 * fe : ctx->S[l & 1]);
       if (l > 0 && ctx->axis) HIPCHK(ctx, les::launch_axis_avg(ctx->s, L, (double*)in));
       if (l > 0 || stage_ckpt) {
-        const unsigned bit = l > 0 && !stage_ckpt ? 1u << ((l - 1) & 1) : 0;
+        const unsigned bit = l > 0 && !stage_ckpt && !ctx->fill_all ? 1u << ((l - 1) & 1) : 0;
         if (needs_fill(ctx, wrap, held & bit))
           HIPCHK(ctx, les::launch_ghost_fill(ctx->s, L, ctx->bc, wrap, (double*)in, held & bit ? nullptr : Q,
                                              faces_of(ctx)));
@@ -809,6 +810,13 @@ int les_probe_objective(les_ctx* ctx, const double* Q, int i_p, double p_inf, do
 int les_debug_use_reference(les_ctx* ctx, int on) {
   if (!ctx) return LES_ERR_ARG;
   ctx->use_ref = on ? 1 : 0;
+  return LES_OK;
+}
+
+// Steps with every ghost filled before every stage (les_debug.h).
+int les_debug_fill_ghosts(les_ctx* ctx, int on) {
+  if (!ctx) return LES_ERR_ARG;
+  ctx->fill_all = on ? 1 : 0;
   return LES_OK;
 }
 

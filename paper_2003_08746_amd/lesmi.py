@@ -125,6 +125,8 @@ def lib():
     L.les_debug_stage_time.argtypes = [_vp, _dp, ctypes.POINTER(ctypes.c_longlong)]
     L.les_debug_dynamic_coefficients.restype = ctypes.c_int
     L.les_debug_dynamic_coefficients.argtypes = [_vp, _vp, _vp]
+    L.les_debug_fill_ghosts.restype = ctypes.c_int
+    L.les_debug_fill_ghosts.argtypes = [_vp, ctypes.c_int]
     L.les_debug_metric_copy.restype = ctypes.c_int
     L.les_debug_metric_copy.argtypes = [_vp, ctypes.c_int]
     L.les_debug_segments.restype = ctypes.c_int
@@ -274,6 +276,10 @@ def les_stats_profiles(ctx, acc_ptr, samples, u_jet, core_frac, prof_ptr, core_p
 
 def les_debug_use_reference(ctx, on: bool):
     _check(lib().les_debug_use_reference(ctx, 1 if on else 0), ctx, "les_debug_use_reference")
+
+
+def les_debug_fill_ghosts(ctx, on: bool):
+    _check(lib().les_debug_fill_ghosts(ctx, 1 if on else 0), ctx, "les_debug_fill_ghosts")
 
 
 def les_debug_metric_copy(ctx, use=True) -> bool:
