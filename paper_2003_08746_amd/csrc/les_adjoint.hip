@@ -16,10 +16,11 @@
 //   dissipation pass (k_adj_diss): reverses the faces, radii and sensors and
 //      adds the flux pass's part.  Output nodes are the interior nodes and
 //      the ghost nodes that are images of interior nodes;
-//   fold (interior nodes with ghost images): adds the adjoint of every
-//      periodic ghost image to its interior node and pulls the adjoint of a
-//      boundary face's ghosts back to the face's boundary node through the
-//      face rule's Jacobian (frozen Dirichlet ghosts carry no dependence).
+//   faces (k_adj_face): pulls the adjoint of a boundary face's ghosts back to
+//      the face's boundary node through the face rule's Jacobian;
+//   fold (k_adj_fold, interior nodes with ghost images): adds the adjoint of
+//      every periodic or face ghost to its interior node (frozen Dirichlet
+//      ghosts carry no dependence).
 // Non-smooth points take the derivative of the active branch: d|x|/dx =
 // sign(x) with 0 at 0, max(a, b) follows a when a >= b, and the eddy
 // viscosity's |S| has derivative 0 at |S| = 0.
@@ -27,8 +28,8 @@
 // les_adjoint_step applies it stage by stage in reverse from the stage
 // inputs saved by les_rk_step: for l = 5..1, fbar += alpha_l dt qbar on the
 // source plane and qbar' = (dR/dQ|Q^(l-1))^T (-alpha_l dt qbar); finally Qbar
-// is the sum of all qbar.  The fbar update and the final sum run inside the
-// dissipation pass and the fold of the next (or last) stage.
+// is the sum of all qbar (k_adj_sum).  The fbar update runs inside the
+// dissipation pass and the fold of the stage whose result it takes.
 #include "les_adjoint.hpp"
 #include "les_tile.hpp"
 
@@ -44,17 +45,10 @@ enum {
   W_NF = 35
 };
 
-// Anisotropic scaling Lam_d and its partial derivatives w.r.t. (lam_d, lam_e, lam_f).
+// Anisotropic scaling Lam_d and its partial derivatives w.r.t. (lam_d, lam_e,
+// lam_f) for an exponent other than 1/2 (which k_adj_diss<true> takes by roots).
 __device__ __forceinline__ double aniso_d(double ld, double le, double lf, const Phys& P, double& dd, double& de,
                                           double& df) {
-  if (P.alpha_half) {
-    // Lam = ld + sqrt(ld) (sqrt(le) + sqrt(lf))
-    const double sd = sqrt_pos(ld), se = sqrt_pos(le), sf = sqrt_pos(lf);
-    dd = 1.0 + 0.5 * (se + sf) * rcp_nr(sd);
-    de = 0.5 * sd * rcp_nr(se);
-    df = 0.5 * sd * rcp_nr(sf);
-    return ld + sd * (se + sf);
-  }
   const double a = P.alpha;
   const double re = pow(le / ld, a), rf = pow(lf / ld, a);
   dd = 1.0 + (1.0 - a) * (re + rf);

@@ -10,8 +10,8 @@
 // * k_residual_ref / k_stage_ref: one thread per interior node evaluating the
 //   residual (Eq. 12-15 with Turkel-Vatsa dissipation) directly from global
 //   memory, recomputing every neighbour quantity.  It is the simple,
-//   structure-independent GPU formulation used by les_residual and to
-//   cross-check the fused stage kernel.
+//   structure-independent GPU formulation used by les_residual for an R off
+//   16-byte alignment and to cross-check the fused stage kernel.
 // * k_norm_final: RMS / max norms of R from per-block partials (FP64).
 // * k_probe: pressure-fluctuation objective on a plane and its gradient.
 // * k_stats: running sums of the primitives and their second moments over

@@ -22,7 +22,6 @@ hipError_t launch_ghost_fill_f32(hipStream_t s, const Layout& L, const int bc[3]
 hipError_t launch_stats(hipStream_t s, const Layout& L, const Phys& P, int nks, const double* Q, double* acc);
 hipError_t launch_stats_profiles(hipStream_t s, const Layout& L, const double* acc, double samples, double core_u,
                                  double* prof, unsigned char* core);
-// p[0 .. n) = 0 on stream s.
 // host (pinned) = scal[16], the flag (cleared), and dts[0 .. nd)
 constexpr int PUBLISH_FLAG = 16, PUBLISH_DTS = 17;
 hipError_t launch_publish(hipStream_t s, const double* scal, int* flag, const double* dts, int nd, double* host);

@@ -1,8 +1,8 @@
 // les_tile.hpp -- building blocks of the tiled gfx950 kernels that march a
 // 32 x 16 patch of nodes in k (the stage kernel, the adjoint passes and the
 // dynamic closure): segments and their schedule, periodic ghosts read at their
-// source, asynchronous row copies, counted waits, LDS-only barriers,
-// lane shifts and the schedule of (k chunk, tile) segments.
+// source, asynchronous row copies, counted waits, LDS-only barriers and lane
+// shifts.
 #pragma once
 #include "les_common.hpp"
 
