@@ -394,11 +394,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
       if (P.sgs) {
         const double musb = mtb + kapb * P.Cp_over_Prsgs;
         rb += musb * cd2 * Smag + pb * cid2 * ss;
-        double sb2 = 2.0 * pb * rho * cid2;
-        if (Smag > 0.0) sb2 += 2.0 * musb * rho * cd2 * rcp_nr(Smag);
-        // (a node whose flux no residual uses has no adjoint, and may have a
-        // strain of ghosts that nothing reads: its weights stay 0)
-        if (sb2 != 0.0) {
+        // (|S| > 0 fails for a NaN too: a node whose flux no residual uses may
+        // have a strain of ghosts that nothing reads, and its weights stay 0)
+        if (Smag > 0.0) {
+          const double sb2 = 2.0 * pb * rho * cid2 + 2.0 * musb * rho * cd2 * rcp_nr(Smag);
           Sb11 += S11 * sb2;
           Sb22 += S22 * sb2;
           Sb33 += S33 * sb2;
